@@ -44,7 +44,11 @@ constexpr int perm_row(int ci) { return (9 * perm_cip(ci) + 15) / 16 * 16 + 8; }
 constexpr int kPermW1 = (kNParam + 7) / 8 * 8;
 constexpr int kPermW2 = kPermW1 + kC1 * perm_row(kC0);
 constexpr int kPermW3 = kPermW2 + kC2 * perm_row(kC1);
-constexpr int kWbfElems = kPermW3 + kC3 * perm_row(kC2);
+// Then, for the backward kernels, the weights of layers 2 and 3 once more
+// as [tap][ci][co].
+constexpr int kBackW2 = kPermW3 + kC3 * perm_row(kC2);
+constexpr int kBackW3 = kBackW2 + 9 * kC1 * kC2;
+constexpr int kWbfElems = kBackW3 + 9 * kC2 * kC3;
 
 // Per-cell sums that pass 1 accumulates for every image (feature mode):
 // [image][2][kCellCount] (or [2][gy kCells][gx kCells] for one image whose
@@ -63,15 +67,13 @@ struct NetBuffers {
     const uint16_t *w;       // bfloat16 copy of the parameters (kWbfElems entries)
     const float *theta;      // FP32 parameters (biases, head)
     uint16_t *a1, *a2, *a3;  // ReLU outputs
-    uint16_t *g1, *g2, *g3;  // masked gradients w.r.t. the pre-activations
+    uint16_t *g1, *g2;       // masked gradients w.r.t. the pre-activations of layers 1 and 2
     float *gap;              // [B][32]
     float *logits;           // [B]
-    float *dz;               // [B] d loss / d logit
-    float *lossb;            // [B] per-sample loss
     const float *labels;     // [N] (indexed through idx)
     float *grad;             // [kNParam]
     float *loss;             // [1] mean loss, or nullptr
-    float *partial;          // split-K partial weight gradients
+    float *partial;          // partial weight gradients, one set per workgroup and layer
     int B;
 };
 
@@ -79,6 +81,7 @@ struct NetBuffers {
 constexpr long long act_elems(int B) {
     return (long long)B * (kC1 * kH1 * kH1 + kC2 * kH2 * kH2 + kC3 * kH3 * kH3);
 }
+constexpr long long gact_elems(int B) { return (long long)B * (kC1 * kH1 * kH1 + kC2 * kH2 * kH2); }
 long long partial_elems(int B);
 
 struct AdamArgs {

@@ -6,12 +6,11 @@
 // (3 -> 16 -> 32 -> 32 channels, 128 -> 64 -> 32 -> 16), ReLU after each,
 // global average pooling and a linear layer to one logit.  The convolutions
 // run as implicit GEMMs on v_mfma_f32_16x16x16_bf16 with FP32 accumulation:
-// forward, a workgroup stages its input rows and the weights in LDS; the
-// backward kernels gather their operands from the activation maps, one
-// wave per 16 x (all channels) block.  Stored activations and their
+// forward, a workgroup stages its input rows and the weights in LDS;
+// backward, a band of the layer's input and of its output gradient.  Stored activations and their
 // gradients are bfloat16; biases, the head, the loss and AdamW are FP32.
-// Every reduction has a fixed order (split-K partials are summed in split
-// order, no float atomics), so a training step is deterministic.
+// Every reduction has a fixed order (the workgroups' partial weight gradients are
+// summed in a fixed order, no float atomics), so a training step is deterministic.
 #include "logfx_gate.h"
 
 namespace logfx {
@@ -20,6 +19,8 @@ namespace {
 
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef short short8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 __device__ inline uint16_t to_bf16(float f) {
     // round to nearest, ties to even (finite values)
@@ -35,12 +36,15 @@ __device__ inline f32x4 mfma(const bf16x4 &a, const bf16x4 &b, const f32x4 &d) {
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, d, 0, 0, 0);
 }
 
+// The same on a 32-deep block: lane l = 16 q + c holds A(c, 8q + i) and
+// B(8q + i, c) for i = 0..7.
+__device__ inline f32x4 mfma32(const bf16x8 &a, const bf16x8 &b, const f32x4 &d) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, d, 0, 0, 0);
+}
+
 template <int CI, int CO, int HI>
 struct Geo {
     static constexpr int HO = HI / 2, HWI = HI * HI, HWO = HO * HO;
-    static constexpr int K = CI * 9, KP = (K + 15) / 16 * 16;   // weights per output channel
-    static constexpr int NW1 = K + 1;                            // weight-gradient columns + bias
-    static constexpr int NT = (NW1 + 15) / 16;                   // 16-column tiles of them
     static constexpr int MB = CO / 16;
     static_assert(CO % 16 == 0 && HWO % 16 == 0, "layer shape");
 };
@@ -222,162 +226,370 @@ __global__ __launch_bounds__(256) void head_fwd(const uint16_t *__restrict__ a3,
 }
 
 // ---------------------------------------------------------------- backward
-// dz = (sigmoid(z) - y) / B, the per-sample loss, and the masked gradient
-// of the last convolution: g3 = bf16(dz wf[c] / 256) where a3 > 0.
-__global__ __launch_bounds__(256) void head_bwd(NetBuffers n) {
-    constexpr int HW = kH3 * kH3;
-    const int b = blockIdx.x;
-    const float z = n.logits[b];
-    const float y = n.labels[n.idx ? n.idx[b] : b];
-    const float dz = (1.0f / (1.0f + expf(-z)) - y) / (float)n.B;
-    if (threadIdx.x == 0) {
-        n.dz[b] = dz;
-        n.lossb[b] = fmaxf(z, 0.0f) - z * y + log1pf(expf(-fabsf(z)));
-    }
-    for (int i = threadIdx.x; i < kC3 * HW; i += blockDim.x) {
-        const long long at = (long long)b * kC3 * HW + i;
-        const float d = dz * n.theta[kOffWf + i / HW] / (float)HW;
-        n.g3[at] = n.a3[at] != 0 ? to_bf16(d) : (uint16_t)0;
-    }
+// d loss / d logit of batch row b: (sigmoid(z) - y) / B.
+__device__ inline float dlogit(const NetBuffers &n, int b) {
+    return (1.0f / (1.0f + expf(-n.logits[b])) - n.labels[n.idx ? n.idx[b] : b]) / (float)n.B;
 }
 
-// Head gradients and the mean loss: one wave, samples in order.
-__global__ __launch_bounds__(64) void head_grad(NetBuffers n) {
-    const int c = threadIdx.x;
-    if (c < kC3) {
-        float s = 0.0f;
-        for (int b = 0; b < n.B; ++b) s += n.gap[b * kC3 + c] * n.dz[b];
-        n.grad[kOffWf + c] = s;
-    }
-    if (c == 0) {
-        float s = 0.0f, l = 0.0f;
-        for (int b = 0; b < n.B; ++b) {
-            s += n.dz[b];
-            l += n.lossb[b];
+// A band of the input of a stride-2 convolution in LDS, one plane per kernel
+// column kx: plane (kx, ci) holds in[ci][2 oy0 - 1 + r][2 u + kx - 1] at
+// r HO + u, r = 0 .. 2 TH.  The pixels that consecutive output columns u
+// read through one tap are then consecutive, so eight of them are one
+// 16-byte LDS read.  A plane takes an odd number of 16-byte units: lanes on
+// neighbouring channels (or taps) read different banks.
+template <int CI, int HI, int TH>
+struct Planes {
+    static constexpr int HO = HI / 2, R = 2 * TH + 1;
+    static constexpr int STR = (R * HO / 8 + 1 - (R * HO / 8) % 2) * 8;   // elements per plane
+    static constexpr int ELEMS = 3 * CI * STR;
+    static_assert(HO % 8 == 0 && HI % 8 == 0, "whole 16-byte units");
+    // Fills the planes from the image at `ib`: eight input pixels and the
+    // one to their left per item, U items' loads in flight.
+    static __device__ void fill(uint16_t *pl, const uint16_t *__restrict__ ib, int oy0, int t) {
+        typedef uint32_t u32x4a2 __attribute__((ext_vector_type(4), aligned(2)));
+        constexpr int XC = HI / 8, N = CI * R * XC, U = (N + 255) / 256 < 9 ? (N + 255) / 256 : 9;
+        for (int i0 = t; i0 < N; i0 += 256 * U) {
+            u32x4a2 v[U];
+            uint32_t lf[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int it = i0 + 256 * k, xc = it % XC, rc = it / XC, r = rc % R, ci = rc / R;
+                const int iy = 2 * oy0 - 1 + r;
+                v[k] = u32x4a2{0u, 0u, 0u, 0u};
+                lf[k] = 0u;
+                if (it < N && iy >= 0) {
+                    const uint16_t *p = ib + (long long)ci * HI * HI + iy * HI + 8 * xc;
+                    v[k] = *reinterpret_cast<const u32x4a2 *>(p);
+                    if (xc > 0) lf[k] = p[-1];
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int it = i0 + 256 * k, xc = it % XC, rc = it / XC, r = rc % R, ci = rc / R;
+                if (it >= N) break;
+                const uint32_t e0 = (v[k].x & 0xFFFFu) | (v[k].y << 16), e1 = (v[k].z & 0xFFFFu) | (v[k].w << 16);
+                const uint32_t o0 = (v[k].x >> 16) | (v[k].y & 0xFFFF0000u), o1 = (v[k].z >> 16) | (v[k].w & 0xFFFF0000u);
+                uint16_t *q = pl + ci * STR + r * HO + 4 * xc;
+                *reinterpret_cast<uint2 *>(q) = make_uint2(lf[k] | (o0 << 16), (o0 >> 16) | (o1 << 16));
+                *reinterpret_cast<uint2 *>(q + CI * STR) = make_uint2(e0, e1);
+                *reinterpret_cast<uint2 *>(q + 2 * CI * STR) = make_uint2(o0, o1);
+            }
         }
-        n.grad[kOffBf] = s;
-        if (n.loss) n.loss[0] = l / (float)n.B;
     }
-}
+};
 
-// gin[b][ci][y][x] = bf16(sum_{co,ky,kx} w[co][ci][ky][kx] g[b][co][oy][ox]) where act[b][ci][y][x] > 0,
-// over (oy, ox) with y = 2oy + ky - 1, x = 2ox + kx - 1.  GEMM rows = ci,
-// columns = 16 input pixels, reduction over (co, ky, kx).
-template <int CI, int CO, int HI>
-__global__ __launch_bounds__(256) void conv_bwd_data(const uint16_t *__restrict__ g, const uint16_t *__restrict__ w,
-                                                     const uint16_t *__restrict__ act, uint16_t *__restrict__ gin,
-                                                     int B) {
-    using G = Geo<CI, CO, HI>;
-    constexpr int PB = G::HWI / 16, K = CO * 9, MB = CI / 16;
-    static_assert(CI % 16 == 0, "input channels");
-    const int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + threadIdx.x / 64);
-    if (wave >= B * PB) return;
-    const int b = wave / PB, p0 = (wave % PB) * 16;
-    const int l = threadIdx.x & 63, q = l >> 4, c = l & 15;
-    const int p = p0 + c, y = p / HI, x = p % HI;
-    const uint16_t *gb = g + (long long)b * CO * G::HWO;
-    f32x4 acc[MB];
+// Partial sums of a layer's weight gradient, one set per workgroup:
+// [co][tap][ci], then the biases [co].
+template <int CI, int CO> constexpr int kGradSet = CO * (9 * CI + 1);
+
+// Workgroups of a backward kernel: each walks items g, g + groups, ... and
+// keeps its weight-gradient sums in registers, so that the partial sums the
+// reduction reads stay at 29 MB however large the batch is.  512 workgroups
+// are two per CU; at batch 256 they take 1 item each (layer 3) and 4 (layers
+// 2 and 1).  Layer 2 took 32 us with 512, 38 with 768 (a last round of
+// items on a third of them); bands of 8 rows there, one workgroup per CU, 52.
+constexpr int kBwdGroups = 512;
+constexpr int kBand3 = 8, kBand2 = 4, kBand1 = 8;   // output rows per item
+constexpr int bwd_groups(int B, int ho, int th) { return B * (ho / th) < kBwdGroups ? B * (ho / th) : kBwdGroups; }
+
+// Backward of one layer with 32 output channels: the weight and bias
+// gradient, and the data gradient gin[b][ci][y][x] = bf16(sum_{co,ky,kx}
+// w[co][ci][ky][kx] g[b][co][oy][ox]) where act[b][ci][y][x] > 0, over
+// (oy, ox) with y = 2 oy + ky - 1, x = 2 ox + kx - 1.
+//
+// An item is a band of TH output rows of one sample.  Its gradient rows
+// (and the row below, which the band's odd input rows read) and the band of
+// the layer's input are staged in LDS once and serve both products:
+//  * weight gradient: rows = co, columns = 16 input channels at one tap,
+//    reduction over the band's output pixels, 32 per MFMA; both operands
+//    are eight consecutive pixels, one 16-byte LDS read.  The tiles of
+//    (tap, 16 channels) are dealt to the four waves.
+//  * data gradient: the input pixels of one parity class (y mod 2, x mod 2)
+//    read the same taps -- 1, 2, 2 and 4 of the nine -- so each class is a
+//    dense product of 16 pixels x 32 output channels per tap: nine MFMAs
+//    give 64 input pixels, and no product with a zero is formed.
+// The gather form this replaces (2-byte global loads per operand element,
+// the nine taps over all pixels) took 89 + 41 us (layer 3) and 209 + 105 us
+// (layer 2) on 256 samples, this one 28 and 32 us; the bytes alone take 5
+// and 13 us.  More loads in flight change nothing: the LDS traffic of the
+// staging and the operands, two or three workgroups per CU, bounds it.
+// HEAD: g is the last layer's gradient, bf16(dz wf[c] / 256) where a3 > 0,
+// formed from the activations `g` while they are staged.
+template <int CI, int HI, int TH, bool HEAD>
+__global__ __launch_bounds__(256) void conv_bwd(NetBuffers n, const uint16_t *__restrict__ g,
+                                                const uint16_t *__restrict__ act, const uint16_t *__restrict__ wd,
+                                                uint16_t *__restrict__ gin, float *__restrict__ partial) {
+    constexpr int CO = 32, HO = HI / 2, BANDS = HO / TH, PX = TH * HO;
+    constexpr int MB = CI / 16, NT = 9 * MB, TPW = (NT + 1 + 3) / 4;   // column tiles (and the bias) per wave
+    using PL = Planes<CI, HI, TH>;
+    constexpr int GPS = PX + 8;        // pixel-innermost gradient rows: an odd number of 16-byte units
+    constexpr int GCS = CO + 8;        // channel-innermost pixels: 5 units
+    static_assert(PX % 32 == 0 && (PX / 8) % 2 == 0 && HO % 16 == 0 && (TH * HO / 16) % 4 == 0, "band shape");
+    __shared__ __align__(16) uint16_t pl[PL::ELEMS];
+    __shared__ __align__(16) uint16_t gp[CO * GPS];
+    __shared__ __align__(16) uint16_t gc[(TH + 1) * (HO + 1) * GCS];
+    const int t = threadIdx.x, l = t & 63, q = l >> 4, c = l & 15;
+    const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    f32x4 acc[TPW][2];
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-    for (int kb = 0; kb < K; kb += 16) {
-        bf16x4 bv;
+    for (int j = 0; j < TPW; ++j) acc[j][0] = acc[j][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 wa[9][MB];                  // the data gradient's weights: rows = ci, reduction over co
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int k = kb + 4 * q + i;
-            const int co = k / 9, t = k - 9 * co, ky = t / 3, kx = t - 3 * ky;
-            const int ty = y + 1 - ky, tx = x + 1 - kx;
-            const bool ok = ty >= 0 && tx >= 0 && !(ty & 1) && !(tx & 1) && ty < HI && tx < HI;
-            bv[i] = ok ? (short)gb[co * G::HWO + (ty >> 1) * G::HO + (tx >> 1)] : (short)0;
+    for (int tap = 0; tap < 9; ++tap)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+            wa[tap][mb] = *reinterpret_cast<const bf16x8 *>(wd + (tap * CI + 16 * mb + c) * CO + 8 * q);
+
+    for (int item = blockIdx.x; item < n.B * BANDS; item += gridDim.x) {
+        const int b = item / BANDS, oy0 = (item % BANDS) * TH;
+        PL::fill(pl, act + (long long)b * CI * HI * HI, oy0, t);
+        // gradient rows oy0 .. oy0 + TH, four pixels of four channels per item
+        constexpr int XQ = HO / 4, NG = (CO / 4) * (TH + 1) * XQ;
+        const float dz = HEAD ? dlogit(n, b) : 0.0f;
+        for (int it = t; it < NG; it += 256) {
+            const int xq = it % XQ, rg = it / XQ, r = rg % (TH + 1), c4 = rg / (TH + 1);
+            uint2 v[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                v[j] = make_uint2(0u, 0u);
+                if (oy0 + r < HO) {
+                    v[j] = *reinterpret_cast<const uint2 *>(g + ((long long)b * CO + 4 * c4 + j) * HO * HO +
+                                                            (oy0 + r) * HO + 4 * xq);
+                    if constexpr (HEAD) {
+                        const uint32_t d = to_bf16(dz * n.theta[kOffWf + 4 * c4 + j] / (float)(kH3 * kH3));
+                        v[j].x = ((v[j].x & 0xFFFFu) ? d : 0u) | ((v[j].x >> 16) ? d << 16 : 0u);
+                        v[j].y = ((v[j].y & 0xFFFFu) ? d : 0u) | ((v[j].y >> 16) ? d << 16 : 0u);
+                    }
+                }
+                if (r < TH) *reinterpret_cast<uint2 *>(gp + (4 * c4 + j) * GPS + r * HO + 4 * xq) = v[j];
+            }
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const int sh = 16 * (p & 1);
+                uint32_t w[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) w[j] = ((p < 2 ? v[j].x : v[j].y) >> sh) & 0xFFFFu;
+                *reinterpret_cast<uint2 *>(gc + (r * (HO + 1) + 4 * xq + p) * GCS + 4 * c4) =
+                    make_uint2(w[0] | (w[1] << 16), w[2] | (w[3] << 16));
+            }
         }
+        // column HO of the gradient: zero
+        for (int it = t; it < (TH + 1) * (CO / 4); it += 256)
+            *reinterpret_cast<uint2 *>(gc + ((it / (CO / 4)) * (HO + 1) + HO) * GCS + 4 * (it % (CO / 4))) =
+                make_uint2(0u, 0u);
+        __syncthreads();
+
+        // weight gradient
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            bf16x4 av;
+        for (int kb = 0; kb < PX / 32; ++kb) {
+            const int p = 32 * kb + 8 * q, oy = p / HO, ox = p % HO;   // the lane's eight pixels
+            bf16x8 av[2];
+#pragma unroll
+            for (int m = 0; m < 2; ++m) av[m] = *reinterpret_cast<const bf16x8 *>(gp + (16 * m + c) * GPS + p);
+#pragma unroll
+            for (int j = 0; j < TPW; ++j) {
+                const int tile = wv + 4 * j;   // wave-uniform
+                bf16x8 bv;
+                if (tile < NT) {
+                    const int tap = tile / MB, h = tile - tap * MB, ky = tap / 3, kx = tap - 3 * ky;
+                    bv = *reinterpret_cast<const bf16x8 *>(pl + (kx * CI + 16 * h + c) * PL::STR + (2 * oy + ky) * HO + ox);
+                } else {
+                    const short one = tile == NT && c == 0 ? 0x3F80 : 0;   // 1.0: the bias
+                    const short8 o = {one, one, one, one, one, one, one, one};
+                    bv = __builtin_bit_cast(bf16x8, o);
+                }
+#pragma unroll
+                for (int m = 0; m < 2; ++m) acc[j][m] = mfma32(av[m], bv, acc[j][m]);
+            }
+        }
+        // data gradient: jobs of 16 columns u of one row v
+        constexpr int UB = HO / 16, JOBS = TH * UB;
+        for (int job = wv; job < JOBS; job += 4) {
+            const int v = job / UB, u = (job % UB) * 16 + c;   // v relative to oy0
+            f32x4 d[2][2][MB];
+#pragma unroll
+            for (int k = 0; k < 4 * MB; ++k) d[k >> 1 & 1][k & 1][k >> 2] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int tap = 0; tap < 9; ++tap) {
+                const int ky = tap / 3, kx = tap - 3 * ky;
+                const bf16x8 bv = *reinterpret_cast<const bf16x8 *>(
+                    gc + ((v + (ky == 0)) * (HO + 1) + u + (kx == 0)) * GCS + 8 * q);
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) d[ky != 1][kx != 1][mb] = mfma32(wa[tap][mb], bv, d[ky != 1][kx != 1][mb]);
+            }
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int py = 0; py < 2; ++py)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int ci = 16 * mb + 4 * q + i;
+                        const uint16_t *a = pl + (CI + ci) * PL::STR + (2 * v + py + 1) * HO + u;
+                        const uint32_t e = a[0] != 0 ? to_bf16(d[py][0][mb][i]) : 0u;
+                        const uint32_t o = a[CI * PL::STR] != 0 ? to_bf16(d[py][1][mb][i]) : 0u;
+                        *reinterpret_cast<uint32_t *>(gin + (((long long)b * CI + ci) * HI + 2 * (oy0 + v) + py) * HI + 2 * u) =
+                            e | (o << 16);
+                    }
+        }
+        __syncthreads();   // the staged band is replaced by the next item's
+    }
+    float *set = partial + (long long)blockIdx.x * kGradSet<CI, CO>;
+#pragma unroll
+    for (int j = 0; j < TPW; ++j) {
+        const int tile = wv + 4 * j;
+        const int tap = tile / MB, h = tile - tap * MB;
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int k = kb + 4 * q + i;
-                const int co = k / 9, t = k - 9 * co;
-                av[i] = (short)w[(co * CI + mb * 16 + c) * 9 + t];
+                const int co = 16 * m + 4 * q + i;
+                if (tile < NT) set[(co * 9 + tap) * CI + 16 * h + c] = acc[j][m][i];
+                else if (tile == NT && c == 0) set[CO * 9 * CI + co] = acc[j][m][i];
             }
-            acc[mb] = mfma(av, bv, acc[mb]);
-        }
     }
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int ci = mb * 16 + 4 * q + i;
-            const long long at = ((long long)b * CI + ci) * G::HWI + p;
-            gin[at] = act[at] != 0 ? to_bf16(acc[mb][i]) : (uint16_t)0;
-        }
 }
 
-// Weight and bias gradients, one split of the reduction per sample:
-// partial[b][co][n] = sum over the output pixels of sample b of
-// g[b][co][p] * X(p, n), X(p, n) = in[b][ci][2oy+ky-1][2ox+kx-1] for
-// n = (ci, ky, kx) < CI*9 and X = 1 for n = CI*9 (the bias).
-template <int CI, int CO, int HI>
-__global__ __launch_bounds__(256) void conv_bwd_weight(const uint16_t *__restrict__ g, const uint16_t *__restrict__ in,
-                                                       const int *__restrict__ idx, float *__restrict__ partial,
-                                                       int B) {
-    using G = Geo<CI, CO, HI>;
-    const int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + threadIdx.x / 64);
-    if (wave >= B * G::NT) return;
-    const int b = wave / G::NT, n0 = (wave % G::NT) * 16;
-    const int l = threadIdx.x & 63, q = l >> 4, c = l & 15;
-    const int n = n0 + c;
-    const int ci = n / 9, t = n - 9 * ci, ky = t / 3, kx = t - 3 * ky;
-    const uint16_t *ib = in + (long long)(idx ? idx[b] : b) * CI * G::HWI + (n < G::K ? ci * G::HWI : 0);
-    const uint16_t *gb = g + (long long)b * CO * G::HWO;
-    f32x4 acc[G::MB];
+// Weight and bias gradient of the first layer (3 input channels, no data
+// gradient): rows = the 16 output channels, columns = the 27 (ci, tap)
+// pairs and the bias, reduction over the pixels of a band of TH output
+// rows, each wave a quarter of them.  The gradient operand is eight
+// consecutive pixels of a channel straight from memory.  256 samples: 13 us
+// (the 59 MB it reads take 11), 128 us with gathered operands before.
+template <int TH>
+__global__ __launch_bounds__(256) void conv1_bwd(NetBuffers n, float *__restrict__ partial) {
+    constexpr int CI = kC0, CO = kC1, HI = kH0, HO = kH1, BANDS = HO / TH, KB = TH * HO / 32 / 4;
+    using PL = Planes<CI, HI, TH>;
+    static_assert(CO == 16 && 9 * CI + 1 <= 32 && TH * HO % 128 == 0 && HO % 32 == 0, "layer shape");
+    __shared__ __align__(16) uint16_t pl[PL::ELEMS];
+    __shared__ float red[3][64][8];
+    const int t = threadIdx.x, l = t & 63, q = l >> 4, c = l & 15;
+    const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+    // the lane's two columns: n = ci 9 + tap, 27 = the bias, above: nothing
+    int at[2];
+    short pad[2];
 #pragma unroll
-    for (int mb = 0; mb < G::MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-    for (int kb = 0; kb < G::HWO; kb += 16) {
-        bf16x4 bv;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int p = kb + 4 * q + i, oy = p / G::HO, ox = p % G::HO;
-            const int iy = 2 * oy + ky - 1, ix = 2 * ox + kx - 1;
-            short v = 0;
-            if (n < G::K) v = (iy >= 0 && ix >= 0) ? (short)ib[iy * HI + ix] : (short)0;
-            else if (n == G::K) v = (short)0x3F80;   // 1.0
-            bv[i] = v;
-        }
-#pragma unroll
-        for (int mb = 0; mb < G::MB; ++mb) {
-            // four consecutive pixels of channel mb*16 + c: one 8-byte load
-            const bf16x4 av = *reinterpret_cast<const bf16x4 *>(gb + (mb * 16 + c) * G::HWO + kb + 4 * q);
-            acc[mb] = mfma(av, bv, acc[mb]);
-        }
+    for (int j = 0; j < 2; ++j) {
+        const int col = 16 * j + c, ci = col / 9, tap = col - 9 * ci, ky = tap / 3, kx = tap - 3 * ky;
+        at[j] = col < 9 * CI ? (kx * CI + ci) * PL::STR + ky * HO : -1;
+        pad[j] = col == 9 * CI ? 0x3F80 : 0;
     }
-    if (n >= G::NW1) return;
+    for (int item = blockIdx.x; item < n.B * BANDS; item += gridDim.x) {
+        const int b = item / BANDS, oy0 = (item % BANDS) * TH;
+        const uint16_t *gb = n.g1 + ((long long)b * CO + c) * HO * HO + oy0 * HO;
+        bf16x8 av[KB];
 #pragma unroll
-    for (int mb = 0; mb < G::MB; ++mb)
+        for (int k = 0; k < KB; ++k) av[k] = *reinterpret_cast<const bf16x8 *>(gb + 32 * (wv * KB + k) + 8 * q);
+        PL::fill(pl, n.x0 + (long long)(n.idx ? n.idx[b] : b) * CI * HI * HI, oy0, t);
+        __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int co = mb * 16 + 4 * q + i;
-            partial[((long long)b * CO + co) * G::NW1 + n] = acc[mb][i];
+        for (int k = 0; k < KB; ++k) {
+            const int p = 32 * (wv * KB + k) + 8 * q, oy = p / HO, ox = p % HO;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const short8 o = {pad[j], pad[j], pad[j], pad[j], pad[j], pad[j], pad[j], pad[j]};
+                bf16x8 bv = __builtin_bit_cast(bf16x8, o);
+                if (at[j] >= 0) bv = *reinterpret_cast<const bf16x8 *>(pl + at[j] + 2 * oy * HO + ox);
+                acc[j] = mfma32(av[k], bv, acc[j]);
+            }
         }
+        __syncthreads();
+    }
+    // the four waves' sums, in wave order
+    if (wv > 0) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) red[wv - 1][l][k] = acc[k >> 2][k & 3];
+    }
+    __syncthreads();
+    if (wv > 0) return;
+    float *set = partial + (long long)blockIdx.x * kGradSet<CI, CO>;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        float s = acc[k >> 2][k & 3];
+#pragma unroll
+        for (int w = 0; w < 3; ++w) s += red[w][l][k];
+        const int col = 16 * (k >> 2) + c, co = 4 * q + (k & 3), ci = col / 9;
+        if (col < 9 * CI) set[(co * 9 + col - 9 * ci) * CI + ci] = s;
+        else if (col == 9 * CI) set[CO * 9 * CI + co] = s;
+    }
 }
 
-// Sum the per-sample partials in sample order into the flat gradient.
+// The gradient from the partial sums, and the head's gradient and the mean
+// loss from the logits.  32 parameters per workgroup: 32 threads each
+// add every 32nd set in order, and their sums are added in order, so the
+// result does not depend on timing.  15 us at batch 256, with all of a
+// thread's loads in flight; one thread per parameter walking all sets, and
+// one wave walking the samples for the head, took 60 us a layer and 79 us
+// (8 threads per parameter: 26 us in all).
+constexpr int kRedCols = 32, kRedWays = 32;
 template <int CI, int CO>
-__global__ __launch_bounds__(256) void reduce_weight(const float *__restrict__ partial, float *__restrict__ grad,
-                                                     int offw, int offb, int B) {
-    constexpr int NW = CI * 9, NW1 = NW + 1;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= CO * NW1) return;
+__device__ void reduce_layer(const float *__restrict__ partial, float *__restrict__ grad, int offw, int offb, int sets,
+                             int block, float (*sum)[kRedCols]) {
+    constexpr int SET = kGradSet<CI, CO>;
+    const int k = threadIdx.x % kRedCols, way = threadIdx.x / kRedCols, i = block * kRedCols + k;
     float s = 0.0f;
-    for (int b = 0; b < B; ++b) s += partial[(long long)b * CO * NW1 + i];
-    const int co = i / NW1, n = i - co * NW1;
-    if (n < NW) grad[offw + co * NW + n] = s;
-    else grad[offb + co] = s;
+    if (i < SET) {
+#pragma unroll 16
+        for (int w = way; w < sets; w += kRedWays) s += partial[(long long)w * SET + i];
+    }
+    sum[way][k] = s;
+    __syncthreads();
+    if (way != 0 || i >= SET) return;
+#pragma unroll
+    for (int w = 1; w < kRedWays; ++w) s += sum[w][k];
+    const int co = i / (9 * CI), tap = (i - co * 9 * CI) / CI, ci = i % CI;
+    if (i < CO * 9 * CI) grad[offw + (co * CI + ci) * 9 + tap] = s;
+    else grad[offb + i - CO * 9 * CI] = s;
+}
+__device__ void reduce_head(const NetBuffers &n, float (*sum)[kRedCols]) {
+    __shared__ float sdz[kRedWays], sl[kRedWays];
+    const int c = threadIdx.x % kRedCols, way = threadIdx.x / kRedCols;
+    float s = 0.0f, d = 0.0f, lo = 0.0f;
+    for (int b = way; b < n.B; b += kRedWays) {
+        const float dz = dlogit(n, b), z = n.logits[b], y = n.labels[n.idx ? n.idx[b] : b];
+        s += n.gap[b * kC3 + c] * dz;
+        d += dz;
+        lo += fmaxf(z, 0.0f) - z * y + log1pf(expf(-fabsf(z)));
+    }
+    sum[way][c] = s;
+    if (c == 0) {
+        sdz[way] = d;
+        sl[way] = lo;
+    }
+    __syncthreads();
+    if (way != 0) return;
+#pragma unroll
+    for (int w = 1; w < kRedWays; ++w) s += sum[w][c];
+    n.grad[kOffWf + c] = s;
+    if (c == 0) {
+#pragma unroll
+        for (int w = 1; w < kRedWays; ++w) {
+            d += sdz[w];
+            lo += sl[w];
+        }
+        n.grad[kOffBf] = d;
+        if (n.loss) n.loss[0] = lo / (float)n.B;
+    }
+}
+constexpr int red_blocks(int set) { return (set + kRedCols - 1) / kRedCols; }
+constexpr int kRed3 = red_blocks(kGradSet<kC2, kC3>), kRed2 = red_blocks(kGradSet<kC1, kC2>),
+              kRed1 = red_blocks(kGradSet<kC0, kC1>);
+static_assert(kC3 == kRedCols, "one column per head weight");
+__global__ __launch_bounds__(kRedCols * kRedWays) void reduce_grad(NetBuffers n, const float *p3, const float *p2, const float *p1,
+                                                   int s3, int s2, int s1) {
+    __shared__ float sum[kRedWays][kRedCols];
+    const int b = blockIdx.x;   // uniform over the workgroup
+    if (b < kRed3) reduce_layer<kC2, kC3>(p3, n.grad, kOffW3, kOffB3, s3, b, sum);
+    else if (b < kRed3 + kRed2) reduce_layer<kC1, kC2>(p2, n.grad, kOffW2, kOffB2, s2, b - kRed3, sum);
+    else if (b < kRed3 + kRed2 + kRed1) reduce_layer<kC0, kC1>(p1, n.grad, kOffW1, kOffB1, s1, b - kRed3 - kRed2, sum);
+    else reduce_head(n, sum);
 }
 
 // ---------------------------------------------------------------- AdamW
 // Index in the bfloat16 copy of parameter i's second place, in the forward
-// layout of its convolution's weights, or -1 for biases and the head.
+// layout of its convolution's weights, or -1 for biases and the head; and of
+// its third, in the data gradient's layout ([tap][ci][co], layers 2 and 3),
+// or -1.
 template <int CI>
 __device__ inline int forward_at_layer(int n, int perm) {
     const int co = n / (CI * 9), k = n - co * CI * 9, ci = k / 9, tap = k - 9 * ci;
@@ -388,6 +600,24 @@ __device__ inline int forward_at(int i) {
     if (i >= kOffW2 && i < kOffB2) return forward_at_layer<kC1>(i - kOffW2, kPermW2);
     if (i >= kOffW3 && i < kOffB3) return forward_at_layer<kC2>(i - kOffW3, kPermW3);
     return -1;
+}
+
+template <int CI, int CO>
+__device__ inline int backward_at_layer(int n, int perm) {
+    const int co = n / (CI * 9), k = n - co * CI * 9, ci = k / 9, tap = k - 9 * ci;
+    return perm + (tap * CI + ci) * CO + co;
+}
+__device__ inline int backward_at(int i) {
+    if (i >= kOffW2 && i < kOffB2) return backward_at_layer<kC1, kC2>(i - kOffW2, kBackW2);
+    if (i >= kOffW3 && i < kOffB3) return backward_at_layer<kC2, kC3>(i - kOffW3, kBackW3);
+    return -1;
+}
+__device__ inline void store_bf16(uint16_t *wbf, int i, float v) {
+    const uint16_t h = to_bf16(v);
+    wbf[i] = h;
+    const int f = forward_at(i), b = backward_at(i);
+    if (f >= 0) wbf[f] = h;
+    if (b >= 0) wbf[b] = h;
 }
 
 // Decoupled weight decay on every parameter; refreshes the bfloat16 copy.
@@ -402,19 +632,13 @@ __global__ __launch_bounds__(256) void adamw(AdamArgs a) {
     const float p = a.theta[i];
     const float np = p - a.lr * ((m / a.bc1) / (sqrtf(v / a.bc2) + a.eps) + a.wd * p);
     a.theta[i] = np;
-    const uint16_t h = to_bf16(np);
-    a.wbf[i] = h;
-    const int j = forward_at(i);
-    if (j >= 0) a.wbf[j] = h;
+    store_bf16(a.wbf, i, np);
 }
 
 __global__ __launch_bounds__(256) void params_to_bf16(const float *theta, uint16_t *wbf) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= kNParam) return;
-    const uint16_t h = to_bf16(theta[i]);
-    wbf[i] = h;
-    const int j = forward_at(i);
-    if (j >= 0) wbf[j] = h;
+    store_bf16(wbf, i, theta[i]);
 }
 
 // ---------------------------------------------------------------- features
@@ -492,34 +716,12 @@ hipError_t fwd(const uint16_t *in, const int *idx, const uint16_t *w, const floa
     return hipGetLastError();
 }
 
-template <int CI, int CO, int HI>
-hipError_t bwd_weight(const uint16_t *g, const uint16_t *in, const int *idx, float *partial, float *grad, int offw,
-                      int offb, int B, hipStream_t s) {
-    using G = Geo<CI, CO, HI>;
-    hipLaunchKernelGGL((conv_bwd_weight<CI, CO, HI>), dim3(blocks((long long)B * G::NT, 4)), dim3(256), 0, s, g, in,
-                       idx, partial, B);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((reduce_weight<CI, CO>), dim3(blocks(CO * G::NW1, 256)), dim3(256), 0, s, partial, grad, offw,
-                       offb, B);
-    return hipGetLastError();
-}
-
-template <int CI, int CO, int HI>
-hipError_t bwd_data(const uint16_t *g, const uint16_t *w, const uint16_t *act, uint16_t *gin, int B, hipStream_t s) {
-    using G = Geo<CI, CO, HI>;
-    hipLaunchKernelGGL((conv_bwd_data<CI, CO, HI>), dim3(blocks((long long)B * (G::HWI / 16), 4)), dim3(256), 0, s, g,
-                       w, act, gin, B);
-    return hipGetLastError();
-}
-
 }  // namespace
 
 long long partial_elems(int B) {
-    const long long a = (long long)kC1 * Geo<kC0, kC1, kH0>::NW1;
-    const long long b = (long long)kC2 * Geo<kC1, kC2, kH1>::NW1;
-    const long long c = (long long)kC3 * Geo<kC2, kC3, kH2>::NW1;
-    return (long long)B * (a > b ? (a > c ? a : c) : (b > c ? b : c));
+    return (long long)bwd_groups(B, kH3, kBand3) * kGradSet<kC2, kC3> +
+           (long long)bwd_groups(B, kH2, kBand2) * kGradSet<kC1, kC2> +
+           (long long)bwd_groups(B, kH1, kBand1) * kGradSet<kC0, kC1>;
 }
 
 hipError_t launch_zero_cells(unsigned long long *cells, long long nsets, hipStream_t s) {
@@ -550,18 +752,19 @@ hipError_t launch_forward(const NetBuffers &n, hipStream_t s, int *flags, uint8_
 }
 
 hipError_t launch_backward(const NetBuffers &n, hipStream_t s) {
+    static_assert(kC2 == 32 && kC3 == 32 && kBackW2 % 8 == 0 && kBackW3 % 8 == 0, "conv_bwd's layers");
+    const int s3 = bwd_groups(n.B, kH3, kBand3), s2 = bwd_groups(n.B, kH2, kBand2), s1 = bwd_groups(n.B, kH1, kBand1);
+    float *p3 = n.partial, *p2 = p3 + (long long)s3 * kGradSet<kC2, kC3>, *p1 = p2 + (long long)s2 * kGradSet<kC1, kC2>;
     hipError_t e;
-    hipLaunchKernelGGL(head_bwd, dim3(n.B), dim3(256), 0, s, n);
+    hipLaunchKernelGGL((conv_bwd<kC2, kH2, kBand3, true>), dim3(s3), dim3(256), 0, s, n, n.a3, n.a2, n.w + kBackW3,
+                       n.g2, p3);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = bwd_weight<kC2, kC3, kH2>(n.g3, n.a2, nullptr, n.partial, n.grad, kOffW3, kOffB3, n.B, s)) != hipSuccess)
-        return e;
-    if ((e = bwd_data<kC2, kC3, kH2>(n.g3, n.w + kOffW3, n.a2, n.g2, n.B, s)) != hipSuccess) return e;
-    if ((e = bwd_weight<kC1, kC2, kH1>(n.g2, n.a1, nullptr, n.partial, n.grad, kOffW2, kOffB2, n.B, s)) != hipSuccess)
-        return e;
-    if ((e = bwd_data<kC1, kC2, kH1>(n.g2, n.w + kOffW2, n.a1, n.g1, n.B, s)) != hipSuccess) return e;
-    if ((e = bwd_weight<kC0, kC1, kH0>(n.g1, n.x0, n.idx, n.partial, n.grad, kOffW1, kOffB1, n.B, s)) != hipSuccess)
-        return e;
-    hipLaunchKernelGGL(head_grad, dim3(1), dim3(64), 0, s, n);
+    hipLaunchKernelGGL((conv_bwd<kC1, kH1, kBand2, false>), dim3(s2), dim3(256), 0, s, n, n.g2, n.a1, n.w + kBackW2,
+                       n.g1, p2);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL((conv1_bwd<kBand1>), dim3(s1), dim3(256), 0, s, n, p1);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(reduce_grad, dim3(kRed3 + kRed2 + kRed1 + 1), dim3(kRedCols * kRedWays), 0, s, n, p3, p2, p1, s3, s2, s1);
     return hipGetLastError();
 }
 

@@ -113,8 +113,8 @@ struct logfx_ctx {
         bool loaded = false;
         long long step = 0;             // AdamW steps since the parameters were set
         uint16_t *act = nullptr, *gact = nullptr;   // activations / gradients of a batch
-        float *small = nullptr;         // gap [B][32], logits [B], dz [B], loss [B]
-        float *partial = nullptr;       // split-K weight-gradient partials
+        float *small = nullptr;         // gap [B][32], logits [B]
+        float *partial = nullptr;       // partial weight gradients
         long long capB = 0;
         unsigned long long *cells = nullptr;   // [capImg][2][cells^2]
         uint16_t *feats = nullptr;             // [capImg][3][cells^2]
@@ -275,8 +275,8 @@ int ensure_gate_batch(logfx_ctx *ctx, long long B) {
     G.capB = 0;
     int rc;
     if ((rc = realloc_dev(ctx, G.act, gate::act_elems((int)B))) != LOGFX_OK ||
-        (rc = realloc_dev(ctx, G.gact, gate::act_elems((int)B))) != LOGFX_OK ||
-        (rc = realloc_dev(ctx, G.small, B * (gate::kC3 + 3))) != LOGFX_OK ||
+        (rc = realloc_dev(ctx, G.gact, gate::gact_elems((int)B))) != LOGFX_OK ||
+        (rc = realloc_dev(ctx, G.small, B * (gate::kC3 + 1))) != LOGFX_OK ||
         (rc = realloc_dev(ctx, G.partial, gate::partial_elems((int)B))) != LOGFX_OK)
         return rc;
     G.capB = B;
@@ -314,11 +314,8 @@ gate::NetBuffers net_buffers(logfx_ctx *ctx, int B, const uint16_t *feats, const
     n.a3 = G.act + e1 + e2;
     n.g1 = G.gact;
     n.g2 = G.gact + e1;
-    n.g3 = G.gact + e1 + e2;
     n.gap = G.small;
     n.logits = G.small + (long long)B * kC3;
-    n.dz = n.logits + B;
-    n.lossb = n.dz + B;
     n.labels = labels;
     n.grad = grad ? grad : G.grad;
     n.loss = loss;

@@ -140,6 +140,39 @@ def test_gradient_matches_oracle(ctx, B, seed):
         o += n
 
 
+@pytest.mark.parametrize("n,parts", [(2, 2), (64, 64), (128, 32), (512, 8), (66, 2), (514, 2)])
+def test_gradient_of_a_batch_is_the_mean_of_its_parts(ctx, n, parts):
+    """Batches on both sides of the sizes where a backward workgroup takes a
+    second band (64 samples in layers 1 and 2, 256 in layer 3).  parts is a
+    power of two, so dz and every bfloat16 gradient of a part are those of
+    the whole times it, exactly, and only the FP32 sums differ: about a
+    hundred roundings of 2^-24, relative to sums of magnitudes up to about
+    a hundred times the result's norm: 1e-4 relative L2 per tensor.
+    (66 and 514: one half of the batch repeats the other.)"""
+    import torch
+    rng = np.random.default_rng(n)
+    ctx.gate_set_params(og.init(3))
+    m = n // parts
+    N = m if n in (66, 514) else n
+    feats = _bf16_dev(rng.random((N, 3, 128, 128)))
+    labels = torch.from_numpy((rng.random(N) < 0.5).astype(np.float32)).cuda()
+    order = rng.permutation(N).astype(np.int32)
+    idx = torch.from_numpy(order if N == n else np.concatenate([order] * parts)).cuda()
+    whole, loss = ctx.gate_backward(feats, labels, idx)
+    mean, lmean = np.zeros(logfx.GATE_NPARAM), 0.0
+    for k in range(parts):
+        g, lo = ctx.gate_backward(feats, labels, idx[k * m:(k + 1) * m].contiguous())
+        mean += g.double().cpu().numpy() / parts
+        lmean += float(lo.cpu()[0]) / parts
+    whole = whole.double().cpu().numpy()
+    assert abs(float(loss.cpu()[0]) - lmean) <= 1e-5 * (1 + abs(lmean))
+    at = 0
+    for size in (432, 16, 4608, 32, 9216, 32, 32, 1):
+        a, b = whole[at:at + size], mean[at:at + size]
+        at += size
+        assert np.linalg.norm(a - b) <= 1e-4 * np.linalg.norm(b) + 1e-9
+
+
 def test_adamw_step_matches_oracle(ctx):
     """Three AdamW steps on given gradients: FP32 on the GPU, FP64 in the
     oracle, same formula."""
