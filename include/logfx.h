@@ -196,7 +196,9 @@ int logfx_make_log_mask(int32_t size, double sigma, int32_t grid_bits, float *ta
  * ranges, mask symmetry, the exactness bound).  img->data must be non-NULL
  * but is not dereferenced.  path_out (nullable) receives the arithmetic path
  * (LOGFX_PATH_INT32 when sum|k| * (2^bits - 1) < 2^30, else
- * LOGFX_PATH_FP64).  Host-only. */
+ * LOGFX_PATH_FP64; the class names that bound -- a call of the second class
+ * whose sums provably fit int32 all the same, such as a zero-sum mask's up
+ * to twice the bound, runs in int32, with the same values).  Host-only. */
 int logfx_check_params(const logfx_image *img, const logfx_params *p, int32_t *path_out);
 
 /* The whole pipeline on one image (Sec. 4.1, Fig. 1 flow):

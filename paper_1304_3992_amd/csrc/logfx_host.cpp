@@ -57,7 +57,7 @@ struct logfx_ctx {
     bool graph = true;               // batches: replay a captured hipGraph
     bool store_z = true;             // pass 1 stores the strengths, pass 2 reads them
     bool pack_log = true;            // integer LoG on packed 16-bit sums where it applies
-    void *zmap = nullptr;            // strength pairs of the images of a call
+    void *zmap = nullptr;            // strengths of the images of a call
     long long zcap = 0;              // bytes
     uint8_t *cmap = nullptr;         // 0/1 maps between the levels of a median cascade
     long long ccap = 0;              // bytes
@@ -342,6 +342,7 @@ struct MaskInfo {
     double unit = 1.0;       // grid unit u: taps = k * u
     double k[81];            // integer taps (exact in double)
     double sumabs = 0.0;     // sum |k|
+    double sumpos = 0.0;     // sum of the positive k
     double maxabs = 0.0;     // max |k|
 };
 
@@ -371,7 +372,7 @@ int analyze_mask(logfx_ctx *ctx, const logfx_mask &m, int which, MaskInfo &mi, b
         if (lsb < min_lsb) min_lsb = lsb;
     }
     mi.unit = any ? std::ldexp(1.0, min_lsb) : 1.0;
-    mi.sumabs = mi.maxabs = 0.0;
+    mi.sumabs = mi.sumpos = mi.maxabs = 0.0;
     for (int i = 0; i < s * s; ++i) {
         const double k = (double)m.taps[i] / mi.unit;
         if (std::fabs(k) > 9007199254740992.0 && !inexact_ok)
@@ -380,6 +381,7 @@ int analyze_mask(logfx_ctx *ctx, const logfx_mask &m, int which, MaskInfo &mi, b
                            "(LOGFX_ALLOW_INEXACT runs them with rounded sums)", which);
         mi.k[i] = k;
         mi.sumabs += std::fabs(k);
+        if (k > 0.0) mi.sumpos += k;
         if (std::fabs(k) > mi.maxabs) mi.maxabs = std::fabs(k);
     }
     // the eight symmetries of the square grid
@@ -401,7 +403,8 @@ struct Plan {
     MaskInfo mi[2];
     int order[2];         // kernel mask slot -> user mask index
     int ra = 1, rb = 1;   // kernel radii, ra <= rb
-    int path = LOGFX_PATH_INT32;
+    int path = LOGFX_PATH_INT32;   // the class the caller is told (bound 2^30 on sum|k| maxpix)
+    bool i32 = true;      // the LoG runs in exact int32 (every call of that class, and more: check_all)
     double maxpix = 255.0;
     bool std5 = false;    // the 5x5 first deviation stage is on (std5_max >= 0)
     bool inexact = false; // the FP64 LoG sums round (LOGFX_ALLOW_INEXACT)
@@ -474,8 +477,21 @@ int check_all(logfx_ctx *ctx, const logfx_image *img, const logfx_params *p, Pla
             return rc;
     pl.maxpix = std::ldexp(1.0, bits) - 1.0;
     bool int_ok = true, f64_ok = true;
+    pl.i32 = true;
     for (int j = 0; j < 2; ++j) {
         const double bound = pl.mi[j].sumabs * pl.maxpix;
+        // int32 arithmetic needs every response and partial sum below 2^30 in
+        // magnitude (pixels are >= 0, so they lie between minus the sum of
+        // the negative taps and the sum of the positive ones, times maxpix;
+        // the crossing test adds two of them) and their range, the strength,
+        // below 2^31.  A zero-sum mask has half of sum|k| on either side, so
+        // it runs in int32 up to twice the bound the class is named by, 12-bit
+        // images with the default masks among them (2000^2, whole call with
+        // its report: 108 us in FP64, 86 in int32).
+        const double pos = pl.mi[j].sumpos * pl.maxpix;
+        if (!(pos < 1073741824.0 && bound - pos < 1073741824.0 && bound < 2147483648.0 &&
+              pl.mi[j].maxabs < 8388608.0))
+            pl.i32 = false;
         if (!(bound < 1073741824.0 && pl.mi[j].maxabs < 8388608.0)) int_ok = false;  // 2^30, 2^23
         if (!(bound < 4503599627370496.0)) f64_ok = false;                              // 2^52
     }
@@ -493,7 +509,7 @@ int check_all(logfx_ctx *ctx, const logfx_image *img, const logfx_params *p, Pla
     pl.rb = std::max(1, std::max(r0, r1));
     // packed 16-bit sums: every v(d, c) (at most four pixels) below 2^15
     OrbitTapsI probe;
-    pl.pk_ok = pl.path == LOGFX_PATH_INT32 && pl.maxpix <= 8191.0 && fill_packed_taps(pl, probe);
+    pl.pk_ok = pl.i32 && pl.maxpix <= 8191.0 && fill_packed_taps(pl, probe);
     pl.std5 = p->std5_max >= 0.0;
     if (p->gate_region < 0) return set_err(ctx, LOGFX_EINVAL, "gate_region %d < 0", p->gate_region);
     pl.region = 0;
@@ -610,6 +626,7 @@ struct Call {
     Launch L;
     int n = 1;
     bool storez = false;   // pass 1 stores the strengths in ctx->zmap, pass 2 reads them
+    long long px = 0;      // pixels of all images (when the strengths are stored)
     int rows1 = 64;        // pass-1 strip height of this call
     int cell_slots = 0, cell_rows = 0;   // LDS slots of pass 1's gate cell sums per tile
     std::vector<ImageTiles> tiles;
@@ -633,10 +650,13 @@ void cell_layout(int n, const logfx_image *imgs, const Plan &pl, int rows, long 
     }
 }
 
-// Device memory for the strength pairs of `px` pixels; false if it cannot
+// Device memory for the strengths of `px` pixels (ZMap); false if it cannot
 // be had (the call then recomputes the strengths in pass 2).
-bool ensure_zmap(logfx_ctx *ctx, long long px, int path) {
-    const long long bytes = px * (path == LOGFX_PATH_INT32 ? 8 : 16);
+// zmap_words: words of the code plane, rounded up so that the plane of low
+// bits after it is aligned.
+long long zmap_words(long long px) { return (px + 63) / 64 * 64; }
+bool ensure_zmap(logfx_ctx *ctx, long long px, bool i32) {
+    const long long bytes = zmap_words(px) * (i32 ? 8 : 16);
     if (bytes <= ctx->zcap) return true;
     (void)hipFree(ctx->zmap);
     ctx->zmap = nullptr;
@@ -681,14 +701,14 @@ int prepare(logfx_ctx *ctx, int n, const logfx_image *imgs, const logfx_params *
     c.storez = false;
     const bool need_z = c.pl.std5 || c.pl.ncas > 0 || c.pl.region > 0;
     if (need_out && (ctx->store_z || need_z)) {
-        long long px = 0;
+        long long &px = c.px;
         for (int i = 0; i < n; ++i) px += (long long)imgs[i].height * imgs[i].width;
-        c.storez = ensure_zmap(ctx, px, c.pl.path);
+        c.storez = ensure_zmap(ctx, px, c.pl.i32);
         if (!c.storez && need_z)
             return set_err(ctx, LOGFX_ENOMEM, "the 5x5 first deviation stage, the median cascade and the "
                                               "per-region gate need %lld bytes of device memory for the "
                                               "crossing strengths",
-                           px * (c.pl.path == LOGFX_PATH_INT32 ? 8 : 16));
+                           px * (c.pl.i32 ? 8 : 16));
         if (c.pl.ncas > 0 && px > ctx->ccap) {
             (void)hipFree(ctx->cmap);
             ctx->cmap = nullptr;
@@ -794,7 +814,8 @@ struct Launches {
     } p2;
     FinalizeArgs fin;
     int grid1, grid2;
-    int path, ra, rb;
+    int ra, rb;
+    bool i32;                      // exact int32 LoG, else FP64
     bool packed;                   // pass 1 on packed 16-bit sums (integer path)
     bool dbg;
     bool storez;
@@ -848,22 +869,37 @@ void fill_args(const Call &c, logfx_ctx *ctx, const logfx_params *p, double *con
     a2.counts = ctx->counts2;
     a2.smooth = p->smooth != LOGFX_SMOOTH_NEVER;   // GATE without a gate falls back to ALWAYS
     if (c.storez) {
-        a1.zmap = ctx->zmap;
-        a2.zmap = ctx->zmap;
+        // the split form where the strengths, at most sum|k| maxpix, are
+        // exact integers of at most kZSplitBits bits
+        ZMap &z = a1.z;
+        int bits[2];
+        for (int slot = 0; slot < 2; ++slot) {
+            const MaskInfo &mi = c.pl.mi[c.pl.order[slot]];
+            bits[slot] = std::ilogb(std::max(1.0, mi.sumabs * c.pl.maxpix)) + 1;
+            z.shift[slot] = std::max(0, bits[slot] - 16);
+        }
+        z.split = !c.pl.inexact && std::max(bits[0], bits[1]) <= kZSplitBits;
+        if (!z.split) z.shift[0] = z.shift[1] = 0;
+        z.hi = ctx->zmap;
+        z.lo = static_cast<char *>(ctx->zmap) + zmap_words(c.px) * 4;
+        a2.z = z;
     }
     a2.median_size = p->median_size;
     a1.cells_lx = kGateCellsLog2 + c.pl.lgx;
     a1.cells_ly = kGateCellsLog2 + c.pl.lgy;
     a2.std5 = c.pl.std5 && c.storez;
+    a2.zfloor = c.pl.inexact ? std::ldexp(1.0f, -120) : 0.0f;
     for (int slot = 0; slot < 2; ++slot) {
         const double t = a2.std5 ? p->std5_max / c.pl.mi[c.pl.order[slot]].unit : 0.0;
         a2.thr600[slot] = 600.0 * t * t;   // s5 > t <=> 25 sum z^2 - (sum z)^2 > 600 t^2 (t >= 0)
+        const double zmax = c.pl.mi[c.pl.order[slot]].sumabs * c.pl.maxpix;
+        a2.zscale[slot] = c.pl.inexact && zmax > 0.0 ? std::ldexp(1.0, std::min(0, 51 - std::ilogb(zmax))) : 1.0;
     }
 }
 
 hipError_t launch_all(const Launches &k, hipStream_t s, hipEvent_t *ev, int until) {
     hipError_t e;
-    const bool i32 = k.path == LOGFX_PATH_INT32;
+    const bool i32 = k.i32;
     const int mode = (k.dbg ? kP1Maps : 0) | (k.features ? kP1Cells : 0) | (k.storez ? kP1StoreZ : 0) |
                      (k.packed ? kP1Packed : 0);
     if (k.features && (e = gate::launch_zero_cells(k.cells, k.nsets, s)) != hipSuccess) return e;
@@ -910,12 +946,12 @@ int check_cells(logfx_ctx *ctx, int n, const logfx_image *imgs, const Plan &pl) 
 int build_launches(logfx_ctx *ctx, const Call &c, const logfx_params *p, double *const L[2],
                    double *const Z[2], Launches &k, int gate = 0, uint16_t *feats = nullptr) {
     std::memset(&k, 0, sizeof k);
-    k.path = c.pl.path;
+    k.i32 = c.pl.i32;
     k.ra = c.pl.ra;
     k.rb = c.pl.rb;
     k.storez = c.storez;
     k.packed = use_packed(ctx, c.pl);
-    if (k.path == LOGFX_PATH_INT32) fill_args<OrbitTapsI, int>(c, ctx, p, L, Z, k.p1.i, k.p2.i, k.dbg, k.packed);
+    if (k.i32) fill_args<OrbitTapsI, int>(c, ctx, p, L, Z, k.p1.i, k.p2.i, k.dbg, k.packed);
     else fill_args<OrbitTapsD, double>(c, ctx, p, L, Z, k.p1.d, k.p2.d, k.dbg, false);
     k.gx = c.pl.gx;
     k.gy = c.pl.gy;
@@ -928,7 +964,7 @@ int build_launches(logfx_ctx *ctx, const Call &c, const logfx_params *p, double 
         k.cells = G.cells;
         k.feats = feats ? feats : G.feats;
         k.maxval = c.pl.maxpix;
-        if (k.path == LOGFX_PATH_INT32)
+        if (k.i32)
             k.p1.i.cells = G.cells, k.p1.i.cell_slots = c.cell_slots, k.p1.i.cell_rows = c.cell_rows;
         else
             k.p1.d.cells = G.cells, k.p1.d.cell_slots = c.cell_slots, k.p1.d.cell_rows = c.cell_rows;
@@ -937,7 +973,7 @@ int build_launches(logfx_ctx *ctx, const Call &c, const logfx_params *p, double 
             k.gated = true;
             k.net = net_buffers(ctx, k.nsets, k.feats, nullptr, nullptr, nullptr, nullptr);
             k.flags = G.flags;
-            if (k.path == LOGFX_PATH_INT32) {
+            if (k.i32) {
                 k.p2.i.med_flags = G.flags;
                 k.p2.i.region = c.pl.region;
                 k.p2.i.reg_gx = c.pl.gx;
@@ -953,7 +989,7 @@ int build_launches(logfx_ctx *ctx, const Call &c, const logfx_params *p, double 
     if (k.ncas > 0) {
         // level i reads the scratch map iff an odd number of levels remain
         uint8_t *first = k.ncas % 2 ? ctx->cmap : nullptr;
-        if (k.path == LOGFX_PATH_INT32) k.p2.i.out_map = first;
+        if (k.i32) k.p2.i.out_map = first;
         else k.p2.d.out_map = first;
         for (int i = 0; i < k.ncas; ++i) {
             LevelArgs &l = k.lev[i];
@@ -978,7 +1014,7 @@ int build_launches(logfx_ctx *ctx, const Call &c, const logfx_params *p, double 
     if (c.n > 1 && ctx->persistent && !k.dbg) {
         // a persistent launch: as many workgroups as fit on the device
         int m1 = 0, m2 = 0;
-        const bool i32 = k.path == LOGFX_PATH_INT32;
+        const bool i32 = k.i32;
         const int mode = (k.storez ? kP1StoreZ : 0) | (k.packed ? kP1Packed : 0);
         hipError_t e = i32 ? launch_pass1_i(k.ra, k.rb, k.p1.i, mode, 0, nullptr, &m1)
                            : launch_pass1_d(k.ra, k.rb, k.p1.d, mode, 0, nullptr, &m1);
@@ -1109,7 +1145,7 @@ int run(logfx_ctx *ctx, int n, const logfx_image *imgs, const logfx_params *p, u
         log_line("%s: %d image(s), first %lld x %lld, %s path, radii %d/%d, tiles %d/%d (rows %d/%d), %s, smooth %d%s%s",
              maps ? "extract_maps" : (n > 1 ? "extract_batch" : "extract"), n, (long long)imgs[0].height,
              (long long)imgs[0].width,
-             c.pl.path != LOGFX_PATH_INT32 ? "fp64" : k.packed ? "int32 (packed)" : "int32", c.pl.ra, c.pl.rb,
+             !c.pl.i32 ? "fp64" : k.packed ? "int32 (packed)" : "int32", c.pl.ra, c.pl.rb,
              c.L.total1, c.L.total2, c.rows1, ctx->tiles.rows2, c.storez ? "stored strengths" : "recomputed strengths",
              p->smooth, gated ? " (gated)" : "", use_graph ? ", graph" : "");
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -1186,7 +1222,7 @@ std::string tune_key(logfx_ctx *ctx, const Call &c, const logfx_params *p, const
         if (colon != std::string::npos) arch.resize(colon);
     }
     std::ostringstream k;
-    k << arch << "|" << (c.pl.path != LOGFX_PATH_INT32 ? "fp64" : use_packed(ctx, c.pl) ? "int32pk" : "int32")
+    k << arch << "|" << (!c.pl.i32 ? "fp64" : use_packed(ctx, c.pl) ? "int32pk" : "int32")
       << "|r" << c.pl.ra << c.pl.rb
       << "|" << (img0->dtype == LOGFX_U8 ? "u8" : "u16") << "|med"
       << (p->smooth != LOGFX_SMOOTH_NEVER ? p->median_size : 0) << (p->smooth == LOGFX_SMOOTH_GATE ? "g" : "")
@@ -1448,7 +1484,7 @@ int logfx_extract_noalloc(logfx_ctx *ctx, const logfx_image *img, const logfx_pa
     long long *counts1 = reinterpret_cast<long long *>(base + kNoAllocCounts1Off);
     int *counts2 = reinterpret_cast<int *>(base + kNoAllocCounts2Off);
     DevStats *stats = reinterpret_cast<DevStats *>(base + kNoAllocStatsOff);
-    if (k.path == LOGFX_PATH_INT32) {
+    if (k.i32) {
         k.p1.i.partials = partials, k.p1.i.counts = counts1;
         k.p2.i.stats = stats, k.p2.i.counts = counts2;
     } else {

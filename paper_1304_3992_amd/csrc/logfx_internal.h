@@ -90,6 +90,22 @@ __host__ __device__ constexpr int tile_lds_stride(int halo, int rb) {
 static_assert(tile_out_width(kHalo1) % 8 == 0 && tile_out_width(kHalo2) % 8 == 0,
               "image-reading passes need 8-multiple tile widths");
 
+// Storage of the crossing strengths (Z_1, Z_2) between the passes, pixel i
+// of an image at element zoff + i.
+//  split (the integer path, and the FP64 path where the strengths are exact
+//   integers below 2^47): `hi` holds one 32-bit word per pixel, the top 16
+//   bits of each strength, code_j = Z_j >> shift[j]; `lo` what restores the
+//   exact value: the low 16 bits of both in one word (integer path, where
+//   shift <= 16) or the low 32 bits of each (FP64 path).  Pass 2 decides
+//   nearly every pixel from the codes and reads `lo` where it has to.
+//  pairs (other FP64 calls): `hi` holds a double2 per pixel.
+struct ZMap {
+    void *hi, *lo;
+    int shift[2];
+    int split;
+};
+constexpr int kZSplitBits = 47;   // strengths of the split form are below 2^47
+
 // One image of a launch: its input, its output and where its tiles sit in
 // the launch's tile list.
 struct ImageJob {
@@ -99,7 +115,7 @@ struct ImageJob {
     int tiles_x1, tiles_x2;  // tiles across the image in pass 1 / pass 2
     int base1, base2;        // index of the image's first tile among the launch's tiles
     int ntiles1, ntiles2;
-    long long zoff;          // first element of the image's strength pairs in the Z map (H*W of them)
+    long long zoff;          // first element of the image's strengths in the Z map (H*W of them)
 };
 
 // The work of one launch: one image (passed inline) or a batch of images
@@ -127,9 +143,8 @@ struct Pass1Args {
     double *dbgL[2];
     double *dbgZ[2];
     double unit[2];
-    // Strength pairs (kP1StoreZ): int2 (integer path) or double2 (FP64
-    // path) per pixel, image i at element jobs[i].zoff, row pitch W.
-    void *zmap;
+    // Strengths (kP1StoreZ): image i at element jobs[i].zoff, row pitch W.
+    ZMap z;
     // Gate features (kP1Cells): [nimg][2][cells] counters, zeroed before
     // the launch; plane 0 sums pixel values, plane 1 sums
     // [Z_1 != 0] + 2^32 [Z_2 != 0] (every cell must hold < 2^32 pixels).
@@ -156,9 +171,11 @@ struct Pass2Args {
     int smooth;             // 0 = E, 1 = hybrid median of E
     int median_size;        // 3 or 5
     const int *med_flags;   // [nimg] or nullptr: when given, image i is smoothed iff med_flags[i] != 0
-    const void *zmap;       // strength pairs written by pass 1 (pass 2 on stored strengths)
+    ZMap z;                 // strengths written by pass 1 (pass 2 on stored strengths)
     int std5;               // the 5x5 first stage: E_j also needs s5 > std5_max (stored strengths only)
     double thr600[2];       // 600 (std5_max / unit_j)^2, compared with 25 sum z^2 - (sum z)^2
+    double zscale[2];       // pairs: power of two that brings the largest strength to 2^52 (1: it is below)
+    float zfloor;           // and what scaled strengths may lose to underflow (0 when the sums are exact)
     uint8_t *out_map;       // or nullptr: output of image i at out_map + jobs[i].zoff, pitch W
                             // (the first level of a median cascade; stored strengths only)
     int region;             // > 0 (single image, gated): med_flags holds one flag per square

@@ -492,26 +492,37 @@ __device__ inline ImageJob job_of(const Launch &L, int image) {
 }
 
 
-// Storage of the crossing-strength pair of a pixel between the passes: the
-// integer path keeps the exact integer strengths as int32 pairs, the FP64
-// path as double pairs (LoG grid units either way).
-template <class Acc> struct ZStore;
-template <> struct ZStore<int> {
-    using T = int2;
-    __device__ static T make(const int (&z)[2]) { return make_int2(z[0], z[1]); }
-    __device__ static void get(const T &v, double &z0, double &z1) {
-        z0 = (double)v.x;
-        z1 = (double)v.y;
+// Strengths into and out of the Z map (ZMap in logfx_internal.h).  The codes
+// and low halves are packed by byte permutes: two of them and two shifts per
+// pixel on the integer path.
+__device__ inline void store_strengths(const ZMap &m, long long row, unsigned x, const int (&z)[2]) {
+    const unsigned c0 = (unsigned)z[0] >> m.shift[0], c1 = (unsigned)z[1] << (16 - m.shift[1]);
+    (static_cast<unsigned *>(m.hi) + row)[x] = __builtin_amdgcn_perm(c1, c0, 0x07060100u);
+    (static_cast<unsigned *>(m.lo) + row)[x] = __builtin_amdgcn_perm((unsigned)z[1], (unsigned)z[0], 0x05040100u);
+}
+__device__ inline void store_strengths(const ZMap &m, long long row, unsigned x, const double (&z)[2]) {
+    if (!m.split) {
+        (static_cast<double2 *>(m.hi) + row)[x] = make_double2(z[0], z[1]);
+        return;
     }
-};
-template <> struct ZStore<double> {
-    using T = double2;
-    __device__ static T make(const double (&z)[2]) { return make_double2(z[0], z[1]); }
-    __device__ static void get(const T &v, double &z0, double &z1) {
-        z0 = v.x;
-        z1 = v.y;
-    }
-};
+    // z + 2^52 holds the integer z in its mantissa
+    const double i0 = z[0] + 4503599627370496.0, i1 = z[1] + 4503599627370496.0;
+    const unsigned l0 = __double2loint(i0), l1 = __double2loint(i1);
+    const unsigned c0 = __builtin_amdgcn_alignbit(__double2hiint(i0), l0, m.shift[0]);
+    const unsigned c1 = __builtin_amdgcn_alignbit(__double2hiint(i1), l1, m.shift[1]);
+    (static_cast<unsigned *>(m.hi) + row)[x] = __builtin_amdgcn_perm(c1, c0, 0x05040100u);
+    (static_cast<uint2 *>(m.lo) + row)[x] = make_uint2(l0, l1);
+}
+// The exact strengths from both planes.
+__device__ inline void restore_strengths(const ZMap &m, unsigned hi, unsigned lo, double (&z)[2]) {
+    z[0] = (double)((((hi & 0xFFFFu) << m.shift[0]) & 0xFFFF0000u) | (lo & 0xFFFFu));
+    z[1] = (double)((((hi >> 16) << m.shift[1]) & 0xFFFF0000u) | (lo >> 16));
+}
+__device__ inline void restore_strengths(const ZMap &m, unsigned hi, uint2 lo, double (&z)[2]) {
+    const unsigned h0 = ((hi & 0xFFFFu) >> 1) >> (31 - m.shift[0]), h1 = ((hi >> 16) >> 1) >> (31 - m.shift[1]);
+    z[0] = __hiloint2double(0x43300000 | h0, lo.x) - 4503599627370496.0;
+    z[1] = __hiloint2double(0x43300000 | h1, lo.y) - 4503599627370496.0;
+}
 
 // ------------------------------------------------------------- pass 1
 // Occupancy: the integer path is held to 128 VGPRs (4 waves per SIMD, the
@@ -530,7 +541,7 @@ constexpr int kPass1Waves =
     !std::is_same<Acc, int>::value ? kMinWaves<Acc>
     : (MODE & kP1Maps) != 0 ? 2   // inspection only: room for the FP64 map writes
     : (MODE & kP1Packed) != 0 ? 4
-    : (MODE & kP1Cells) != 0 || LOOP ? 3
+    : (MODE & (kP1Cells | kP1StoreZ)) != 0 || LOOP ? 3
     : kMinWaves<Acc>;
 // The recomputing pass 2 (the fallback without stored strengths) keeps the
 // LoG rings, the deviation rows and the median rows at once.
@@ -590,9 +601,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPass1Waves
     const uint16_t *lrow = lds + (2 * RB) * g.stride + g.lc;   // LDS row of step si
     // packed form: the words of the next step's row, read one step ahead
     // (the last step's read lands in the spare LDS row after the tile); the
-    // cell-summing variants of the two widest radius pairs would spill the
-    // five registers it holds and read each row in its step
-    constexpr bool AHEAD = PK && ((MODE & kP1Cells) == 0 || RA + RB < 7);
+    // cell-summing variants would spill the five registers it holds and read
+    // each row in its step
+    constexpr bool AHEAD = PK && (MODE & kP1Cells) == 0;
     RowWords ahead{};
     if constexpr (AHEAD) ahead = read_hrow_pk<RB>(lrow);
 
@@ -713,9 +724,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPass1Waves
         }
         if constexpr ((MODE & kP1StoreZ) != 0) {
             // the row's base is wave-uniform: scalar base + the lane's column
-            typename ZStore<Acc>::T *zrow =
-                static_cast<typename ZStore<Acc>::T *>(a.zmap) + (J.zoff + (long long)r * g.W);
-            if (use) zrow[g.xc] = ZStore<Acc>::make(zr);
+            if (use) store_strengths(a.z, J.zoff + (long long)r * g.W, (unsigned)g.xc, zr);
         }
         if constexpr ((MODE & kP1Cells) != 0) {
             // every lane accumulates; the halo rows before the strip are

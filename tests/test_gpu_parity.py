@@ -684,3 +684,85 @@ def test_allow_inexact_masks(ctx):
     mism = F != o["F"]
     assert not (mism & ~cone).any(), int((mism & ~cone).sum())
     print("inexact masks:", int(mism.sum()), "differing pixels,", int(cone.sum()), "in the rounding cone")
+
+
+def _stored_cases():
+    rng = np.random.default_rng(17)
+    flat = np.clip(np.rint(300 + rng.normal(0, 1.0, (301, 517))), 0, 2047).astype(np.uint16)
+    steps = (rng.integers(0, 3, (150, 240)) * 40).astype(np.uint8)      # ties and repeated windows
+    line = np.zeros((90, 130), np.uint16)
+    line[:, 60] = 2047
+    scene = scenes.panchromatic(333, 401, 31, n_rect=60, n_poly=5, noise_sigma=9.0, sp_density=0.03, bits=11)
+    return {
+        "scene_u11": (scene, 11, 16, {}),
+        "scene_u12": (scene, 12, 16, {}),
+        "scene_u16": (scene, 16, 16, {}),
+        "scene_grid23": (scene, 11, 23, {}),
+        # thresholds of a few code steps and below: the low bits decide every row
+        "flat_low_noise": (flat, 11, 16, {}),
+        "flat_low_noise_u16": (flat, 16, 16, {}),
+        "code_step_threshold": (scene, 11, 16, dict(std_mode=logfx.STD_ABS, std_k=2.0 ** -2)),
+        "just_past_the_line": (scene, 11, 16, dict(std_mode=logfx.STD_ABS, std_k=12.0)),
+        "zero_threshold": (scene, 11, 16, dict(std_k=0.0)),
+        "infinite_threshold": (scene, 11, 16, dict(std_k=1e200)),
+        "steps_u8": (steps, 8, 16, {}),
+        "steps_zero_threshold": (steps, 8, 16, dict(std_k=0.0)),
+        "one_line": (line, 11, 16, {}),
+        "constant": (np.full((40, 70), 9, np.uint8), 8, 16, {}),
+        "one_bit": (rng.integers(0, 2, (65, 59)).astype(np.uint8), 1, 2, {}),
+    }
+
+
+@pytest.mark.parametrize("name", sorted(_stored_cases()))
+def test_stored_strengths_decide_as_the_recomputed_ones(ctx, name):
+    """Pass 2 on stored strengths decides from 16-bit codes and FP32 where
+    they can decide and exactly elsewhere; the recomputing pass 2 is FP64
+    throughout.  Same bytes, for thresholds above, at and below the code
+    step, on the integer and the FP64 path."""
+    img, bits, grid, kw = _stored_cases()[name]
+    params = logfx.Params(logfx.make_log_mask(5, 0.8, grid)[0], logfx.make_log_mask(9, 1.4, grid)[0], **kw)
+    dev = to_device(img)
+    outs = []
+    try:
+        for store in (1, 0):
+            ctx.set_option(logfx.OPT_STORE_Z, store)
+            out, rep = ctx.extract(dev, params, bits=bits, report=True)
+            outs.append((out.cpu().numpy(), rep["extracted"], rep["output"]))
+    finally:
+        ctx.set_option(logfx.OPT_STORE_Z, 1)
+    assert np.array_equal(outs[0][0], outs[1][0])
+    assert outs[0][1:] == outs[1][1:]
+
+
+@pytest.mark.parametrize("form", ["packed", "32-bit"])
+@pytest.mark.parametrize("bits", [11, 12])
+def test_int32_sums_at_their_largest(ctx, bits, form):
+    """12-bit images with the default masks are past the bound 2^30 on
+    sum|k| maxpix but run in int32, since each side of the zero-sum masks
+    stays below it.  Windows that hold the largest pixel exactly where a
+    mask is positive (or negative) reach the extreme responses, and their
+    neighbours the opposite ones: L, Z and the map equal the oracle's."""
+    import torch
+    orc_t, lib_t = masks()
+    maxv = (1 << bits) - 1
+    img = np.zeros((150, 330), np.uint16)
+    for y in range(8, 140, 10):
+        for x in range(8, 320, 10):
+            t = orc_t[((x + y) // 10) % 2]
+            r = t.shape[0] // 2
+            img[y - r:y + r + 1, x - r:x + r + 1] = np.where((t > 0) == (((x // 10) // 2) % 2 == 0), maxv, 0)
+    params = logfx.Params(*lib_t)
+    dev = to_device(img)
+    ctx.set_option(logfx.OPT_PACKED_LOG, 1 if form == "packed" else 0)
+    try:
+        out, rep = ctx.extract(dev, params, bits=bits, report=True)
+        maps = ctx.extract_maps(dev, params, bits=bits)
+        torch.cuda.synchronize()
+    finally:
+        ctx.set_option(logfx.OPT_PACKED_LOG, 1)
+    o = run_oracle(img, orc_t)
+    for j in (1, 2):
+        assert np.array_equal(maps[f"L{j}"].cpu().numpy(), o[f"L{j}"])
+        assert np.array_equal(maps[f"Z{j}"].cpu().numpy(), o[f"Z{j}"])
+    assert np.array_equal(out.cpu().numpy(), o["F"])
+    assert rep["path"] == (logfx.PATH_INT32 if bits == 11 else logfx.PATH_FP64)
