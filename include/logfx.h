@@ -272,7 +272,10 @@ enum {
     LOGFX_OPT_PACKED_LOG = 6  /* 1 (default) = on the integer path, pass 1 evaluates the LoG on packed
                                  16-bit sums of pixel pairs (two taps per multiply-add) where the
                                  pixels have at most 13 bits and every tap but the centre fits 16
-                                 bits; 0 = always the 32-bit form.  Both give the same bits. */
+                                 bits; on the FP64 path it evaluates it on the matrix cores, from
+                                 the bytes of pixels and taps, where the taps fit 16 bits (those of
+                                 the centre row 17); 0 = always the 32-bit and FP64 forms.  All give
+                                 the same bits. */
 };
 int logfx_set_option(logfx_ctx *ctx, int32_t option, int64_t value);
 int logfx_get_option(logfx_ctx *ctx, int32_t option, int64_t *value);

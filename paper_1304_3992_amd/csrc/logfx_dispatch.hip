@@ -91,7 +91,16 @@ __global__ __launch_bounds__(kFinThreads) void finalize_kernel(FinalizeArgs a) {
     }
 }
 
+__global__ __launch_bounds__(256) void write_table(MatTable t, unsigned char *dst) {
+    for (int i = threadIdx.x; i < kMatBytes; i += 256) dst[i] = t.b[i];
+}
+
 }  // namespace kern
+
+hipError_t launch_write_table(const MatTable &t, unsigned char *dst, hipStream_t s) {
+    hipLaunchKernelGGL(kern::write_table, dim3(1), dim3(256), 0, s, t, dst);
+    return hipGetLastError();
+}
 
 hipError_t launch_pass1_i(int ra, int rb, const Pass1Args<OrbitTapsI> &a, int mode, int grid,
                           hipStream_t s, int *max_grid) {

@@ -100,6 +100,12 @@ struct logfx_ctx {
     std::vector<hipEvent_t> events;
     long long timed_calls = 0;
     std::vector<char> timed_graph;   // per timed call: 1 if it was a graph replay
+    // tap tables of the matrix form, one per pair of masks the context has
+    // met.  A table is never changed or freed before the context is: a graph
+    // that a caller captured keeps its address.  Past kMatTables pairs the
+    // other forms run.
+    unsigned char *mat_dev = nullptr;          // [kMatTables][kMatBytes]
+    std::vector<MatTable> mat_tabs;            // what the first of them hold
     int alloc_count = 0;
     int fail_alloc_at = -1;          // test hook: LOGFX_FAIL_ALLOC=n fails the n-th allocation
     // device address of the static scratch of logfx_extract_noalloc on this
@@ -127,6 +133,8 @@ struct logfx_ctx {
 };
 
 namespace {
+
+constexpr size_t kMatTables = 64;   // 74 KB of device memory
 
 // LOGFX_LOG=1 (read once): one line per call and every error on stderr.
 bool log_on() {
@@ -409,6 +417,8 @@ struct Plan {
     bool std5 = false;    // the 5x5 first deviation stage is on (std5_max >= 0)
     bool inexact = false; // the FP64 LoG sums round (LOGFX_ALLOW_INEXACT)
     bool pk_ok = false;   // the integer LoG may run on packed 16-bit sums (kP1Packed)
+    bool mat_ok = false;  // the LoG may run on the matrix cores (kP1Matrix), with these taps
+    MatTable mat;
     int ncas = 0;         // further median levels (applied where the first level is)
     int cas[3] = {0, 0, 0};
     int region = 0;       // > 0: the gate decides per region x region square (single images)
@@ -433,6 +443,36 @@ bool fill_packed_taps(const Plan &pl, OrbitTapsI &t) {
                 t.pk[slot][d * kPkPerRow + m] =
                     (unsigned)(uint16_t)(int16_t)lo | (unsigned)(uint16_t)(int16_t)hi << 16;
             }
+    }
+    return true;
+}
+
+// The taps of the matrix form (layout in logfx_internal.h).  False when one
+// does not fit two signed bytes (-32896 .. 32639), or twice that in the
+// centre row, whose entry comes twice.
+bool fill_matrix_taps(const Plan &pl, MatTable &t) {
+    std::memset(&t, 0, sizeof t);
+    for (int slot = 0; slot < 2; ++slot) {
+        const MaskInfo &mi = pl.mi[pl.order[slot]];
+        const int r = mi.radius, s = mi.size;
+        for (int e = 0; e < kMatEntries; ++e) {
+            const int dy = e < 2 ? 0 : e - 1;
+            const bool again = e == 1;   // the centre row's second entry
+            if (dy > r) continue;
+            for (int dx = -r; dx <= r; ++dx) {
+                const double k = mi.k[(r + dy) * s + (r + dx)];
+                double v = k;
+                if (dy == 0) {
+                    v = std::min(std::max(k, -32896.0), 32639.0);
+                    if (again) v = k - v;
+                }
+                if (!(v >= -32896.0 && v <= 32639.0)) return false;
+                const int n = (int)v, hi = (n + 128) >> 8, lo = n - 256 * hi;
+                unsigned char *row = t.b + ((slot * kMatEntries + e) * 2) * kMatRow + 23 + dx;
+                row[0] = (unsigned char)(signed char)hi;
+                row[kMatRow] = (unsigned char)(signed char)lo;
+            }
+        }
     }
     return true;
 }
@@ -510,6 +550,7 @@ int check_all(logfx_ctx *ctx, const logfx_image *img, const logfx_params *p, Pla
     // packed 16-bit sums: every v(d, c) (at most four pixels) below 2^15
     OrbitTapsI probe;
     pl.pk_ok = pl.i32 && pl.maxpix <= 8191.0 && fill_packed_taps(pl, probe);
+    pl.mat_ok = !pl.inexact && fill_matrix_taps(pl, pl.mat);
     pl.std5 = p->std5_max >= 0.0;
     if (p->gate_region < 0) return set_err(ctx, LOGFX_EINVAL, "gate_region %d < 0", p->gate_region);
     pl.region = 0;
@@ -560,6 +601,32 @@ void fill_taps(const Plan &pl, Taps &t) {
 // The packed integer form runs when the plan allows it and the context
 // does not turn it off (LOGFX_OPT_PACKED_LOG).
 bool use_packed(const logfx_ctx *ctx, const Plan &pl) { return pl.pk_ok && ctx->pack_log; }
+
+// Device table of the plan's taps for the matrix form, written on the call's
+// stream when the context meets the masks for the first time; nullptr when
+// the form does not apply (LOGFX_OPT_PACKED_LOG = 0 asks for the 32-bit form)
+// or its table cannot be made now: the caller is capturing the stream, which
+// would put off the writing to a replay.
+const unsigned char *matrix_table(logfx_ctx *ctx, const Plan &pl, hipStream_t s) {
+    if (!pl.mat_ok || pl.i32 || !ctx->pack_log) return nullptr;
+    for (size_t i = 0; i < ctx->mat_tabs.size(); ++i)
+        if (std::memcmp(&ctx->mat_tabs[i], &pl.mat, sizeof pl.mat) == 0) return ctx->mat_dev + i * kMatBytes;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (ctx->mat_tabs.size() >= kMatTables || hipStreamIsCapturing(s, &st) != hipSuccess ||
+        st != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    if (!ctx->mat_dev && hipMalloc((void **)&ctx->mat_dev, kMatTables * kMatBytes) != hipSuccess) {
+        ctx->mat_dev = nullptr;
+        (void)hipGetLastError();   // clear the sticky out-of-memory error
+        return nullptr;
+    }
+    unsigned char *dst = ctx->mat_dev + ctx->mat_tabs.size() * kMatBytes;
+    if (launch_write_table(pl.mat, dst, s) != hipSuccess) return nullptr;
+    ctx->mat_tabs.push_back(pl.mat);
+    return dst;
+}
 
 // ------------------------------------------------------------ one call
 // Tiling of one image in both passes.
@@ -627,6 +694,7 @@ struct Call {
     int n = 1;
     bool storez = false;   // pass 1 stores the strengths in ctx->zmap, pass 2 reads them
     long long px = 0;      // pixels of all images (when the strengths are stored)
+    const unsigned char *table = nullptr;   // taps of the matrix form, where it runs
     int rows1 = 64;        // pass-1 strip height of this call
     int cell_slots = 0, cell_rows = 0;   // LDS slots of pass 1's gate cell sums per tile
     std::vector<ImageTiles> tiles;
@@ -721,6 +789,7 @@ int prepare(logfx_ctx *ctx, int n, const logfx_image *imgs, const logfx_params *
             ctx->ccap = px;
         }
     }
+    c.table = matrix_table(ctx, c.pl, s);
     const int bits0 = imgs[0].bits == 0 ? (imgs[0].dtype == LOGFX_U8 ? 8 : 16) : imgs[0].bits;
     c.n = n;
     c.tiles.resize(n);
@@ -817,6 +886,7 @@ struct Launches {
     int ra, rb;
     bool i32;                      // exact int32 LoG, else FP64
     bool packed;                   // pass 1 on packed 16-bit sums (integer path)
+    bool matrix;                   // pass 1 on the matrix cores (either path; before the packed form)
     bool dbg;
     bool storez;
     // median cascade: further levels after pass 2 (pass 2 writes the
@@ -901,7 +971,7 @@ hipError_t launch_all(const Launches &k, hipStream_t s, hipEvent_t *ev, int unti
     hipError_t e;
     const bool i32 = k.i32;
     const int mode = (k.dbg ? kP1Maps : 0) | (k.features ? kP1Cells : 0) | (k.storez ? kP1StoreZ : 0) |
-                     (k.packed ? kP1Packed : 0);
+                     (k.matrix ? kP1Matrix : k.packed ? kP1Packed : 0);
     if (k.features && (e = gate::launch_zero_cells(k.cells, k.nsets, s)) != hipSuccess) return e;
     e = i32 ? launch_pass1_i(k.ra, k.rb, k.p1.i, mode, k.grid1, s)
             : launch_pass1_d(k.ra, k.rb, k.p1.d, mode, k.grid1, s);
@@ -953,6 +1023,20 @@ int build_launches(logfx_ctx *ctx, const Call &c, const logfx_params *p, double 
     k.packed = use_packed(ctx, c.pl);
     if (k.i32) fill_args<OrbitTapsI, int>(c, ctx, p, L, Z, k.p1.i, k.p2.i, k.dbg, k.packed);
     else fill_args<OrbitTapsD, double>(c, ctx, p, L, Z, k.p1.d, k.p2.d, k.dbg, false);
+    k.matrix = c.table != nullptr && !k.dbg;
+    if (k.matrix) {
+        MatArgs &m = k.i32 ? k.p1.i.mat : k.p1.d.mat;
+        m.table = c.table;
+        m.planes = c.pl.maxpix <= 255.0 && k.i32 ? 1 : 2;
+        for (int slot = 0; slot < 2; ++slot) {
+            // the planes hold the pixels' bytes less 128
+            const MaskInfo &mi = c.pl.mi[c.pl.order[slot]];
+            const double sum = 2.0 * mi.sumpos - mi.sumabs, off = (m.planes == 2 ? 128.0 * 257.0 : 128.0) * sum;
+            m.sum |= off != 0.0;
+            m.kd[slot] = off;
+            m.ki[slot] = (int)(uint32_t)(int64_t)off;
+        }
+    }
     k.gx = c.pl.gx;
     k.gy = c.pl.gy;
     k.nsets = c.n * c.pl.gx * c.pl.gy;
@@ -1015,7 +1099,7 @@ int build_launches(logfx_ctx *ctx, const Call &c, const logfx_params *p, double 
         // a persistent launch: as many workgroups as fit on the device
         int m1 = 0, m2 = 0;
         const bool i32 = k.i32;
-        const int mode = (k.storez ? kP1StoreZ : 0) | (k.packed ? kP1Packed : 0);
+        const int mode = (k.storez ? kP1StoreZ : 0) | (k.matrix ? kP1Matrix : k.packed ? kP1Packed : 0);
         hipError_t e = i32 ? launch_pass1_i(k.ra, k.rb, k.p1.i, mode, 0, nullptr, &m1)
                            : launch_pass1_d(k.ra, k.rb, k.p1.d, mode, 0, nullptr, &m1);
         if (e == hipSuccess && k.storez)
@@ -1364,6 +1448,7 @@ int logfx_destroy(logfx_ctx *ctx) {
             if (S.own1) (void)hipHostFree(S.own1);
             if (S.own2) (void)hipHostFree(S.own2);
         }
+        (void)hipFree(ctx->mat_dev);
         (void)hipFree(ctx->zmap);
         (void)hipFree(ctx->cmap);
         (void)hipFree(ctx->partials);

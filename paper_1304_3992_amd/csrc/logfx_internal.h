@@ -27,6 +27,7 @@ constexpr int kP1Maps = 1;     // FP64 maps of L and Z (single images, for inspe
 constexpr int kP1Cells = 2;    // the gate's per-cell sums
 constexpr int kP1StoreZ = 4;   // the (Z_1, Z_2) pair of every pixel for pass 2
 constexpr int kP1Packed = 8;   // integer path: the LoG on packed 16-bit pixel sums
+constexpr int kP1Matrix = 16;  // the LoG on the matrix cores (logfx_pass1m.h)
 
 // Side of the cell grid over which pass 1 sums the smoothing gate's
 // features (kGateCells x kGateCells cells per image).
@@ -60,6 +61,23 @@ struct OrbitTapsI {
     unsigned pk[2][kPkTaps];
 };
 struct OrbitTapsD { double k[2][kMaxOrbits]; };
+
+// Taps of the matrix form (kP1Matrix): per mask kMatEntries rows, each as two
+// byte rows (high, then low: k = 256 kh + kl) of kMatRow bytes, tap column dx
+// at 23 + dx and zero elsewhere.  Entry 0 is the centre row, entry 1 the
+// centre row again, with what its taps exceed the range of two bytes by, and
+// entry 1 + d the rows at distance d.
+constexpr int kMatEntries = 2 + kMaxRadius;
+constexpr int kMatRow = 48;
+constexpr int kMatBytes = 2 * kMatEntries * 2 * kMatRow;
+struct MatTable { unsigned char b[kMatBytes]; };
+struct MatArgs {
+    const unsigned char *table;   // device copy of a MatTable
+    int sum;                      // the masks do not both sum to zero:
+    int ki[2];                    // what the pixels' offset adds, int32 (modulo 2^32)
+    double kd[2];                 // and FP64
+    int planes;                   // bytes per pixel: 1 (images of at most 8 bits) or 2
+};
 
 // Device-side statistics written by the finalize kernel (LoG grid units).
 struct DevStats {
@@ -143,6 +161,7 @@ struct Pass1Args {
     double *dbgL[2];
     double *dbgZ[2];
     double unit[2];
+    MatArgs mat;           // the matrix form's taps (kP1Matrix)
     // Strengths (kP1StoreZ): image i at element jobs[i].zoff, row pitch W.
     ZMap z;
     // Gate features (kP1Cells): [nimg][2][cells] counters, zeroed before
@@ -220,6 +239,8 @@ hipError_t launch_pass2_i(int ra, int rb, const Pass2Args<OrbitTapsI> &a, int gr
 hipError_t launch_pass2_d(int ra, int rb, const Pass2Args<OrbitTapsD> &a, int grid, hipStream_t s,
                           int *max_grid = nullptr);
 hipError_t launch_finalize(const FinalizeArgs &a, hipStream_t s);
+// Writes a tap table to device memory.
+hipError_t launch_write_table(const MatTable &t, unsigned char *dst, hipStream_t s);
 // Pass 2 on the strengths stored by pass 1 (no LoG, no LDS): tiles of
 // tile_out_width(kHalo2Z) columns, or tile_out_width(kHalo2Z5) with the 5x5
 // first stage (a.std5).

@@ -2,7 +2,7 @@
 // LOGFX_RA <= LOGFX_RB given on the command line.  The build compiles this
 // file once per supported pair of radii, so the units compile in parallel;
 // logfx_dispatch.hip selects among them at run time.
-#include "logfx_kernels.h"
+#include "logfx_pass1m.h"
 
 #if !defined(LOGFX_RA) || !defined(LOGFX_RB)
 #error "compile with -DLOGFX_RA=<radius of mask 1> -DLOGFX_RB=<radius of mask 2>"
@@ -18,10 +18,27 @@ namespace {   // one copy per radius pair: internal linkage keeps the units' cop
 
 // Pass-1 variants built: statistics only, maps, cells, stored strengths,
 // stored strengths with cells; on the integer path each also in the packed
-// form.
+// form, and all but the maps in the matrix form, for one byte per pixel
+// (integer path) and two.
+template <class Acc, int PL>
+hipError_t pass1_matrix(const Pass1Args<typename kern::AccOps<Acc>::Taps> &a, int mode, int grid, hipStream_t s,
+                        int *max_grid) {
+    switch (mode) {
+    case 0: return kern::p1m<Acc, LOGFX_RA, LOGFX_RB, 0, PL>(a, grid, s, max_grid);
+    case kP1Cells: return kern::p1m<Acc, LOGFX_RA, LOGFX_RB, kP1Cells, PL>(a, grid, s, max_grid);
+    case kP1StoreZ: return kern::p1m<Acc, LOGFX_RA, LOGFX_RB, kP1StoreZ, PL>(a, grid, s, max_grid);
+    case kP1StoreZ | kP1Cells: return kern::p1m<Acc, LOGFX_RA, LOGFX_RB, kP1StoreZ | kP1Cells, PL>(a, grid, s, max_grid);
+    }
+    return hipErrorInvalidValue;
+}
 template <class Acc>
 hipError_t pass1_any(const Pass1Args<typename kern::AccOps<Acc>::Taps> &a, int mode, int grid, hipStream_t s,
                      int *max_grid) {
+    if (mode & kP1Matrix) {
+        if constexpr (std::is_same<Acc, double>::value)
+            return pass1_matrix<Acc, 2>(a, mode & ~kP1Matrix, grid, s, max_grid);
+        return hipErrorInvalidValue;
+    }
     switch (mode) {
     case 0: return kern::p1<Acc, LOGFX_RA, LOGFX_RB, 0>(a, grid, s, max_grid);
     case kP1Maps: return kern::p1<Acc, LOGFX_RA, LOGFX_RB, kP1Maps>(a, grid, s, max_grid);

@@ -766,3 +766,117 @@ def test_int32_sums_at_their_largest(ctx, bits, form):
         assert np.array_equal(maps[f"Z{j}"].cpu().numpy(), o[f"Z{j}"])
     assert np.array_equal(out.cpu().numpy(), o["F"])
     assert rep["path"] == (logfx.PATH_INT32 if bits == 11 else logfx.PATH_FP64)
+
+
+def _symmetric_mask(rng, size, lo, hi, centre, corner):
+    """Random integer taps with the square's symmetries, not summing to zero."""
+    r = size // 2
+    m = np.zeros((size, size), np.float32)
+    for i in range(r + 1):
+        for j in range(i + 1):
+            v = float(rng.integers(lo, hi + 1))
+            for y, x in ((i, j), (j, i)):
+                for sy in (-1, 1):
+                    for sx in (-1, 1):
+                        m[r + sy * y, r + sx * x] = v
+    m[r, r] = centre
+    m[0, 0] = m[0, -1] = m[-1, 0] = m[-1, -1] = corner
+    return m
+
+
+MATRIX_CASES = {
+    "r1r2": (((3, 0.5), (5, 0.8)), (130, 517), 16, None),
+    "r1r4": (((3, 0.5), (9, 1.4)), (65, 249), 16, None),
+    "r2r4": (((5, 0.8), (9, 1.4)), (131, 500), 16, None),
+    "r3r3": (((7, 1.1), (7, 1.2)), (64, 248), 16, None),
+    "r4r4": (((9, 1.4), (9, 1.2)), (7, 300), 15, None),
+    "r3r4_narrow": (((7, 1.1), (9, 1.4)), (300, 7), 16, None),
+    "one_pixel": (((5, 0.8), (9, 1.4)), (1, 1), 16, None),
+    "one_row": (((5, 0.8), (9, 1.4)), (1, 400), 16, None),
+    "tap_limits": (None, (75, 260), 16, (65278, -32896)),        # twice the high limit at the centre
+    "tap_limits_low": (None, (75, 260), 16, (-65792, 32639)),
+    "past_the_limits": (None, (75, 260), 16, (65280, 32639)),    # one more at the centre: the FP64 form
+    "corner_past": (None, (75, 260), 16, (100, 32640)),
+    "zeros": (((5, 0.8), (9, 1.4)), (150, 260), 16, None),
+    "strips": (((5, 0.8), (9, 1.4)), (203, 330), 16, None),
+}
+
+
+@pytest.mark.parametrize("name", sorted(MATRIX_CASES))
+def test_matrix_form_agrees_with_the_fp64_form(ctx, name):
+    """16-bit images: pass 1 with the LoG on the matrix cores and in FP64 on
+    the vector unit, against each other and (E and F) the oracle; taps at the
+    limits of two bytes and past them, masks that do not sum to zero, every
+    parity of the radii, flat areas (zero responses), strips of 1 to 100
+    rows.  Both are exact; only the order in which the strengths are summed
+    differs (relative 1e-12 in sigma)."""
+    pair, (h, w), bits, taps = MATRIX_CASES[name]
+    rng = np.random.default_rng(5)
+    if pair:
+        orc_t, lib_t = masks(pair)
+    else:
+        m2 = _symmetric_mask(rng, 9, -900, 900, *taps)
+        orc_t = lib_t = (_symmetric_mask(rng, 5, -900, 900, taps[0], 77.0), m2)
+    img = rng.integers(0, 1 << bits, (h, w)).astype(np.uint16)
+    if name == "zeros":
+        img = (rng.integers(0, 3, (h // 10 + 1, w // 10 + 1)) * 30000).astype(np.uint16)
+        img = np.kron(img, np.ones((10, 10), np.uint16))[:h, :w]
+    dev, params = to_device(img), logfx.Params(*lib_t)
+    rows = (1, 7, 30, 31, 100) if name == "strips" else (64,)
+    try:
+        for r in rows:
+            got = []
+            ctx.set_option(logfx.OPT_ROWS1, r)
+            for form in (1, 0):
+                ctx.set_option(logfx.OPT_PACKED_LOG, form)
+                out, rep = ctx.extract(dev, params, bits=bits, report=True)
+                got.append((out.cpu().numpy(), rep))
+            assert got[0][1]["path"] == logfx.PATH_FP64
+            assert np.array_equal(got[0][0], got[1][0])
+            for k in ("zc_count", "extracted", "output"):
+                assert got[0][1][k] == got[1][1][k]
+            assert np.allclose(got[0][1]["sigma_g"], got[1][1]["sigma_g"], rtol=1e-12, atol=0)
+    finally:
+        ctx.set_option(logfx.OPT_PACKED_LOG, 1)
+        ctx.set_option(logfx.OPT_ROWS1, 64)
+    compare(got[0][0], run_oracle(img, orc_t), smooth=True, median_size=5)
+
+
+def test_matrix_form_under_capture_and_many_masks():
+    """A context's first call with a pair of masks writes their table; one
+    that is first met under capture, and pairs past the 64 a context keeps
+    tables for, run the other form.  Same maps, replays included, with other
+    masks used in between."""
+    import torch
+    img = np.random.default_rng(3).integers(0, 65536, (90, 300)).astype(np.uint16)
+    dev = to_device(img)
+    pars = [logfx.Params(logfx.make_log_mask(5, 0.6 + 0.01 * i, 16)[0], logfx.make_log_mask(9, 1.4, 16)[0])
+            for i in range(70)]
+    with logfx.Context(0) as c:
+        want = []
+        c.set_option(logfx.OPT_PACKED_LOG, 0)
+        for p in pars:
+            want.append(c.extract(dev, p).clone())
+        c.set_option(logfx.OPT_PACKED_LOG, 1)
+        graphs = []
+        for k, warm in ((0, True), (1, False)):
+            out = torch.empty(img.shape, dtype=torch.uint8, device="cuda")
+            s = torch.cuda.Stream()
+            s.wait_stream(torch.cuda.current_stream())
+            if warm:
+                with torch.cuda.stream(s):
+                    c.extract(dev, pars[k], out, stream=s)
+            torch.cuda.synchronize()
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g, stream=s):
+                c.extract(dev, pars[k], out, stream=s)
+            graphs.append((g, out, k))
+        for i, p in enumerate(pars):
+            assert torch.equal(c.extract(dev, p), want[i]), i
+            if i % 23 == 0:
+                for g, out, k in graphs:
+                    out.fill_(9)
+                    torch.cuda.synchronize()
+                    g.replay()
+                    torch.cuda.synchronize()
+                    assert torch.equal(out, want[k]), (i, k)
