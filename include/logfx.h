@@ -260,7 +260,9 @@ int logfx_extract_batch(logfx_ctx *ctx, int32_t n, const logfx_image *imgs, cons
 
 /* Context options (logfx_set_option / logfx_get_option). */
 enum {
-    LOGFX_OPT_ROWS1 = 1,      /* output rows per wave strip in pass 1 (1..1024, default 64) */
+    LOGFX_OPT_ROWS1 = 1,      /* output rows per wave strip in pass 1 (1..1024, default 64; until it is set,
+                                 by this option, logfx_tune or LOGFX_TILE, calls on fewer than 2^25
+                                 pixels take lower strips where those fill the device better) */
     LOGFX_OPT_ROWS2 = 2,      /* the same for pass 2 (default 64) */
     LOGFX_OPT_PERSISTENT = 3, /* batches: 1 = persistent launch, 0 = one workgroup per tile (default) */
     LOGFX_OPT_GRAPH = 4,      /* batches: 1 = replay a captured hipGraph (default), 0 = direct launches */

@@ -30,9 +30,11 @@ namespace {
 thread_local std::string g_thread_error;
 
 // Output rows per wave strip of each pass (tiles are kTileWaves strips wide).
+// Heights that were not asked for are upper bounds (strip_rows).
 struct TileCfg {
     int rows1 = 64;  // pass 1
     int rows2 = 64;  // pass 2
+    bool set1 = false, set2 = false;   // by an option, the tuner or the environment
 };
 
 // LOGFX_TILE="rows1,rows2" overrides the defaults (used by the tuner and
@@ -42,7 +44,7 @@ TileCfg tile_cfg_from_env() {
     if (const char *s = std::getenv("LOGFX_TILE")) {
         int a, b;
         if (std::sscanf(s, "%d,%d", &a, &b) == 2 && a >= 1 && a <= 1024 && b >= 1 && b <= 1024)
-            t.rows1 = a, t.rows2 = b;
+            t.rows1 = a, t.rows2 = b, t.set1 = t.set2 = true;
     }
     return t;
 }
@@ -634,9 +636,11 @@ struct ImageTiles {
     int tiles_x1, ntiles1, tiles_x2, ntiles2;
 };
 
-int tile_image(logfx_ctx *ctx, const logfx_image *img, const Plan &pl, bool storez, int rows1, ImageTiles &t) {
-    TileCfg c = ctx->tiles;
+int tile_image(logfx_ctx *ctx, const logfx_image *img, const Plan &pl, bool storez, int rows1, int rows2,
+               ImageTiles &t) {
+    TileCfg c;
     c.rows1 = rows1;
+    c.rows2 = rows2;
     const long long H = img->height, W = img->width;
     if (H >= (1LL << 30) || W >= (1LL << 30))
         return set_err(ctx, LOGFX_EUNSUPPORTED, "image sides must be below 2^30");
@@ -695,7 +699,7 @@ struct Call {
     bool storez = false;   // pass 1 stores the strengths in ctx->zmap, pass 2 reads them
     long long px = 0;      // pixels of all images (when the strengths are stored)
     const unsigned char *table = nullptr;   // taps of the matrix form, where it runs
-    int rows1 = 64;        // pass-1 strip height of this call
+    int rows1 = 64, rows2 = 64;   // strip heights of this call
     int cell_slots = 0, cell_rows = 0;   // LDS slots of pass 1's gate cell sums per tile
     std::vector<ImageTiles> tiles;
 };
@@ -716,6 +720,32 @@ void cell_layout(int n, const logfx_image *imgs, const Plan &pl, int rows, long 
         slots = std::max(slots, std::min(CX, (TW - 1) * CX / W + 2));
         crows = std::max(crows, std::min(CY, (rows - 1) * CY / H + 2));
     }
+}
+
+// Strip height for tiles `tw` columns wide, where none was asked for.  A
+// workgroup takes about rows + halo row times, alone on its CU each half as
+// long again (`alone`) as with others to fill its waits, so a call takes
+// about (rows + halo) max(alone, tiles per CU, rounded up) of them: low strips
+// where tall ones leave CUs idle, tall ones where the halo rows add up.
+// Pass 1, measured: 512^2 34 us with 64 rows, 13 with 8; 2000^2 45 and 31
+// with 24; 4000^2 82 and 77 with 48 (114 with 8); pass 2: 512^2 14.7 and 8.4
+// with 8, 2000^2 19.4 and 14.0 with 24, 6000^2 57 with 64 and 83 with 8.
+// From 2^25 pixels on, the tallest is within 4 % of the best.
+int strip_rows(int n, const logfx_image *imgs, long long tw, int most, int step, int halo, double alone) {
+    constexpr int kCus = 256;
+    if (n > 64) return most;
+    long long px = 0;
+    for (int i = 0; i < n; ++i) px += (long long)imgs[i].height * imgs[i].width;
+    if (px >= (1LL << 25)) return most;
+    int best = most;
+    double cost = 1e300;
+    for (int r = most; r >= std::min(most, 6); r -= step) {
+        long long tiles = 0;
+        for (int i = 0; i < n; ++i) tiles += ((imgs[i].width + tw - 1) / tw) * ((imgs[i].height + r - 1) / r);
+        const double c = (r + halo) * std::max(alone, (double)((tiles + kCus - 1) / kCus));
+        if (c < cost) cost = c, best = r;
+    }
+    return best;
 }
 
 // Device memory for the strengths of `px` pixels (ZMap); false if it cannot
@@ -745,7 +775,13 @@ int prepare(logfx_ctx *ctx, int n, const logfx_image *imgs, const logfx_params *
     if (n < 1 || !imgs) return set_err(ctx, LOGFX_EINVAL, "no images");
     int rc = check_all(ctx, &imgs[0], p, c.pl);
     if (rc != LOGFX_OK) return rc;
+    c.table = matrix_table(ctx, c.pl, s);
     c.rows1 = ctx->tiles.rows1;
+    c.rows2 = ctx->tiles.rows2;
+    // (the matrix form works through blocks of 8 rows, the strip's and one
+    // above and below it: 62, 54, ..)
+    if (!ctx->tiles.set1)
+        c.rows1 = strip_rows(n, imgs, tile_out_width(kHalo1), c.table ? 62 : 64, c.table ? 8 : 4, 6, 1.7);
     if (features) {
         // pass 1 keeps a slot per (cell row, cell column) a tile spans in
         // LDS beside the tile: lower the strip height where they would not
@@ -789,7 +825,8 @@ int prepare(logfx_ctx *ctx, int n, const logfx_image *imgs, const logfx_params *
             ctx->ccap = px;
         }
     }
-    c.table = matrix_table(ctx, c.pl, s);
+    if (!ctx->tiles.set2 && c.storez)
+        c.rows2 = strip_rows(n, imgs, tile_out_width(c.pl.std5 ? kHalo2Z5 : kHalo2Z), 64, 8, 4, 1.5);
     const int bits0 = imgs[0].bits == 0 ? (imgs[0].dtype == LOGFX_U8 ? 8 : 16) : imgs[0].bits;
     c.n = n;
     c.tiles.resize(n);
@@ -804,7 +841,7 @@ int prepare(logfx_ctx *ctx, int n, const logfx_image *imgs, const logfx_params *
                                                   "dtype and bits", i);
         }
         if (need_out && (!outs || !outs[i])) return set_err(ctx, LOGFX_EINVAL, "output %d is NULL", i);
-        if ((rc = tile_image(ctx, &imgs[i], c.pl, c.storez, c.rows1, c.tiles[i])) != LOGFX_OK) return rc;
+        if ((rc = tile_image(ctx, &imgs[i], c.pl, c.storez, c.rows1, c.rows2, c.tiles[i])) != LOGFX_OK) return rc;
         t1 += c.tiles[i].ntiles1;
         t2 += c.tiles[i].ntiles2;
     }
@@ -934,7 +971,7 @@ void fill_args(const Call &c, logfx_ctx *ctx, const logfx_params *p, double *con
     a1.rows = c.rows1;
     a1.partials = ctx->partials;
     a1.counts = ctx->counts1;
-    a2.rows = ctx->tiles.rows2;
+    a2.rows = c.rows2;
     a2.stats = ctx->stats;
     a2.counts = ctx->counts2;
     a2.smooth = p->smooth != LOGFX_SMOOTH_NEVER;   // GATE without a gate falls back to ALWAYS
@@ -1078,7 +1115,7 @@ int build_launches(logfx_ctx *ctx, const Call &c, const logfx_params *p, double 
         for (int i = 0; i < k.ncas; ++i) {
             LevelArgs &l = k.lev[i];
             l.L = c.L;
-            l.rows = ctx->tiles.rows2;
+            l.rows = c.rows2;
             l.median_size = c.pl.cas[i];
             l.from_scratch = (k.ncas - i) % 2;
             l.scratch = ctx->cmap;
@@ -1230,7 +1267,7 @@ int run(logfx_ctx *ctx, int n, const logfx_image *imgs, const logfx_params *p, u
              maps ? "extract_maps" : (n > 1 ? "extract_batch" : "extract"), n, (long long)imgs[0].height,
              (long long)imgs[0].width,
              !c.pl.i32 ? "fp64" : k.packed ? "int32 (packed)" : "int32", c.pl.ra, c.pl.rb,
-             c.L.total1, c.L.total2, c.rows1, ctx->tiles.rows2, c.storez ? "stored strengths" : "recomputed strengths",
+             c.L.total1, c.L.total2, c.rows1, c.rows2, c.storez ? "stored strengths" : "recomputed strengths",
              p->smooth, gated ? " (gated)" : "", use_graph ? ", graph" : "");
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
     const bool timed = ctx->timing && !maps;
@@ -1536,6 +1573,7 @@ int logfx_extract_noalloc(logfx_ctx *ctx, const logfx_image *img, const logfx_pa
     if (!out) return set_err(ctx, LOGFX_EINVAL, "output 0 is NULL");
     Call c;   // c.tiles stays empty: this path allocates nothing, host or device
     c.rows1 = ctx->tiles.rows1;
+    c.rows2 = ctx->tiles.rows2;
     int rc = check_all(ctx, img, p, c.pl);
     if (rc != LOGFX_OK) return rc;
     if (c.pl.std5 || c.pl.ncas > 0 || c.pl.region > 0)
@@ -1544,7 +1582,7 @@ int logfx_extract_noalloc(logfx_ctx *ctx, const logfx_image *img, const logfx_pa
     if (p->smooth == LOGFX_SMOOTH_GATE && ctx->gate.loaded)
         return set_err(ctx, LOGFX_EINVAL, "the gate needs context memory (logfx_extract runs it)");
     ImageTiles t;
-    if ((rc = tile_image(ctx, img, c.pl, false, ctx->tiles.rows1, t)) != LOGFX_OK) return rc;
+    if ((rc = tile_image(ctx, img, c.pl, false, c.rows1, c.rows2, t)) != LOGFX_OK) return rc;
     if (t.ntiles1 > kNoAllocMaxTiles || t.ntiles2 > kNoAllocMaxTiles)
         return set_err(ctx, LOGFX_EINVAL, "a %lld x %lld image needs %d pass-1 and %d pass-2 tiles; the static "
                                           "scratch holds %lld per pass", (long long)img->height,
@@ -1603,6 +1641,7 @@ int logfx_set_option(logfx_ctx *ctx, int32_t option, int64_t value) {
     case LOGFX_OPT_ROWS2:
         if (value < 1 || value > 1024) return set_err(ctx, LOGFX_EINVAL, "rows %lld not in 1..1024", (long long)value);
         (option == LOGFX_OPT_ROWS1 ? ctx->tiles.rows1 : ctx->tiles.rows2) = (int)value;
+        (option == LOGFX_OPT_ROWS1 ? ctx->tiles.set1 : ctx->tiles.set2) = true;
         return LOGFX_OK;
     case LOGFX_OPT_PERSISTENT: ctx->persistent = value != 0; return LOGFX_OK;
     case LOGFX_OPT_GRAPH: ctx->graph = value != 0; return LOGFX_OK;
@@ -1876,6 +1915,7 @@ int logfx_tune(logfx_ctx *ctx, int32_t n, const logfx_image *imgs, const logfx_p
         const TileCfg saved = ctx->tiles;
         const bool saved_p = ctx->persistent, saved_g = ctx->graph, saved_t = ctx->timing;
         ctx->graph = false;   // direct launches, so that each kernel is timed on its own
+        ctx->tiles.set1 = ctx->tiles.set2 = true;
         const int cand[] = {32, 40, 48, 56, 64, 96};
         constexpr int ncand = sizeof cand / sizeof cand[0];
         // the candidates are timed round-robin, twice, and each keeps its
@@ -1943,6 +1983,7 @@ int logfx_tune(logfx_ctx *ctx, int32_t n, const logfx_image *imgs, const logfx_p
     }
     ctx->tiles.rows1 = best.rows1;
     ctx->tiles.rows2 = best.rows2;
+    ctx->tiles.set1 = ctx->tiles.set2 = true;
     ctx->persistent = best.persistent != 0;
     if (res) *res = best;
     return LOGFX_OK;

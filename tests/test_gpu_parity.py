@@ -880,3 +880,28 @@ def test_matrix_form_under_capture_and_many_masks():
                     g.replay()
                     torch.cuda.synchronize()
                     assert torch.equal(out, want[k]), (i, k)
+
+
+@pytest.mark.parametrize("h,w,kw", [(131, 257, {}), (512, 512, dict(median_size=3)), (700, 90, {}), (40, 3000, {}),
+                                    (1500, 1400, dict(median_cascade=(3, 5))), (333, 1200, dict(smooth=False)),
+                                    (600, 700, dict(std5_max=5.0))])
+def test_default_strips_give_what_64_row_strips_give(h, w, kw):
+    """A context whose strip heights were not set takes lower strips on small
+    images; the map and the counts are those of 64-row strips, singly and in
+    a batch (sigma: the same sums in another order, 1e-12)."""
+    import torch
+    img = scenes.panchromatic(h, w, 77, n_rect=max(3, h * w // 6000), noise_sigma=4.0, sp_density=0.02, bits=8)
+    dev, params = to_device(img), logfx.Params(*masks()[1], **kw)
+    with logfx.Context(0) as low, logfx.Context(0) as tall:
+        tall.set_option(logfx.OPT_ROWS1, 64)
+        tall.set_option(logfx.OPT_ROWS2, 64)
+        a, ra = low.extract(dev, params, report=True)
+        b, rb = tall.extract(dev, params, report=True)
+        assert low.get_option(logfx.OPT_ROWS1) == 64
+        c = low.extract_batch([dev, dev[: h // 2]], params)
+        d = tall.extract_batch([dev, dev[: h // 2]], params)
+        torch.cuda.synchronize()
+        assert torch.equal(a, b) and torch.equal(c[0], d[0]) and torch.equal(c[1], d[1]) and torch.equal(a, c[0])
+    for k in ("zc_count", "extracted", "output"):
+        assert ra[k] == rb[k]
+    assert np.allclose(ra["sigma_g"], rb["sigma_g"], rtol=1e-12, atol=0)
