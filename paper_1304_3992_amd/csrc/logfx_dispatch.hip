@@ -72,22 +72,9 @@ __global__ __launch_bounds__(kFinThreads) void finalize_kernel(FinalizeArgs a) {
         __syncthreads();
     }
     if (t == 0) {
-        const long long npx = J.img.H * J.img.W;
-        const double n = (double)npx;
-        DevStats &st = a.stats[image];
-        for (int j = 0; j < 2; ++j) {
-            const double S = sd[j][0], Q = sd[2 + j][0];
-            double var = npx > 1 ? (Q - S * (S / n)) / (n - 1.0) : 0.0;
-            if (!(var > 0.0)) var = 0.0;
-            const double sg = sqrt(var);
-            const double T = a.std_mode == 0 ? a.std_k * sg : a.abs_thr[j];
-            st.sum[j] = S;
-            st.sumsq[j] = Q;
-            st.sigma[j] = sg;
-            st.thresh[j] = T;
-            st.thr72[j] = 72.0 * T * T;
-            st.zc[j] = sc[j][0];
-        }
+        const double v[4] = {sd[0][0], sd[1][0], sd[2][0], sd[3][0]};
+        const long long z[2] = {sc[0][0], sc[1][0]};
+        image_stats(a, J.img.H * J.img.W, v, z, a.stats[image]);
     }
 }
 

@@ -919,6 +919,7 @@ struct Launches {
         Pass2Args<OrbitTapsD> d;
     } p2;
     FinalizeArgs fin;
+    bool fused;                    // pass 2 does the finalize
     int grid1, grid2;
     int ra, rb;
     bool i32;                      // exact int32 LoG, else FP64
@@ -1019,7 +1020,7 @@ hipError_t launch_all(const Launches &k, hipStream_t s, hipEvent_t *ev, int unti
         return gate::launch_forward(k.net, s, k.flags, k.decisions);
     }
     if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return e;
-    if ((e = launch_finalize(k.fin, s)) != hipSuccess) return e;
+    if (!k.fused && (e = launch_finalize(k.fin, s)) != hipSuccess) return e;
     if (k.gated) {
         if ((e = gate::launch_finish_features(k.fin.L, k.cells, k.maxval, k.feats, k.gx, k.gy, s)) != hipSuccess ||
             (e = gate::launch_forward(k.net, s, k.flags, k.decisions)) != hipSuccess)
@@ -1130,6 +1131,9 @@ int build_launches(logfx_ctx *ctx, const Call &c, const logfx_params *p, double 
     k.fin.std_k = p->std_k;
     for (int slot = 0; slot < 2; ++slot) k.fin.abs_thr[slot] = p->std_k / c.pl.mi[c.pl.order[slot]].unit;
     k.fin.stats = ctx->stats;
+    k.fused = c.n == 1 && k.storez && !k.gated && c.L.total1 <= kFuseTiles;
+    if (k.i32) k.p2.i.fin = k.fin, k.p2.i.fused = k.fused;
+    else k.p2.d.fin = k.fin, k.p2.d.fused = k.fused;
     k.grid1 = c.L.total1;
     k.grid2 = c.L.total2;
     if (c.n > 1 && ctx->persistent && !k.dbg) {

@@ -178,6 +178,16 @@ struct Pass1Args {
     int cell_slots, cell_rows;
 };
 
+struct FinalizeArgs {
+    Launch L;
+    const double *partials;
+    const long long *counts;
+    int std_mode;          // 0 relative, 1 absolute
+    double std_k;
+    double abs_thr[2];     // absolute threshold per mask in grid units (std_mode 1)
+    DevStats *stats;       // [nimg]
+};
+
 template <class Taps>
 struct Pass2Args {
     Launch L;
@@ -186,6 +196,9 @@ struct Pass2Args {
     int zc_thr_i[2];
     int rows;
     const DevStats *stats;  // [nimg] thresholds from the finalize kernel
+    FinalizeArgs fin;       // fused: what that kernel would take
+    int fused;              // single images of few pass-1 tiles (kFuseTiles): every workgroup of the
+                            // stored-strength pass 2 forms the thresholds, the first writes stats
     int *counts;            // [total2][2]: E pixels, output pixels per tile
     int smooth;             // 0 = E, 1 = hybrid median of E
     int median_size;        // 3 or 5
@@ -201,6 +214,9 @@ struct Pass2Args {
     int reg_gx;             // region of this side, reg_gx regions per region row, row-major
 };
 
+// Pass-1 tiles up to which pass 2 takes the finalize over.
+constexpr int kFuseTiles = 512;
+
 // One further level of the hybrid median cascade, on maps of 0/1 bytes,
 // with the tiling of the stored-strength pass 2 (halo 3, or 4 with the 5x5
 // first stage).
@@ -212,16 +228,6 @@ struct LevelArgs {
     uint8_t *scratch;       // image i at scratch + jobs[i].zoff, pitch W
     const int *med_flags;   // [nimg] or nullptr: images whose flag is 0 are copied unfiltered
     int *counts;            // [total2][2] or nullptr: each tile's output count into counts[2 t + 1]
-};
-
-struct FinalizeArgs {
-    Launch L;
-    const double *partials;
-    const long long *counts;
-    int std_mode;          // 0 relative, 1 absolute
-    double std_k;
-    double abs_thr[2];     // absolute threshold per mask in grid units (std_mode 1)
-    DevStats *stats;       // [nimg]
 };
 
 // Launchers (defined in logfx_dispatch.hip).  They return hipSuccess or the

@@ -803,6 +803,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPass1Waves
     });
 }
 
+// ------------------------------------------------------------- statistics
+// sigma_j, T_j and 72 T_j^2 of an image from the sums over its pixels:
+// s[j] = sum Z_j, s[2 + j] = sum Z_j^2, c[j] = pixels with Z_j != 0.
+__device__ inline void image_stats(const FinalizeArgs &a, long long npx, const double (&s)[4], const long long (&c)[2],
+                                   DevStats &st) {
+    const double n = (double)npx;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const double S = s[j], Q = s[2 + j];
+        double var = npx > 1 ? (Q - S * (S / n)) / (n - 1.0) : 0.0;
+        if (!(var > 0.0)) var = 0.0;
+        const double sg = sqrt(var);
+        const double T = a.std_mode == 0 ? a.std_k * sg : a.abs_thr[j];
+        st.sum[j] = S;
+        st.sumsq[j] = Q;
+        st.sigma[j] = sg;
+        st.thresh[j] = T;
+        st.thr72[j] = 72.0 * T * T;
+        st.zc[j] = c[j];
+    }
+}
+
 // ------------------------------------------------------------- pass 2
 // MED: 0 = no smoothing (output E), 3 or 5 = hybrid median window, -3 or
 // -5 = that window on the images whose med_flags entry is set, none on the

@@ -183,6 +183,57 @@ template <class Acc> using LowBits = typename std::conditional<std::is_same<Acc,
 
 template <int MED, bool LOOP, bool S5> constexpr int kPass2zWaves = S5 ? 3 : MED < 0 || LOOP ? 4 : 5;
 
+// The finalize of a single image of few pass-1 tiles, by every workgroup for
+// itself (each thread at most kFuseTiles / 256 tiles, then a butterfly per
+// wave and the waves in order: the same bits in all of them).  A launch of
+// its own for it took 4.7 us of 20 at 512^2.
+__device__ inline void fused_finalize(const FinalizeArgs &a, double (&thr72)[2]) {
+    __shared__ double sd[4][kTileWaves];
+    const ImageJob &J = a.L.one;
+    const int t = threadIdx.x;
+    double s[4] = {0, 0, 0, 0};
+    int c[2] = {0, 0};   // below 2^31: at most kFuseTiles tiles of 248 x 1024 pixels
+#pragma unroll
+    for (int u = 0; u < kFuseTiles / 256; ++u) {
+        const int i = t + 256 * u;
+        if (i < J.ntiles1) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) s[k] += a.partials[(long long)i * 4 + k];
+            if (blockIdx.x == 0) {
+                c[0] += (int)a.counts[(long long)i * 2];
+                c[1] += (int)a.counts[(long long)i * 2 + 1];
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        s[k] = wave_sum(s[k]);
+        if (t % kWave == 0) sd[k][t / kWave] = s[k];
+    }
+    long long z[2] = {0, 0};
+    if (blockIdx.x == 0) {
+        __shared__ int sc[2][kTileWaves];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            c[k] = wave_sum(c[k]);
+            if (t % kWave == 0) sc[k][t / kWave] = c[k];
+        }
+        __syncthreads();
+        for (int w = 0; w < kTileWaves; ++w) {
+            z[0] += sc[0][w];
+            z[1] += sc[1][w];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) s[k] = ((sd[k][0] + sd[k][1]) + sd[k][2]) + sd[k][3];
+    DevStats st;
+    image_stats(a, J.img.H * J.img.W, s, z, st);
+    if (blockIdx.x == 0 && t == 0) a.stats[0] = st;
+    thr72[0] = st.thr72[0];
+    thr72[1] = st.thr72[1];
+}
+
 // S5: with the 5x5 first stage, E_j(p) also needs the 5x5 deviation of Z_j
 // above std5_max; the halo grows to 4 columns (56 output columns per wave).
 // SPLIT: the form of the strengths (the integer path has only this one).
@@ -223,7 +274,13 @@ __global__ __launch_bounds__(256) void pass2z_kernel(Pass2Args<typename AccOps<A
         if constexpr (MED < 0) {
             if (mixed) rx = min(max(xc, 0), W - 1) / a.region;
         }
-        const double thr72[2] = {a.stats[image].thr72[0], a.stats[image].thr72[1]};
+        double thr72[2];
+        if (MED >= 0 && !LOOP && a.fused) {
+            fused_finalize(a.fin, thr72);
+        } else {
+            thr72[0] = a.stats[image].thr72[0];
+            thr72[1] = a.stats[image].thr72[1];
+        }
         // FP32 strengths are in code steps (split) or scaled by zscale (pairs)
         const double unit[2] = {SPLIT ? __longlong_as_double((long long)(1023 - a.z.shift[0]) << 52) : a.zscale[0],
                                 SPLIT ? __longlong_as_double((long long)(1023 - a.z.shift[1]) << 52) : a.zscale[1]};

@@ -905,3 +905,27 @@ def test_default_strips_give_what_64_row_strips_give(h, w, kw):
     for k in ("zc_count", "extracted", "output"):
         assert ra[k] == rb[k]
     assert np.allclose(ra["sigma_g"], rb["sigma_g"], rtol=1e-12, atol=0)
+
+
+@pytest.mark.parametrize("h", [255, 256, 257])
+def test_finalize_in_pass2_at_its_limit(ctx, h):
+    """Strips of one row, two tiles wide: up to 512 pass-1 tiles pass 2 forms
+    the thresholds itself, past them (and when it recomputes the strengths)
+    the finalize kernel does.  Same map and counts, sigma within 1e-12."""
+    img = np.random.default_rng(h).integers(0, 2048, (h, 490)).astype(np.uint16)
+    dev, params = to_device(img), logfx.Params(*masks()[1])
+    got = []
+    try:
+        ctx.set_option(logfx.OPT_ROWS1, 1)
+        for store in (1, 0):
+            ctx.set_option(logfx.OPT_STORE_Z, store)
+            out, rep = ctx.extract(dev, params, bits=11, report=True)
+            got.append((out.cpu().numpy(), rep))
+    finally:
+        ctx.set_option(logfx.OPT_STORE_Z, 1)
+        ctx.set_option(logfx.OPT_ROWS1, 64)
+    assert np.array_equal(got[0][0], got[1][0])
+    for k in ("zc_count", "extracted", "output"):
+        assert got[0][1][k] == got[1][1][k]
+    for k in ("sigma_g", "thresh"):
+        assert np.allclose(got[0][1][k], got[1][1][k], rtol=1e-12, atol=0)
