@@ -214,7 +214,7 @@ int logfx_extract(logfx_ctx *ctx, const logfx_image *img, const logfx_params *p,
  * graph capture, tight serving loops, harnesses that forbid allocation.
  * The same pipeline and the same output bytes as logfx_extract; the call
  * allocates nothing, host or device.  Its scratch (per-tile sums and counts
- * of both passes, the image's statistics) is a fixed static array of 3.5
+ * of both passes, the image's statistics) is a fixed static array of 4.5
  * MiB on each device, held until the process ends; pass 2 recomputes the
  * crossing strengths (as LOGFX_OPT_STORE_Z = 0 does) instead of storing
  * them.  The tile heights come from ctx's options; no report, no timing.

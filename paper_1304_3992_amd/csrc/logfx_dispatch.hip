@@ -30,12 +30,12 @@ __global__ __launch_bounds__(kFinThreads) void finalize_kernel(FinalizeArgs a) {
     const int t = threadIdx.x;
     const int image = blockIdx.x;
     const ImageJob J = job_of(a.L, image);
-    double s[4] = {0, 0, 0, 0};
-    long long c[2] = {0, 0};
     // thread t adds tiles t, t + kFinThreads, ... in that order; U tiles'
     // loads are in flight at once (a tile past the end adds zeros, which
     // leaves the sums unchanged)
     constexpr int U = 8;
+    long long c[2] = {0, 0};
+    double s[4] = {0, 0, 0, 0};
     for (int i0 = t; i0 < J.ntiles1; i0 += kFinThreads * U) {
         double v[U][4];
         long long w[U][2];
@@ -45,7 +45,7 @@ __global__ __launch_bounds__(kFinThreads) void finalize_kernel(FinalizeArgs a) {
             const long long at = (long long)J.base1 + i;
             const bool in = i < J.ntiles1;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) v[u][k] = in ? a.partials[at * 4 + k] : 0.0;
+            for (int k = 0; k < 4; ++k) v[u][k] = in ? __longlong_as_double((long long)a.partials[at * kTileSums + k]) : 0.0;
             w[u][0] = in ? a.counts[at * 2] : 0;
             w[u][1] = in ? a.counts[at * 2 + 1] : 0;
         }
@@ -76,6 +76,52 @@ __global__ __launch_bounds__(kFinThreads) void finalize_kernel(FinalizeArgs a) {
         const long long z[2] = {sc[0][0], sc[1][0]};
         image_stats(a, J.img.H * J.img.W, v, z, a.stats[image]);
     }
+}
+
+// The same for the integer path's exact sums, in any order: a butterfly per
+// wave, then the waves.
+__global__ __launch_bounds__(kFinThreads) void finalize_exact_kernel(FinalizeArgs a) {
+    constexpr int W = kTileSums + 2, NW = kFinThreads / kWave;
+    __shared__ unsigned long long sw[W][NW];
+    const int t = threadIdx.x, image = blockIdx.x;
+    const ImageJob J = job_of(a.L, image);
+    unsigned long long v[W] = {};   // the tile sums, then the two counts
+#pragma unroll 4
+    for (int i = t; i < J.ntiles1; i += kFinThreads) {
+        const long long at = (long long)J.base1 + i;
+#pragma unroll
+        for (int k = 0; k < kTileSums; ++k) v[k] += a.partials[at * kTileSums + k];
+        v[kTileSums] += (unsigned long long)a.counts[at * 2];
+        v[kTileSums + 1] += (unsigned long long)a.counts[at * 2 + 1];
+    }
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+        v[k] = wave_sum(v[k]);
+        if (t % kWave == 0) sw[k][t / kWave] = v[k];
+    }
+    __syncthreads();
+    if (t >= kWave) return;
+    // lane 16 (k mod 4) + w of the first wave takes wave w's word k, in two rounds
+    static_assert(NW == 16 && W == 8, "words of 16 waves");
+    unsigned long long r[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        r[h] = sw[4 * h + t / NW][t % NW];
+#pragma unroll
+        for (int off = NW / 2; off > 0; off >>= 1) r[h] += __shfl_xor(r[h], off);
+    }
+    unsigned long long q[kTileSums];
+    long long z[2];
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+        const unsigned long long x = __shfl(r[k / 4], NW * (k % 4));
+        if (k < kTileSums) q[k < kTileSums ? k : 0] = x;
+        else z[k & 1] = (long long)x;
+    }
+    if (t != 0) return;
+    double s[4];
+    exact_sums(q, s);
+    image_stats(a, J.img.H * J.img.W, s, z, a.stats[image]);
 }
 
 __global__ __launch_bounds__(256) void write_table(MatTable t, unsigned char *dst) {
@@ -138,7 +184,8 @@ hipError_t noalloc_scratch(int device, void **ptr) {
 }
 
 hipError_t launch_finalize(const FinalizeArgs &a, hipStream_t s) {
-    hipLaunchKernelGGL(kern::finalize_kernel, dim3(a.L.nimg), dim3(kern::kFinThreads), 0, s, a);
+    if (a.exact) hipLaunchKernelGGL(kern::finalize_exact_kernel, dim3(a.L.nimg), dim3(kern::kFinThreads), 0, s, a);
+    else hipLaunchKernelGGL(kern::finalize_kernel, dim3(a.L.nimg), dim3(kern::kFinThreads), 0, s, a);
     return hipGetLastError();
 }
 

@@ -64,7 +64,7 @@ struct logfx_ctx {
     uint8_t *cmap = nullptr;         // 0/1 maps between the levels of a median cascade
     long long ccap = 0;              // bytes
     // device scratch
-    double *partials = nullptr;      // [cap1][4]
+    unsigned long long *partials = nullptr;   // [cap1][kTileSums]
     long long *counts1 = nullptr;    // [cap1][2]
     int *counts2 = nullptr;          // [cap2][2]
     DevStats *stats = nullptr;       // [capn]
@@ -216,7 +216,7 @@ int ensure_scratch(logfx_ctx *ctx, long long n1, long long n2, long long nimg) {
     if (n1 > ctx->cap1 || n2 > ctx->cap2 || nimg > ctx->capn) ctx->tab_valid = false;
     if (n1 > ctx->cap1) {
         ctx->cap1 = 0;
-        if ((rc = realloc_dev(ctx, ctx->partials, n1 * 4)) != LOGFX_OK ||
+        if ((rc = realloc_dev(ctx, ctx->partials, n1 * kTileSums)) != LOGFX_OK ||
             (rc = realloc_dev(ctx, ctx->counts1, n1 * 2)) != LOGFX_OK ||
             (rc = realloc_dev(ctx, ctx->owner1, n1)) != LOGFX_OK)
             return rc;
@@ -409,6 +409,23 @@ int analyze_mask(logfx_ctx *ctx, const logfx_mask &m, int which, MaskInfo &mi, b
     return LOGFX_OK;
 }
 
+// Bound on a crossing's strength in grid units: the largest difference of the
+// responses of two of the five pixels, maxpix times the positive part of the
+// difference of the mask and the mask moved by their offset, summed.
+double strength_bound(const MaskInfo &mi, double maxpix) {
+    static const int off[6][2] = {{0, 1}, {1, 0}, {1, 1}, {1, -1}, {0, 2}, {2, 0}};
+    const int s = mi.size;
+    auto tap = [&](int y, int x) { return y < 0 || y >= s || x < 0 || x >= s ? 0.0 : mi.k[y * s + x]; };
+    double most = 0.0;
+    for (const auto &o : off) {   // the opposite offsets give the same by symmetry of the mask
+        double sum = 0.0;
+        for (int y = -2; y < s + 2; ++y)
+            for (int x = -2; x < s + 2; ++x) sum += std::max(0.0, tap(y, x) - tap(y - o[0], x - o[1]));
+        most = std::max(most, sum);
+    }
+    return most * maxpix;
+}
+
 struct Plan {
     MaskInfo mi[2];
     int order[2];         // kernel mask slot -> user mask index
@@ -534,6 +551,11 @@ int check_all(logfx_ctx *ctx, const logfx_image *img, const logfx_params *p, Pla
         if (!(pos < 1073741824.0 && bound - pos < 1073741824.0 && bound < 2147483648.0 &&
               pl.mi[j].maxabs < 8388608.0))
             pl.i32 = false;
+        // and kFoldRows squares of strengths below 2^64 - 2^48 (those of 2^30 always are)
+        if (pl.i32 && bound >= 1073741824.0) {
+            const double z = strength_bound(pl.mi[j], pl.maxpix);
+            if (!(z * z * kFoldRows < 18446462598732840960.0)) pl.i32 = false;
+        }
         if (!(bound < 1073741824.0 && pl.mi[j].maxabs < 8388608.0)) int_ok = false;  // 2^30, 2^23
         if (!(bound < 4503599627370496.0)) f64_ok = false;                              // 2^52
     }
@@ -778,10 +800,12 @@ int prepare(logfx_ctx *ctx, int n, const logfx_image *imgs, const logfx_params *
     c.table = matrix_table(ctx, c.pl, s);
     c.rows1 = ctx->tiles.rows1;
     c.rows2 = ctx->tiles.rows2;
-    // (the matrix form works through blocks of 8 rows, the strip's and one
-    // above and below it: 62, 54, ..)
+    // (The FP64 path, whose sums round, keeps to one height, so that an
+    // image's statistics are the same bits in a batch and alone.  Its matrix
+    // form works through blocks of 8 rows, the strip's and one above and below
+    // it: 62 rows.)
     if (!ctx->tiles.set1)
-        c.rows1 = strip_rows(n, imgs, tile_out_width(kHalo1), c.table ? 62 : 64, c.table ? 8 : 4, 6, 1.7);
+        c.rows1 = c.pl.i32 ? strip_rows(n, imgs, tile_out_width(kHalo1), 64, 4, 6, 1.7) : c.table ? 62 : c.rows1;
     if (features) {
         // pass 1 keeps a slot per (cell row, cell column) a tile spans in
         // LDS beside the tile: lower the strip height where they would not
@@ -1126,6 +1150,7 @@ int build_launches(logfx_ctx *ctx, const Call &c, const logfx_params *p, double 
     }
     k.fin.L = c.L;
     k.fin.partials = ctx->partials;
+    k.fin.exact = k.i32;
     k.fin.counts = ctx->counts1;
     k.fin.std_mode = p->std_mode;
     k.fin.std_k = p->std_k;
@@ -1607,7 +1632,7 @@ int logfx_extract_noalloc(logfx_ctx *ctx, const logfx_image *img, const logfx_pa
     if ((rc = build_launches(ctx, c, p, nullptr, nullptr, k, 0)) != LOGFX_OK) return rc;
     // the sums, counts and statistics in the static array
     unsigned char *base = static_cast<unsigned char *>(ctx->noalloc);
-    double *partials = reinterpret_cast<double *>(base + kNoAllocPartialsOff);
+    unsigned long long *partials = reinterpret_cast<unsigned long long *>(base + kNoAllocPartialsOff);
     long long *counts1 = reinterpret_cast<long long *>(base + kNoAllocCounts1Off);
     int *counts2 = reinterpret_cast<int *>(base + kNoAllocCounts2Off);
     DevStats *stats = reinterpret_cast<DevStats *>(base + kNoAllocStatsOff);

@@ -124,6 +124,15 @@ struct ZMap {
 };
 constexpr int kZSplitBits = 47;   // strengths of the split form are below 2^47
 
+// Words of a tile's sums.  Integer path (exact): sum Z_1, sum Z_2, the sums
+// over the lanes of the low 32 bits of their sums of Z_j^2, and of the words
+// above.  Being exact, the statistics of an image do not depend on how it was
+// cut into tiles or in which order they are added.  FP64 path: sum Z_1, sum
+// Z_2, sum Z_1^2, sum Z_2^2 as doubles, added in a fixed order.
+constexpr int kTileSums = 6;
+// Strengths of the integer path: kFoldRows of their squares, and 2^48, fit 64 bits.
+constexpr int kFoldRows = 9;
+
 // One image of a launch: its input, its output and where its tiles sit in
 // the launch's tile list.
 struct ImageJob {
@@ -155,7 +164,7 @@ struct Pass1Args {
     double zc_thr[2];      // zero-crossing threshold per mask, grid units
     int zc_thr_i[2];       // the same for integer strengths: floor, capped at INT_MAX
     int rows;              // output rows per wave strip
-    double *partials;      // [total1][4]: sum Z1, sum Z2, sum Z1^2, sum Z2^2 per tile
+    unsigned long long *partials;   // [total1][kTileSums]: the tile's sums of strengths and squares
     long long *counts;     // [total1][2]: crossings of mask 1, mask 2 per tile
     // Optional FP64 maps of a single image (LoG units = grid units * unit[j]).
     double *dbgL[2];
@@ -180,7 +189,8 @@ struct Pass1Args {
 
 struct FinalizeArgs {
     Launch L;
-    const double *partials;
+    const unsigned long long *partials;
+    int exact;             // the tile sums are integers
     const long long *counts;
     int std_mode;          // 0 relative, 1 absolute
     double std_k;
@@ -259,8 +269,8 @@ hipError_t launch_pass2z_d(const Pass2Args<OrbitTapsD> &a, int grid, hipStream_t
 // logfx_dispatch.hip): the per-tile sums and counts of both passes and the
 // image's statistics, for at most kNoAllocMaxTiles tiles per pass.
 constexpr long long kNoAllocMaxTiles = 65536;
-constexpr size_t kNoAllocPartialsOff = 0;                                              // double [T][4]
-constexpr size_t kNoAllocCounts1Off = kNoAllocPartialsOff + kNoAllocMaxTiles * 4 * sizeof(double);  // i64 [T][2]
+constexpr size_t kNoAllocPartialsOff = 0;                                              // u64 [T][kTileSums]
+constexpr size_t kNoAllocCounts1Off = kNoAllocPartialsOff + kNoAllocMaxTiles * kTileSums * 8;       // i64 [T][2]
 constexpr size_t kNoAllocCounts2Off = kNoAllocCounts1Off + kNoAllocMaxTiles * 2 * sizeof(long long); // i32 [T][2]
 constexpr size_t kNoAllocStatsOff = kNoAllocCounts2Off + kNoAllocMaxTiles * 2 * sizeof(int);        // DevStats
 constexpr size_t kNoAllocBytes = (kNoAllocStatsOff + sizeof(DevStats) + 255) / 256 * 256;

@@ -262,6 +262,78 @@ __device__ inline int wave_sum(int v) {
     return v;
 }
 
+__device__ inline unsigned long long wave_sum(unsigned long long v) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    return v;
+}
+
+// Sum over the wave by DPP (row scans, then row totals passed on), the same in
+// every lane: three vector instructions a step instead of two LDS permutes.
+template <int CTRL, int ROWS>
+__device__ inline unsigned long long dpp_add(unsigned long long v) {
+    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)v, CTRL, ROWS, 0xf, false);
+    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(v >> 32), CTRL, ROWS, 0xf, false);
+    return v + ((unsigned long long)hi << 32 | lo);
+}
+__device__ inline unsigned long long wave_total(unsigned long long v) {
+    v = dpp_add<0x111, 0xf>(v);   // row_shr:1, 2, 4, 8: lane 15 of each row holds its sum
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+    v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3: lane 63 holds the total
+    return (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), 63) << 32 |
+           (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, 63);
+}
+
+// A lane's sums of strengths and of their squares.  Integer path: exact, each
+// a 64-bit multiply-add per strength (FP64 takes a conversion, an add and a
+// multiply-add).  The squares' sum is folded, its top 16 bits moved to a sum
+// of their own, at least every kFoldRows rows; the host lets strengths into
+// this path only if kFoldRows squares and 2^48 fit 64 bits.  FP64 path: FP64, in row
+// order.
+template <class Acc> struct LaneSums;
+template <> struct LaneSums<int> {
+    unsigned long long s[2] = {0, 0}, q[2] = {0, 0};
+    unsigned h[2] = {0, 0};   // in units of 2^48
+    __device__ void add(int j, int z) {
+        asm("v_mad_u64_u32 %0, vcc, %1, 1, %0" : "+v"(s[j]) : "v"(z) : "vcc");
+        asm("v_mad_u64_u32 %0, vcc, %1, %1, %0" : "+v"(q[j]) : "v"(z) : "vcc");
+    }
+    __device__ void fold() {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            h[j] += (unsigned)(q[j] >> 48);
+            q[j] &= 0xFFFFFFFFFFFFull;
+        }
+    }
+    // word k of the wave's sums; keep: this lane's count
+    __device__ unsigned long long word(int k, bool keep) const {
+        const int j = k & 1;
+        const unsigned long long v = k < 2 ? s[j] : k < 4 ? (q[j] & 0xFFFFFFFFull) : ((unsigned long long)h[j] << 16) + (q[j] >> 32);
+        return wave_total(keep ? v : 0ull);
+    }
+    static __device__ unsigned long long plus(unsigned long long a, unsigned long long b) { return a + b; }
+    static constexpr int words = 6;
+};
+template <> struct LaneSums<double> {
+    double s[2] = {0.0, 0.0}, q[2] = {0.0, 0.0};
+    __device__ void add(int j, double z) {
+        s[j] += z;
+        q[j] = __fma_rn(z, z, q[j]);
+    }
+    __device__ void fold() {}
+    __device__ unsigned long long word(int k, bool keep) const {
+        const double v = k < 2 ? s[k & 1] : q[k & 1];
+        return (unsigned long long)__double_as_longlong(wave_sum(keep ? v : 0.0));
+    }
+    static __device__ unsigned long long plus(unsigned long long a, unsigned long long b) {
+        return (unsigned long long)__double_as_longlong(__longlong_as_double((long long)a) + __longlong_as_double((long long)b));
+    }
+    static constexpr int words = 4;
+};
+
 // ---- bit-sliced logic for the binary hybrid median ----
 // Every bit of a word is one pixel.  In the wave-row form bit l of a row
 // mask is the pixel of lane l and sh(e, d) moves column x + d to bit l.
@@ -541,7 +613,7 @@ constexpr int kPass1Waves =
     !std::is_same<Acc, int>::value ? kMinWaves<Acc>
     : (MODE & kP1Maps) != 0 ? 2   // inspection only: room for the FP64 map writes
     : (MODE & kP1Packed) != 0 ? 4
-    : (MODE & (kP1Cells | kP1StoreZ)) != 0 || LOOP ? 3
+    : (MODE & kP1Cells) != 0 || LOOP ? 3
     : kMinWaves<Acc>;
 // The recomputing pass 2 (the fallback without stored strengths) keeps the
 // LoG rings, the deviation rows and the median rows at once.
@@ -554,7 +626,7 @@ template <class Acc> constexpr int kPass2Waves = std::is_same<Acc, int>::value ?
 template <class Acc, int RA, int RB, int MODE, bool LOOP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPass1Waves<Acc, MODE, LOOP>))) void pass1_kernel(Pass1Args<typename AccOps<Acc>::Taps> a) {
     extern __shared__ uint16_t lds[];
-    __shared__ double red[4][8];
+    __shared__ unsigned long long red[kTileSums][8];
     __shared__ long long redc[2][8];
     // cell sums of the current cell row, one slot per cell column a tile
     // touches (a.cell_slots of them), in the dynamic LDS after the tile: a
@@ -594,16 +666,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPass1Waves
         else load_hrow<RB>(lds + s * g.stride + g.lc, h[s + 1]);
     }
     Acc L[2][3] = {{0, 0, 0}, {0, 0, 0}};   // rows t-2, t-1, t per mask
-    double sz[2] = {0.0, 0.0}, sq[2] = {0.0, 0.0};
+    LaneSums<Acc> sums;
     int cnt[2] = {0, 0};
     const int nsteps = g.Rv + 2 * HL;
     const int t0 = g.y0 - HL;
     const uint16_t *lrow = lds + (2 * RB) * g.stride + g.lc;   // LDS row of step si
     // packed form: the words of the next step's row, read one step ahead
-    // (the last step's read lands in the spare LDS row after the tile); the
-    // cell-summing variants would spill the five registers it holds and read
-    // each row in its step
-    constexpr bool AHEAD = PK && (MODE & kP1Cells) == 0;
+    // (the last step's read lands in the spare LDS row after the tile)
+    constexpr bool AHEAD = PK;
     RowWords ahead{};
     if constexpr (AHEAD) ahead = read_hrow_pk<RB>(lrow);
 
@@ -702,9 +772,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPass1Waves
             neighbours<C>(c, g.clampL, g.clampR, lf, rt);
             // the strength where this lane holds an output pixel of the strip, else 0
             zr[j] = zc_value<Acc>(c, L[j][0], L[j][2], lf, rt, AccOps<Acc>::thr(a, j), use);
-            const double z = AccOps<Acc>::to_d(zr[j]);
-            sz[j] += z;
-            sq[j] = __fma_rn(z, z, sq[j]);
+            sums.add(j, zr[j]);
             if constexpr ((MODE & kP1Cells) != 0 && std::is_same<Acc, int>::value) {
                 // the cell's crossing count and the wave's in one compare
                 uint64_t nz;
@@ -718,7 +786,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPass1Waves
                 if (use) {
                     const long long at = (long long)r * g.W + g.xc;
                     if (a.dbgL[j]) a.dbgL[j][at] = AccOps<Acc>::to_d(c) * a.unit[j];
-                    if (a.dbgZ[j]) a.dbgZ[j][at] = z * a.unit[j];
+                    if (a.dbgZ[j]) a.dbgZ[j][at] = AccOps<Acc>::to_d(zr[j]) * a.unit[j];
                 }
             }
         }
@@ -741,9 +809,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPass1Waves
         for (; si0 + P <= nsteps; si0 += P) {
 #pragma unroll
             for (int ph = 0; ph < P; ++ph) step(si0 + ph, clamp);
+            sums.fold();
         }
         for (; si0 < nsteps; ++si0) step(si0, clamp);
     };
+    static_assert(P <= kFoldRows, "rows between folds");
     // interior tile: every row and column the strip touches lies strictly
     // inside the image, so no border test is needed
     const bool inner_x = g.x0 - HL >= 1 && g.x0 + Strip<HL, RB>::TW + HL <= g.W - 1;
@@ -776,34 +846,40 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPass1Waves
     // Deterministic per-tile reduction: fixed butterfly per wave, then the
     // waves in order.
     const int wave = threadIdx.x / kWave;
-    double v[4] = {wave_sum(sz[0]), wave_sum(sz[1]), wave_sum(sq[0]), wave_sum(sq[1])};
-    if (g.lane == 0) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) red[k][wave] = v[k];
+    for (int k = 0; k < LaneSums<Acc>::words; ++k) {
+        const unsigned long long v = sums.word(k, true);   // 0 in lanes without an output column
+        if (g.lane == 0) red[k][wave] = v;
+    }
+    if (g.lane == 0) {
         redc[0][wave] = cnt[0];
         redc[1][wave] = cnt[1];
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const int nw = blockDim.x / kWave;
-        double s[4] = {0, 0, 0, 0};
-        long long cc[2] = {0, 0};
-        for (int w = 0; w < nw; ++w) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) s[k] += red[k][w];
-            cc[0] += redc[0][w];
-            cc[1] += redc[1][w];
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) a.partials[(long long)item * 4 + k] = s[k];
-        a.counts[(long long)item * 2 + 0] = cc[0];
-        a.counts[(long long)item * 2 + 1] = cc[1];
+    if (threadIdx.x < LaneSums<Acc>::words) {
+        unsigned long long v = red[threadIdx.x][0];
+        for (int w = 1; w < (int)(blockDim.x / kWave); ++w) v = LaneSums<Acc>::plus(v, red[threadIdx.x][w]);
+        a.partials[(long long)item * kTileSums + threadIdx.x] = v;
+    } else if (threadIdx.x >= kWave && threadIdx.x < kWave + 2) {
+        const int j = threadIdx.x - kWave;
+        long long c = 0;
+        for (int w = 0; w < (int)(blockDim.x / kWave); ++w) c += redc[j][w];
+        a.counts[(long long)item * 2 + j] = c;
     }
     __syncthreads();   // LDS and the reduction buffers are reused by the next tile
     });
 }
 
 // ------------------------------------------------------------- statistics
+// The four sums as doubles from the words of exact sums: sum Z_j rounded
+// once, sum Z_j^2 = low + 2^32 high rounded at most twice.
+__device__ inline void exact_sums(const unsigned long long (&w)[kTileSums], double (&s)[4]) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        s[j] = (double)w[j];
+        s[2 + j] = __fma_rn((double)w[4 + j], 4294967296.0, (double)w[2 + j]);
+    }
+}
 // sigma_j, T_j and 72 T_j^2 of an image from the sums over its pixels:
 // s[j] = sum Z_j, s[2 + j] = sum Z_j^2, c[j] = pixels with Z_j != 0.
 __device__ inline void image_stats(const FinalizeArgs &a, long long npx, const double (&s)[4], const long long (&c)[2],

@@ -133,7 +133,7 @@ void pass1m_kernel(Pass1Args<typename AccOps<Acc>::Taps> a) {
     constexpr int NP = 1 + 2 * GB;                        // row pairs: the centre, then g above, g below
     static_assert(HL == 1, "a strip's responses start one row above it");
     __shared__ __align__(16) unsigned char sm[M::BYTES];
-    __shared__ double red[4][kTileWaves];
+    __shared__ unsigned long long red[kTileSums][kTileWaves];
     __shared__ long long redc[2][kTileWaves];
     extern __shared__ unsigned cellv[];       // cell sums (kP1Cells)
     unsigned *const cellc = cellv + a.cell_rows * a.cell_slots;
@@ -200,7 +200,7 @@ void pass1m_kernel(Pass1Args<typename AccOps<Acc>::Taps> a) {
         for (int i = threadIdx.x; i < a.cell_rows * a.cell_slots; i += blockDim.x) cellv[i] = cellc[i] = 0;
         __syncthreads();
     }
-    double sz[2] = {0.0, 0.0}, sq[2] = {0.0, 0.0};
+    LaneSums<Acc> sums;
     int cnt[2] = {0, 0};
     // the gate's cells: see pass1_kernel (the same sums and slots)
     auto cell_of = [](long long v, int cells, long long d) { return (int)floor((double)v * cells / (double)d); };
@@ -378,9 +378,7 @@ void pass1m_kernel(Pass1Args<typename AccOps<Acc>::Taps> a) {
                     int m = crossing<decltype(zero)::value>(L1[j], L2[j], v[j], lf, rt, AccOps<Acc>::thr(a, j), c);
                     asm("" : "+v"(m));   // one mask, not also its sign bit on its own
                     z[j] = masked(c, m);
-                    const double d = AccOps<Acc>::to_d(z[j]);
-                    sz[j] += d;   // every lane sums; what the lanes outside the output hold is dropped after the strip
-                    sq[j] = __fma_rn(d, d, sq[j]);
+                    sums.add(j, z[j]);   // every lane; what the lanes outside the output hold is dropped after the strip
                     fc[j] -= (unsigned)m;
                 }
                 if constexpr ((MODE & kP1StoreZ) != 0) {
@@ -504,33 +502,25 @@ void pass1m_kernel(Pass1Args<typename AccOps<Acc>::Taps> a) {
 
     // Deterministic per-tile reduction: fixed butterfly per wave, then the
     // waves in order.
-    double v[4];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        v[j] = wave_sum(outc ? sz[j] : 0.0);
-        v[2 + j] = wave_sum(outc ? sq[j] : 0.0);
-        cnt[j] = wave_sum(outc ? cnt[j] : 0);
+    for (int k = 0; k < LaneSums<Acc>::words; ++k) {
+        const unsigned long long v = sums.word(k, outc);
+        if (lane == 0) red[k][wave] = v;
     }
-    if (lane == 0) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) red[k][wave] = v[k];
+    for (int j = 0; j < 2; ++j) cnt[j] = wave_sum(outc ? cnt[j] : 0);
+    if (lane == 0) {
         redc[0][wave] = cnt[0];
         redc[1][wave] = cnt[1];
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double s[4] = {0, 0, 0, 0};
-        long long cc[2] = {0, 0};
-        for (int w = 0; w < kTileWaves; ++w) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) s[k] += red[k][w];
-            cc[0] += redc[0][w];
-            cc[1] += redc[1][w];
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) a.partials[(long long)item * 4 + k] = s[k];
-        a.counts[(long long)item * 2 + 0] = cc[0];
-        a.counts[(long long)item * 2 + 1] = cc[1];
+    if (threadIdx.x < LaneSums<Acc>::words) {
+        unsigned long long v = red[threadIdx.x][0];
+        for (int w = 1; w < kTileWaves; ++w) v = LaneSums<Acc>::plus(v, red[threadIdx.x][w]);
+        a.partials[(long long)item * kTileSums + threadIdx.x] = v;
+    } else if (threadIdx.x >= kWave && threadIdx.x < kWave + 2) {
+        const int j = threadIdx.x - kWave;
+        a.counts[(long long)item * 2 + j] = (redc[j][0] + redc[j][1]) + (redc[j][2] + redc[j][3]);
     }
     __syncthreads();   // the reduction buffers are reused by the next tile
     });

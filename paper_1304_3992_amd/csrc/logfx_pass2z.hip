@@ -184,39 +184,49 @@ template <class Acc> using LowBits = typename std::conditional<std::is_same<Acc,
 template <int MED, bool LOOP, bool S5> constexpr int kPass2zWaves = S5 ? 3 : MED < 0 || LOOP ? 4 : 5;
 
 // The finalize of a single image of few pass-1 tiles, by every workgroup for
-// itself (each thread at most kFuseTiles / 256 tiles, then a butterfly per
-// wave and the waves in order: the same bits in all of them).  A launch of
+// itself, with the finalize kernel's bits: integer sums on the integer path,
+// and on the FP64 path its order (thread t of 256 adds tiles t and t + 256,
+// threads 128 and then 64 apart are added, then a butterfly).  A launch of
 // its own for it took 4.7 us of 20 at 512^2.
+template <class Acc>
 __device__ inline void fused_finalize(const FinalizeArgs &a, double (&thr72)[2]) {
-    __shared__ double sd[4][kTileWaves];
+    constexpr int NW = LaneSums<Acc>::words;
+    __shared__ unsigned long long sd[NW][256];
     const ImageJob &J = a.L.one;
-    const int t = threadIdx.x;
-    double s[4] = {0, 0, 0, 0};
-    int c[2] = {0, 0};   // below 2^31: at most kFuseTiles tiles of 248 x 1024 pixels
+    const int t = threadIdx.x, l = t % kWave;
+    unsigned long long v[NW];
+#pragma unroll
+    for (int k = 0; k < NW; ++k) v[k] = 0;   // also the double 0
+    long long c[2] = {0, 0};
 #pragma unroll
     for (int u = 0; u < kFuseTiles / 256; ++u) {
         const int i = t + 256 * u;
         if (i < J.ntiles1) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) s[k] += a.partials[(long long)i * 4 + k];
+            for (int k = 0; k < NW; ++k) v[k] = LaneSums<Acc>::plus(v[k], a.partials[(long long)i * kTileSums + k]);
             if (blockIdx.x == 0) {
-                c[0] += (int)a.counts[(long long)i * 2];
-                c[1] += (int)a.counts[(long long)i * 2 + 1];
+                c[0] += a.counts[(long long)i * 2];
+                c[1] += a.counts[(long long)i * 2 + 1];
             }
         }
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        s[k] = wave_sum(s[k]);
-        if (t % kWave == 0) sd[k][t / kWave] = s[k];
+    for (int k = 0; k < NW; ++k) sd[k][t] = v[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NW; ++k) {
+        v[k] = LaneSums<Acc>::plus(LaneSums<Acc>::plus(sd[k][l], sd[k][l + 128]),
+                                   LaneSums<Acc>::plus(sd[k][l + 64], sd[k][l + 192]));
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v[k] = LaneSums<Acc>::plus(v[k], __shfl_xor(v[k], off));
     }
     long long z[2] = {0, 0};
     if (blockIdx.x == 0) {
-        __shared__ int sc[2][kTileWaves];
+        __shared__ long long sc[2][kTileWaves];
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            c[k] = wave_sum(c[k]);
-            if (t % kWave == 0) sc[k][t / kWave] = c[k];
+            c[k] = (long long)wave_sum((unsigned long long)c[k]);
+            if (l == 0) sc[k][t / kWave] = c[k];
         }
         __syncthreads();
         for (int w = 0; w < kTileWaves; ++w) {
@@ -224,9 +234,13 @@ __device__ inline void fused_finalize(const FinalizeArgs &a, double (&thr72)[2])
             z[1] += sc[1][w];
         }
     }
-    __syncthreads();
+    double s[4];
+    if constexpr (std::is_same<Acc, int>::value) {
+        exact_sums(v, s);
+    } else {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) s[k] = ((sd[k][0] + sd[k][1]) + sd[k][2]) + sd[k][3];
+        for (int k = 0; k < 4; ++k) s[k] = __longlong_as_double((long long)v[k]);
+    }
     DevStats st;
     image_stats(a, J.img.H * J.img.W, s, z, st);
     if (blockIdx.x == 0 && t == 0) a.stats[0] = st;
@@ -276,7 +290,7 @@ __global__ __launch_bounds__(256) void pass2z_kernel(Pass2Args<typename AccOps<A
         }
         double thr72[2];
         if (MED >= 0 && !LOOP && a.fused) {
-            fused_finalize(a.fin, thr72);
+            fused_finalize<Acc>(a.fin, thr72);
         } else {
             thr72[0] = a.stats[image].thr72[0];
             thr72[1] = a.stats[image].thr72[1];

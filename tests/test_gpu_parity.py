@@ -888,7 +888,7 @@ def test_matrix_form_under_capture_and_many_masks():
 def test_default_strips_give_what_64_row_strips_give(h, w, kw):
     """A context whose strip heights were not set takes lower strips on small
     images; the map and the counts are those of 64-row strips, singly and in
-    a batch (sigma: the same sums in another order, 1e-12)."""
+    a batch, and so is sigma, bit for bit: the integer path's sums are exact."""
     import torch
     img = scenes.panchromatic(h, w, 77, n_rect=max(3, h * w // 6000), noise_sigma=4.0, sp_density=0.02, bits=8)
     dev, params = to_device(img), logfx.Params(*masks()[1], **kw)
@@ -902,30 +902,45 @@ def test_default_strips_give_what_64_row_strips_give(h, w, kw):
         d = tall.extract_batch([dev, dev[: h // 2]], params)
         torch.cuda.synchronize()
         assert torch.equal(a, b) and torch.equal(c[0], d[0]) and torch.equal(c[1], d[1]) and torch.equal(a, c[0])
-    for k in ("zc_count", "extracted", "output"):
-        assert ra[k] == rb[k]
-    assert np.allclose(ra["sigma_g"], rb["sigma_g"], rtol=1e-12, atol=0)
+    assert ra == rb
 
 
 @pytest.mark.parametrize("h", [255, 256, 257])
 def test_finalize_in_pass2_at_its_limit(ctx, h):
     """Strips of one row, two tiles wide: up to 512 pass-1 tiles pass 2 forms
     the thresholds itself, past them (and when it recomputes the strengths)
-    the finalize kernel does.  Same map and counts, sigma within 1e-12."""
+    the finalize kernel does.  Same map and the same report, bit for bit, on
+    both paths, and the batch's (whose finalize is the kernel) too."""
     img = np.random.default_rng(h).integers(0, 2048, (h, 490)).astype(np.uint16)
     dev, params = to_device(img), logfx.Params(*masks()[1])
-    got = []
     try:
         ctx.set_option(logfx.OPT_ROWS1, 1)
-        for store in (1, 0):
-            ctx.set_option(logfx.OPT_STORE_Z, store)
-            out, rep = ctx.extract(dev, params, bits=11, report=True)
-            got.append((out.cpu().numpy(), rep))
+        for bits in (11, 16):
+            got = []
+            for store in (1, 0):
+                ctx.set_option(logfx.OPT_STORE_Z, store)
+                got.append(ctx.extract(dev, params, bits=bits, report=True))
+            ctx.set_option(logfx.OPT_STORE_Z, 1)
+            outs, reps = ctx.extract_batch([dev, dev[:100]], params, bits=bits, report=True)
+            assert np.array_equal(got[0][0].cpu().numpy(), got[1][0].cpu().numpy())
+            assert np.array_equal(got[0][0].cpu().numpy(), outs[0].cpu().numpy())
+            assert got[0][1] == got[1][1] == reps[0]
     finally:
         ctx.set_option(logfx.OPT_STORE_Z, 1)
         ctx.set_option(logfx.OPT_ROWS1, 64)
-    assert np.array_equal(got[0][0], got[1][0])
-    for k in ("zc_count", "extracted", "output"):
-        assert got[0][1][k] == got[1][1][k]
-    for k in ("sigma_g", "thresh"):
-        assert np.allclose(got[0][1][k], got[1][1][k], rtol=1e-12, atol=0)
+
+
+def test_exact_sums_past_64_bits(ctx):
+    """Vertical 12-bit stripes whose crossings are strong on every row: the
+    squares of a lane's strip overflow 64 bits, and sigma still is the
+    oracle's (1e-13: its own sums round)."""
+    orc_t, lib_t = masks()
+    row = np.where(np.arange(330) % 5 < 2, 4095, 0)
+    img = np.tile(row, (200, 1)).astype(np.uint16)
+    o = run_oracle(img, orc_t)
+    z = (o["Z2"] / logfx.make_log_mask(9, 1.4, 16)[1])[:64]
+    assert (z ** 2).sum(0).max() > 2.0 ** 64
+    ctx.set_option(logfx.OPT_ROWS1, 64)
+    out, rep = ctx.extract(to_device(img), logfx.Params(*lib_t), bits=12, report=True)
+    assert np.allclose(rep["sigma_g"], o["stats"][:2], rtol=1e-13, atol=0)
+    assert np.array_equal(out.cpu().numpy(), o["F"])
