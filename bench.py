@@ -84,7 +84,7 @@ KERNEL_BYTES_PER_PX = {"pass1_kernel": 2 + 8, "pass2z_kernel": 8 + 1}
 # The sources the pipeline kernels (pass 1, finalize, pass 2) are compiled
 # from; the gate network's files do not take part.
 PIPELINE_SOURCES = ("logfx_bits.h", "logfx_dispatch.hip", "logfx_internal.h", "logfx_kernels.h",
-                    "logfx_kernels_inst.hip", "logfx_pass2z.hip")
+                    "logfx_kernels_inst.hip", "logfx_pass1m.h", "logfx_pass2z.hip")
 
 
 def kernel_source_hash() -> str:

@@ -456,8 +456,9 @@ bool fill_packed_taps(const Plan &pl, OrbitTapsI &t) {
         auto tap = [&](int d, int c) -> double { return d > r || c > r ? 0.0 : mi.k[(r + d) * s + (r + c)]; };
         for (int d = 0; d <= kMaxRadius; ++d)
             for (int m = 0; m < kPkPerRow; ++m) {
-                const double lo = m == 0 ? (d == 0 ? 0.0 : tap(d, 0)) : tap(d, 2 * m - 1);
-                const double hi = m == 0 ? 0.0 : tap(d, 2 * m);
+                const bool none = m == 0 && d % 2 == 0;
+                const double lo = none ? 0.0 : m == 0 ? tap(d, 0) : tap(d, 2 * m - 1);
+                const double hi = none ? 0.0 : m == 0 ? tap(d + 1, 0) : tap(d, 2 * m);
                 if (!(lo >= -32768.0 && lo <= 32767.0 && hi >= -32768.0 && hi <= 32767.0)) return false;
                 t.pk[slot][d * kPkPerRow + m] =
                     (unsigned)(uint16_t)(int16_t)lo | (unsigned)(uint16_t)(int16_t)hi << 16;
@@ -749,8 +750,8 @@ void cell_layout(int n, const logfx_image *imgs, const Plan &pl, int rows, long 
 // long again (`alone`) as with others to fill its waits, so a call takes
 // about (rows + halo) max(alone, tiles per CU, rounded up) of them: low strips
 // where tall ones leave CUs idle, tall ones where the halo rows add up.
-// Pass 1, measured: 512^2 34 us with 64 rows, 13 with 8; 2000^2 45 and 31
-// with 24; 4000^2 82 and 77 with 48 (114 with 8); pass 2: 512^2 14.7 and 8.4
+// Pass 1, measured: 512^2 34 us with 64 rows, 12 with 7; 2000^2 45 and 29
+// with 25; 4000^2 68 with 61 and 63 with 34; pass 2: 512^2 14.7 and 8.4
 // with 8, 2000^2 19.4 and 14.0 with 24, 6000^2 57 with 64 and 83 with 8.
 // From 2^25 pixels on, the tallest is within 4 % of the best.
 int strip_rows(int n, const logfx_image *imgs, long long tw, int most, int step, int halo, double alone) {
@@ -804,8 +805,14 @@ int prepare(logfx_ctx *ctx, int n, const logfx_image *imgs, const logfx_params *
     // image's statistics are the same bits in a batch and alone.  Its matrix
     // form works through blocks of 8 rows, the strip's and one above and below
     // it: 62 rows.)
+    // Integer path: the strip and the two halo rows are whole rounds of the
+    // row ring, since rows left over take the rolled loop (8192^2: 213 us with
+    // 64 rows, 201 with 61), and five workgroups' LDS fit a CU (196 with 43).
+    // With the gate's cells, whose sums leave the tile at its end, the tallest
+    // that four workgroups' LDS allows (32 of 2048^2: 469 with 43, 451 with 61).
+    const int ring = 2 * c.pl.rb + 1, most1 = ((features ? 62 : 44) + 2) / ring * ring - 2;
     if (!ctx->tiles.set1)
-        c.rows1 = c.pl.i32 ? strip_rows(n, imgs, tile_out_width(kHalo1), 64, 4, 6, 1.7) : c.table ? 62 : c.rows1;
+        c.rows1 = c.pl.i32 ? strip_rows(n, imgs, tile_out_width(kHalo1), most1, ring, 6, 1.7) : c.table ? 62 : c.rows1;
     if (features) {
         // pass 1 keeps a slot per (cell row, cell column) a tile spans in
         // LDS beside the tile: lower the strip height where they would not

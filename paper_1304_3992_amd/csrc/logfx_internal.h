@@ -43,12 +43,11 @@ __host__ __device__ constexpr int orbit_index(int i, int j) { return i * (i + 1)
 // one D4 orbit, that of (max(d, c), min(d, c)), so
 //   L = sum over d, c in 0..R of k'(d, c) v(d, c),  k'(d, c) = k_orbit.
 // Per row offset d the entries are packed in 16-bit halves, kPkPerRow
-// words: (v(d, 0), unused), (v(d, 1), v(d, 2)), (v(d, 3), v(d, 4)); the
-// taps k' are packed the same way (0 in unused halves and past the mask's
-// radius), word d * kPkPerRow + m, and multiplied two at a time
-// (v_dot2_i32_i16).  The centre v(0, 0) (one pixel) takes the orbit tap k[0]
+// words: for odd d (v(d, 0), v(d + 1, 0)); (v(d, 1), v(d, 2)), (v(d, 3),
+// v(d, 4)); the taps k' are packed the same way (0 past the mask's radius),
+// word d * kPkPerRow + m, and multiplied two at a time (v_dot2_i32_i16).  The centre v(0, 0) (one pixel) takes the orbit tap k[0]
 // of the 32-bit form in a 24-bit multiply, since that tap alone may exceed
-// 16 bits; word 0 is unused.  Valid when every v fits int16 (pixels below
+// 16 bits; word 0 of even d is unused.  Valid when every v fits int16 (pixels below
 // 2^13) and every other tap does too; the host checks both.
 constexpr int kPkPerRow = 3;
 constexpr int kPkTaps = (kMaxRadius + 1) * kPkPerRow;

@@ -139,16 +139,16 @@ __device__ inline pk2 add_swapped(unsigned x, unsigned y) {
     return as_pk2(r);
 }
 
-// k * (low 16 bits of w), the 16 bits taken by the operand selection
-__device__ inline int mul_lo16(int k, pk2 w) {
+// k * (high 16 bits of w), the 16 bits taken by the operand selection
+__device__ inline int mul_hi16(int k, pk2 w) {
     int r;
-    asm("v_mul_i32_i24_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0"
+    asm("v_mul_i32_i24_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
         : "=v"(r) : "s"(k), "v"(as_u32(w)));
     return r;
 }
 
-// One row of pair sums at the lane's column, packed: g[0] = (I(x), I(x + 1))
-// (the high half has zero taps), g[1] = (h_1, h_2), g[2] = (h_3, h_4),
+// One row of pair sums at the lane's column, packed: g[0] = the centre column
+// of the row above and of this one, g[1] = (h_1, h_2), g[2] = (h_3, h_4),
 // h_c = I(x - c) + I(x + c).  One unaligned 16-byte LDS read gives
 // I(x - 4) .. I(x + 3) and one 2-byte read I(x + 4); the pairs (I1, I2)
 // and (I3, I4) come from funnel shifts.  (Two 16-byte reads, at x - 4 and
@@ -171,33 +171,33 @@ __device__ inline RowWords read_hrow_pk(const uint16_t *p) {
     return w;
 }
 template <int RB>
-__device__ inline void unpack_hrow_pk(const RowWords &w, pk2 (&g)[pk_words(RB)]) {
-    g[0] = as_pk2(w.a.z);
+__device__ inline void unpack_hrow_pk(const RowWords &w, const pk2 (&above)[pk_words(RB)], pk2 (&g)[pk_words(RB)]) {
+    g[0] = as_pk2(__builtin_amdgcn_alignbit(w.a.z, as_u32(above[0]), 16));
     g[1] = add_swapped(__builtin_amdgcn_alignbit(w.a.w, w.a.z, 16), w.a.y);   // (I1, I2) + (I-1, I-2)
     if constexpr (pk_words(RB) > 2)
         g[2] = add_swapped(__builtin_amdgcn_alignbit(w.i4, w.a.w, 16), w.a.x);   // (I3, I4) + (I-3, I-4)
 }
-template <int RB>
-__device__ inline void load_hrow_pk(const uint16_t *p, pk2 (&g)[pk_words(RB)]) {
-    unpack_hrow_pk<RB>(read_hrow_pk<RB>(p), g);
-}
-
 // Both LoG responses of the centre row of the packed ring (ring row RB):
-// the centre pixel times its 32-bit tap, then v(d, .) of the row pair at
-// +-d by packed adds and two taps per v_dot2_i32_i16.
+// the centre pixel times its 32-bit tap, then two v(d, .) per packed add and
+// two taps per v_dot2_i32_i16.  The centre columns of the rows at +-d and
+// +-(d + 1) come from two words of neighbouring rows, so no half is left
+// empty but in the last pair of an odd radius.
 template <int RA, int RB>
 __device__ inline void log_pair_pk(const pk2 (&g)[2 * RB + 1][pk_words(RB)], const OrbitTapsI &t, int (&out)[2]) {
-    int l0 = mul_lo16(t.k[0][0], g[RB][0]);
-    int l1 = mul_lo16(t.k[1][0], g[RB][0]);
+    int l0 = mul_hi16(t.k[0][0], g[RB][0]);
+    int l1 = mul_hi16(t.k[1][0], g[RB][0]);
+    auto add = [&](const pk2 v, int d, int m) __attribute__((always_inline)) {
+        l1 = __builtin_amdgcn_sdot2(v, as_pk2(t.pk[1][d * kPkPerRow + m]), l1, false);
+        if (d <= RA && m < pk_words(RA))
+            l0 = __builtin_amdgcn_sdot2(v, as_pk2(t.pk[0][d * kPkPerRow + m]), l0, false);
+    };
 #pragma unroll
     for (int d = 0; d <= RB; ++d) {
 #pragma unroll
-        for (int m = d == 0 ? 1 : 0; m < pk_words(RB); ++m) {
-            const pk2 v = d == 0 ? g[RB][m] : g[RB - d][m] + g[RB + d][m];
-            l1 = __builtin_amdgcn_sdot2(v, as_pk2(t.pk[1][d * kPkPerRow + m]), l1, false);
-            if (d <= RA && m < pk_words(RA))
-                l0 = __builtin_amdgcn_sdot2(v, as_pk2(t.pk[0][d * kPkPerRow + m]), l0, false);
-        }
+        for (int m = 1; m < pk_words(RB); ++m) add(d == 0 ? g[RB][m] : g[RB - d][m] + g[RB + d][m], d, m);
+        if (d % 2 == 1)   // (v(d, 0), v(d + 1, 0)); at d = RB the high half has zero taps
+            add(d < RB ? add_swapped(as_u32(g[RB + d + 1][0]), as_u32(g[RB - d][0]))
+                       : add_swapped(as_u32(g[RB - d + 1][0]), as_u32(g[RB + d][0])), d, 0);
     }
     out[0] = l0;
     out[1] = l1;
@@ -221,34 +221,30 @@ __device__ inline bool opposite(double p, double q) { return p * q < 0.0; }
 // lane of the wave holds a zero.  Written without short-circuit logic so
 // that it compiles to straight-line code.
 // keep: an extra condition folded into the selection (0 where false).
+// mask: the wave's lanes with a crossing (their strengths are not zero).
 template <class Acc, class Thr>
-__device__ inline Acc zc_value(Acc a, Acc up, Acc dn, Acc lf, Acc rt, Thr thr, bool keep = true) {
-    // hi / lo: largest / smallest of the five values.  For a < 0, a + hi >= 0
-    // holds iff some neighbour reaches -a (a itself cannot), i.e. iff
-    // a + max(neighbours) >= 0; for a > 0 likewise with lo.
+__device__ inline Acc zc_value(Acc a, Acc up, Acc dn, Acc lf, Acc rt, Thr thr, bool keep, uint64_t &mask) {
+    // hi / lo: largest / smallest of the five values.  For a < 0, a + lo < 0,
+    // and a + hi >= 0 iff some neighbour reaches -a (a itself cannot); for
+    // a > 0, a + hi > 0, and a + lo < 0 likewise.  So for either sign a is a
+    // crossing iff a + lo < 0 <= a + hi, i.e. 0 <= a + hi < hi - lo (one
+    // unsigned compare of integers).  For a = 0 the branch below decides.
     const Acc hi = max(max(max(max(up, dn), lf), rt), a);
     const Acc lo = min(min(min(min(up, dn), lf), rt), a);
-    bool is;
-    if constexpr (std::is_same<Acc, int>::value) {
-        // b = a + hi for a <= 0, a + lo for a > 0 (exact: |L| < 2^30); a
-        // crossing iff b and a differ in sign bit.  For a = 0, b = hi >= 0.
-        const int b = a + (a <= 0 ? hi : lo);
-        is = (b ^ a) < 0;
-    } else {
-        is = ((a < 0) & (a + hi >= 0)) | ((a > 0) & (a + lo < 0));
-    }
-    const Acc c = hi - lo;   // exact: |L| < 2^30 (int) or 2^52 (FP64)
-    const bool strong = (c > thr) & keep;
-    Acc r = (is & strong) ? c : Acc(0);
-    if (__ballot(a == 0)) {
-        const bool z = (a == 0) & (opposite(lf, rt) | opposite(up, dn));
-        r = (z & strong) ? c : r;
-    }
-    return r;
+    const Acc c = hi - lo, u = a + hi;   // exact: |L| < 2^30 (int) or 2^52 (FP64)
+    // lane masks from the compares on: combined on the scalar unit, and the
+    // count of crossings needs no compare of its own
+    const uint64_t strong = __ballot(c > thr) & __ballot(keep);
+    if constexpr (std::is_same<Acc, int>::value) mask = __ballot((unsigned)u < (unsigned)c) & strong;
+    else mask = __ballot(u >= 0) & __ballot(u < c) & strong;
+    const uint64_t zero = __ballot(a == 0);
+    if (zero) mask = (mask & ~zero) | (zero & strong & __ballot(opposite(lf, rt) | opposite(up, dn)));
+    return __builtin_amdgcn_inverse_ballot_w64(mask) ? c : Acc(0);
 }
 template <class Acc, class Thr>
 __device__ inline double zc_strength(Acc a, Acc up, Acc dn, Acc lf, Acc rt, Thr thr) {
-    return AccOps<Acc>::to_d(zc_value<Acc>(a, up, dn, lf, rt, thr));
+    uint64_t mask;
+    return AccOps<Acc>::to_d(zc_value<Acc>(a, up, dn, lf, rt, thr, true, mask));
 }
 
 __device__ inline double wave_sum(double v) {
@@ -268,23 +264,25 @@ __device__ inline unsigned long long wave_sum(unsigned long long v) {
     return v;
 }
 
-// Sum over the wave by DPP (row scans, then row totals passed on), the same in
-// every lane: three vector instructions a step instead of two LDS permutes.
-template <int CTRL, int ROWS>
+// Sum over the wave, as a scalar: DPP adds within the rows of 16 lanes (three
+// vector instructions a step instead of two LDS permutes), then the four row
+// totals on the scalar unit.
+template <int CTRL>
 __device__ inline unsigned long long dpp_add(unsigned long long v) {
-    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)v, CTRL, ROWS, 0xf, false);
-    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(v >> 32), CTRL, ROWS, 0xf, false);
+    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)v, CTRL, 0xf, 0xf, true);
+    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(v >> 32), CTRL, 0xf, 0xf, true);
     return v + ((unsigned long long)hi << 32 | lo);
 }
 __device__ inline unsigned long long wave_total(unsigned long long v) {
-    v = dpp_add<0x111, 0xf>(v);   // row_shr:1, 2, 4, 8: lane 15 of each row holds its sum
-    v = dpp_add<0x112, 0xf>(v);
-    v = dpp_add<0x114, 0xf>(v);
-    v = dpp_add<0x118, 0xf>(v);
-    v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
-    v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3: lane 63 holds the total
-    return (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), 63) << 32 |
-           (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, 63);
+    v = dpp_add<0x111>(v);   // row_shr:1, 2, 4, 8: lane 15 of each row holds its sum
+    v = dpp_add<0x112>(v);
+    v = dpp_add<0x114>(v);
+    v = dpp_add<0x118>(v);
+    auto row = [&](const int lane) {
+        return (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), lane) << 32 |
+               (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, lane);
+    };
+    return (row(15) + row(31)) + (row(47) + row(63));
 }
 
 // A lane's sums of strengths and of their squares.  Integer path: exact, each
@@ -391,7 +389,8 @@ __device__ inline uint64_t clamp_bits(uint64_t e, int lo, int hi) {
 // Eight pixels from element `at` of an image (u16 when `u16`, else u8
 // widened to u16) at any pixel alignment: one 16- or 8-byte global load,
 // which gfx950 serves under the HSA unaligned access mode.
-__device__ inline uint4 load8(const void *data, long long at, bool u16) {
+template <class P>
+__device__ inline uint4 load8(P data, long long at, bool u16) {
     typedef __attribute__((address_space(1))) const uint16_t GU16;
     typedef __attribute__((address_space(1))) const uint8_t GU8;
     typedef unsigned V4 __attribute__((ext_vector_type(4), aligned(2)));
@@ -406,6 +405,9 @@ __device__ inline uint4 load8(const void *data, long long at, bool u16) {
     return make_uint4(__builtin_amdgcn_perm(0u, q.x, 0x0c010c00u), __builtin_amdgcn_perm(0u, q.x, 0x0c030c02u),
                       __builtin_amdgcn_perm(0u, q.y, 0x0c010c00u), __builtin_amdgcn_perm(0u, q.y, 0x0c030c02u));
 }
+
+template <bool B> using bool_c = std::integral_constant<bool, B>;
+template <int V> using int_c = std::integral_constant<int, V>;
 
 // ------------------------------------------------------------- strips
 // Geometry shared by both passes.  A workgroup owns a tile of kTileWaves strips
@@ -446,6 +448,49 @@ struct Strip {
         outc = oc != 0;
     }
 
+    // fill for a tile whose staged rows and columns all lie inside the image
+    // (SZ bytes per pixel, offsets within the tile below 2^31): no clamping,
+    // and a thread's chunks lie a fixed step apart in its row and column, so
+    // each takes two compares and adds to find instead of a division, four
+    // clamps and a 64-bit product.  (With those the fill was a fifth of pass
+    // 1's vector instructions.)
+    template <int SZ>
+    __device__ __attribute__((always_inline)) void fill_inner(uint16_t *lds, const ImageDesc &img, const int nch) const {
+        constexpr int CPR = stride / 8, NT = kTileWaves * kWave, DR = NT / CPR, DC = NT % CPR;
+        typedef __attribute__((address_space(1))) const char G;
+        const unsigned pitch = SZ * (unsigned)img.pitch;
+        G *base = (G *)img.data + SZ * ((long long)(y0 - HL - RB) * img.pitch + (x0 - HL - RB - OFF));
+        const int t = (int)threadIdx.x;
+        int ch = t % CPR;
+        unsigned off = (unsigned)(t / CPR) * pitch + 8 * SZ * ch;
+        const unsigned step = DR * pitch + 8 * SZ * DC, wrap = pitch - 8 * SZ * CPR;
+        uint4 *to = reinterpret_cast<uint4 *>(lds) + t;
+        // the thread's next N chunks (ALL: every thread has them), their
+        // loads in flight together
+        int b = 0;
+        auto part = [&](auto n, auto all) __attribute__((always_inline)) {
+            constexpr int N = decltype(n)::value;
+            uint4 v[N];
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                if (decltype(all)::value || b + k * NT + t < nch) v[k] = load8(base + off, 0, SZ == 2);
+                ch += DC;
+                const bool over = ch >= CPR;
+                off += step + (over ? wrap : 0u);
+                ch -= over ? CPR : 0;
+            }
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+                if (decltype(all)::value || b + k * NT + t < nch) to[b + k * NT] = v[k];
+            b += N * NT;
+        };
+        while (b + 8 * NT <= nch) part(int_c<8>{}, bool_c<true>{});
+        const int left = nch - b;
+        if (left > 4 * NT) part(int_c<8>{}, bool_c<false>{});
+        else if (left > 2 * NT) part(int_c<4>{}, bool_c<false>{});
+        else if (left > 0) part(int_c<2>{}, bool_c<false>{});
+    }
+
     // Stage the input rows y0-HL-RB .. (RH rows) and columns from the
     // 8-aligned origin x0-HL-RB-OFF (stride columns) in LDS as u16, with
     // clamp-to-edge coordinates, in chunks of 8 pixels.  Chunks inside the
@@ -460,9 +505,14 @@ struct Strip {
         constexpr int CPR = stride / 8;
         const int ry0 = y0 - HL - RB, rx0 = x0 - HL - RB - OFF;
         const int nch = RH * CPR;
-        const int nt = blockDim.x;
+        constexpr int nt = kTileWaves * kWave;
         const long long pitch = img.pitch;
         const bool u16 = img.dtype == 1;
+        if (rx0 >= 0 && rx0 + stride <= W && ry0 >= 0 && ry0 + RH <= H && pitch < (1 << 20)) {
+            if (u16) fill_inner<2>(lds, img, nch);
+            else fill_inner<1>(lds, img, nch);
+            return;
+        }
         // chunks nl .. nr-1 of a row lie inside the image columns
         const int nl = rx0 >= 0 ? 0 : min((-rx0 + 7) / 8, CPR);
         const int nr = max(nl, min(CPR, (W - rx0) / 8));
@@ -522,9 +572,6 @@ __device__ inline void ring_push(T (&ring)[N], T v, int row, int H) {
     }
 }
 
-template <bool B> using bool_c = std::integral_constant<bool, B>;
-template <int V> using int_c = std::integral_constant<int, V>;
-
 // ------------------------------------------------------------- work list
 // Tiles of a launch are split into 8 contiguous shares, one per XCD
 // (workgroups are dispatched round-robin over the XCDs), so neighbouring
@@ -547,15 +594,11 @@ __device__ inline void for_each_tile(int total, F &&f) {
     }
 }
 
-// acc + [z != 0] per lane, and the wave's lane mask of z != 0: one compare
-// whose mask is the carry-in of one add.  (Written as C, the compiler keeps
-// the compare's mask across the strength store's branch and rebuilds it as
-// 0 / 1 in a register before adding.)
-__device__ inline unsigned count_nonzero(unsigned acc, int z, uint64_t &mask) {
+// acc + the lane's bit of mask: the mask is the carry-in of one add.
+__device__ inline unsigned add_mask(unsigned acc, uint64_t mask) {
     unsigned r;
     uint64_t co;
-    asm("v_cmp_ne_u32_e64 %1, 0, %3\n\tv_addc_co_u32 %0, %2, 0, %4, %1"
-        : "=v"(r), "=&s"(mask), "=s"(co) : "v"(z), "v"(acc));
+    asm("v_addc_co_u32 %0, %1, 0, %2, %3" : "=v"(r), "=s"(co) : "v"(acc), "s"(mask));
     return r;
 }
 
@@ -564,13 +607,25 @@ __device__ inline ImageJob job_of(const Launch &L, int image) {
 }
 
 
-// Strengths into and out of the Z map (ZMap in logfx_internal.h).  The codes
-// and low halves are packed by byte permutes: two of them and two shifts per
-// pixel on the integer path.
+// p[x] = v for a row p held in scalar registers: the store takes the row as
+// its scalar base and the lane's column as a 32-bit byte offset (W < 2^30),
+// with no 64-bit address arithmetic on the vector unit.
+template <class T>
+__device__ inline void put(void *plane, long long row, unsigned x, T v) {
+    typedef __attribute__((address_space(1))) char G;
+    G *p = (G *)(static_cast<T *>(plane) + row);
+    unsigned off = (unsigned)sizeof(T) * x;
+    asm("" : "+s"(p), "+v"(off));   // else the sum is taken apart before the store's form is chosen
+    *(__attribute__((address_space(1))) T *)(p + off) = v;
+}
+
+// Strengths into and out of the Z map (ZMap in logfx_internal.h), row
+// wave-uniform.  The codes and low halves are packed by byte permutes: two of
+// them and two shifts per pixel on the integer path.
 __device__ inline void store_strengths(const ZMap &m, long long row, unsigned x, const int (&z)[2]) {
     const unsigned c0 = (unsigned)z[0] >> m.shift[0], c1 = (unsigned)z[1] << (16 - m.shift[1]);
-    (static_cast<unsigned *>(m.hi) + row)[x] = __builtin_amdgcn_perm(c1, c0, 0x07060100u);
-    (static_cast<unsigned *>(m.lo) + row)[x] = __builtin_amdgcn_perm((unsigned)z[1], (unsigned)z[0], 0x05040100u);
+    put(m.hi, row, x, __builtin_amdgcn_perm(c1, c0, 0x07060100u));
+    put(m.lo, row, x, __builtin_amdgcn_perm((unsigned)z[1], (unsigned)z[0], 0x05040100u));
 }
 __device__ inline void store_strengths(const ZMap &m, long long row, unsigned x, const double (&z)[2]) {
     if (!m.split) {
@@ -582,8 +637,9 @@ __device__ inline void store_strengths(const ZMap &m, long long row, unsigned x,
     const unsigned l0 = __double2loint(i0), l1 = __double2loint(i1);
     const unsigned c0 = __builtin_amdgcn_alignbit(__double2hiint(i0), l0, m.shift[0]);
     const unsigned c1 = __builtin_amdgcn_alignbit(__double2hiint(i1), l1, m.shift[1]);
-    (static_cast<unsigned *>(m.hi) + row)[x] = __builtin_amdgcn_perm(c1, c0, 0x05040100u);
-    (static_cast<uint2 *>(m.lo) + row)[x] = make_uint2(l0, l1);
+    typedef unsigned V2 __attribute__((ext_vector_type(2)));
+    put(m.hi, row, x, __builtin_amdgcn_perm(c1, c0, 0x05040100u));
+    put(m.lo, row, x, V2{l0, l1});
 }
 // The exact strengths from both planes.
 __device__ inline void restore_strengths(const ZMap &m, unsigned hi, unsigned lo, double (&z)[2]) {
@@ -597,6 +653,12 @@ __device__ inline void restore_strengths(const ZMap &m, unsigned hi, uint2 lo, d
 }
 
 // ------------------------------------------------------------- pass 1
+// Bound by the vector unit: on the packed form a row of a wave takes 64
+// vector instructions (33 for both LoGs, 14 per mask for the crossings and
+// their sums, 4 for the store), with the staging and the ends of the strips
+// 77 by the counters; its LDS reads, at any pixel alignment, keep the LDS
+// busy for most of the same time.  8192^2: 233 us with 77 + 20 instructions
+// and strips of 64 rows, 196 with these and 43.
 // Occupancy: the integer path is held to 128 VGPRs (4 waves per SIMD, the
 // LDS limit); the FP64 path keeps its registers.  Variants that need more
 // run at fewer waves rather than spill.  No kernel here may spill vector
@@ -660,9 +722,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPass1Waves
     static_assert(!PK || std::is_same<Acc, int>::value, "the packed form is integer only");
     int h[PK ? 1 : P][RB + 1];
     pk2 hp[PK ? P : 1][pk_words(RB)];
+    hp[0][0] = pk2{0, 0};
 #pragma unroll
     for (int s = 0; s < P - 1; ++s) {
-        if constexpr (PK) load_hrow_pk<RB>(lds + s * g.stride + g.lc, hp[s + 1]);
+        if constexpr (PK) unpack_hrow_pk<RB>(read_hrow_pk<RB>(lds + s * g.stride + g.lc), hp[s], hp[s + 1]);
         else load_hrow<RB>(lds + s * g.stride + g.lc, h[s + 1]);
     }
     Acc L[2][3] = {{0, 0, 0}, {0, 0, 0}};   // rows t-2, t-1, t per mask
@@ -673,9 +736,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPass1Waves
     const uint16_t *lrow = lds + (2 * RB) * g.stride + g.lc;   // LDS row of step si
     // packed form: the words of the next step's row, read one step ahead
     // (the last step's read lands in the spare LDS row after the tile)
-    constexpr bool AHEAD = PK;
     RowWords ahead{};
-    if constexpr (AHEAD) ahead = read_hrow_pk<RB>(lrow);
+    if constexpr (PK) ahead = read_hrow_pk<RB>(lrow);
 
     // Feature mode: the image is cut into CY x CX cells, CY = 2^cells_ly,
     // CX = 2^cells_lx (row r and column x belong to cell (r * CY / H,
@@ -742,12 +804,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPass1Waves
             for (int s = 0; s < P - 1; ++s)
 #pragma unroll
                 for (int m = 0; m < pk_words(RB); ++m) hp[s][m] = hp[s + 1][m];
-            if constexpr (AHEAD) {
-                unpack_hrow_pk<RB>(ahead, hp[P - 1]);
-                ahead = read_hrow_pk<RB>(lrow + g.stride);
-            } else {
-                load_hrow_pk<RB>(lrow, hp[P - 1]);
-            }
+            unpack_hrow_pk<RB>(ahead, hp[P - 2], hp[P - 1]);
+            ahead = read_hrow_pk<RB>(lrow + g.stride);
             log_pair_pk<RA, RB>(hp, a.taps, Ln);
         } else {
 #pragma unroll
@@ -771,17 +829,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPass1Waves
             Acc lf, rt;
             neighbours<C>(c, g.clampL, g.clampR, lf, rt);
             // the strength where this lane holds an output pixel of the strip, else 0
-            zr[j] = zc_value<Acc>(c, L[j][0], L[j][2], lf, rt, AccOps<Acc>::thr(a, j), use);
+            uint64_t mask;
+            zr[j] = zc_value<Acc>(c, L[j][0], L[j][2], lf, rt, AccOps<Acc>::thr(a, j), use, mask);
             sums.add(j, zr[j]);
-            if constexpr ((MODE & kP1Cells) != 0 && std::is_same<Acc, int>::value) {
-                // the cell's crossing count and the wave's in one compare
-                uint64_t nz;
-                fc[j] = count_nonzero(fc[j], zr[j], nz);
-                cnt[j] += __popcll(nz);   // wave-uniform
-            } else {
-                cnt[j] += __popcll(__ballot(zr[j] != Acc(0)));   // wave-uniform
-                if constexpr ((MODE & kP1Cells) != 0) fc[j] += (unsigned)(zr[j] != Acc(0));
-            }
+            cnt[j] += __popcll(mask);   // wave-uniform
+            if constexpr ((MODE & kP1Cells) != 0) fc[j] = add_mask(fc[j], mask);
             if constexpr ((MODE & kP1Maps) != 0) {
                 if (use) {
                     const long long at = (long long)r * g.W + g.xc;
@@ -798,7 +850,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPass1Waves
             // every lane accumulates; the halo rows before the strip are
             // dropped below and the non-output lanes at the flush
             // pixel (r, xc): the centre of ring row RB - 1
-            if constexpr (PK) fv += as_u32(hp[RB - 1][0]) & 0xFFFFu;
+            if constexpr (PK) fv += as_u32(hp[RB][0]) & 0xFFFFu;
             else fv += (unsigned)h[RB - 1][0];
             if (si < 2) fv = fc[0] = fc[1] = 0;
             else if (r == fend) flush(r);

@@ -944,3 +944,32 @@ def test_exact_sums_past_64_bits(ctx):
     out, rep = ctx.extract(to_device(img), logfx.Params(*lib_t), bits=12, report=True)
     assert np.allclose(rep["sigma_g"], o["stats"][:2], rtol=1e-13, atol=0)
     assert np.array_equal(out.cpu().numpy(), o["F"])
+
+
+@pytest.mark.parametrize("dtype", [np.uint8, np.uint16])
+@pytest.mark.parametrize("w", [503, 504, 505, 760])
+def test_staging_of_inner_tiles(ctx, w, dtype):
+    """Tiles whose staged rows and columns lie inside the image (the second
+    column of tiles from 504 columns on) are staged without clamping, in
+    batches of 2, 4 and 8 chunks a thread: strip heights that end in each,
+    an odd pitch and start, one and two bytes a pixel, against the oracle."""
+    import torch
+    bits = 8 if dtype == np.uint8 else 11
+    img = np.random.default_rng(w).integers(0, 1 << bits, (230, w)).astype(dtype)
+    orc_t, lib_t = masks()
+    wide = torch.zeros((231, w + 5), dtype=torch.uint8 if bits == 8 else torch.uint16, device="cuda:0")
+    dev = wide[1:, 3:w + 3]
+    dev.copy_(to_device(img))
+    params, want = logfx.Params(*lib_t), run_oracle(img, orc_t)
+    try:
+        for r in (1, 20, 43, 52, 61):
+            ctx.set_option(logfx.OPT_ROWS1, r)
+            for store in (1, 0):
+                ctx.set_option(logfx.OPT_STORE_Z, store)
+                ctx.set_option(logfx.OPT_ROWS2, r)
+                out = ctx.extract(dev, params, bits=bits).cpu().numpy()
+                compare(out, want, smooth=True, median_size=5)
+    finally:
+        ctx.set_option(logfx.OPT_STORE_Z, 1)
+        ctx.set_option(logfx.OPT_ROWS1, 64)
+        ctx.set_option(logfx.OPT_ROWS2, 64)
