@@ -76,9 +76,10 @@ TRAFFIC_ROWS = [64, 32]
 TRAFFIC_BYTES = {"pass1_kernel": (67492 * 2.0 + 524819 * 1.0) * 1024,
                  "pass2z_kernel": (270230 * 2.0 + 66880 * 1.0) * 1024}
 # Algorithmic HBM bytes per pixel of each kernel: pass 1 reads the 16-bit
-# image and writes the (Z_1, Z_2) int32 pair; pass 2 reads the pair and
-# writes the output byte.
-KERNEL_BYTES_PER_PX = {"pass1_kernel": 2 + 8, "pass2z_kernel": 8 + 1}
+# image and writes the strengths' plane of 16-bit codes and their plane of
+# low halves (4 bytes each); pass 2 reads the codes (the low halves only of
+# the few rows the codes leave undecided) and writes the output byte.
+KERNEL_BYTES_PER_PX = {"pass1_kernel": 2 + 8, "pass2z_kernel": 4 + 1}
 
 
 # The sources the pipeline kernels (pass 1, finalize, pass 2) are compiled

@@ -750,8 +750,8 @@ void cell_layout(int n, const logfx_image *imgs, const Plan &pl, int rows, long 
 // long again (`alone`) as with others to fill its waits, so a call takes
 // about (rows + halo) max(alone, tiles per CU, rounded up) of them: low strips
 // where tall ones leave CUs idle, tall ones where the halo rows add up.
-// Pass 1, measured: 512^2 34 us with 64 rows, 12 with 7; 2000^2 45 and 29
-// with 25; 4000^2 68 with 61 and 63 with 34; pass 2: 512^2 14.7 and 8.4
+// Pass 1, measured: 512^2 34 us with 64 rows, 12 with 8; 2000^2 45 and 29
+// with 24; 4000^2 68 with 61 and 64 with 32; pass 2: 512^2 14.7 and 8.4
 // with 8, 2000^2 19.4 and 14.0 with 24, 6000^2 57 with 64 and 83 with 8.
 // From 2^25 pixels on, the tallest is within 4 % of the best.
 int strip_rows(int n, const logfx_image *imgs, long long tw, int most, int step, int halo, double alone) {
@@ -805,14 +805,13 @@ int prepare(logfx_ctx *ctx, int n, const logfx_image *imgs, const logfx_params *
     // image's statistics are the same bits in a batch and alone.  Its matrix
     // form works through blocks of 8 rows, the strip's and one above and below
     // it: 62 rows.)
-    // Integer path: the strip and the two halo rows are whole rounds of the
-    // row ring, since rows left over take the rolled loop (8192^2: 213 us with
-    // 64 rows, 201 with 61), and five workgroups' LDS fit a CU (196 with 43).
-    // With the gate's cells, whose sums leave the tile at its end, the tallest
-    // that four workgroups' LDS allows (32 of 2048^2: 469 with 43, 451 with 61).
-    const int ring = 2 * c.pl.rb + 1, most1 = ((features ? 62 : 44) + 2) / ring * ring - 2;
+    // Integer path: up to 48 rows, for which five workgroups' LDS fit a CU
+    // (8192^2: 196 us with 48 rows, 213 with 64, 199 with 43).  With the
+    // gate's cells, whose sums leave the tile at its end, the tallest that
+    // four workgroups' allows (32 of 2048^2: 454 with 48, 449 with 61).
     if (!ctx->tiles.set1)
-        c.rows1 = c.pl.i32 ? strip_rows(n, imgs, tile_out_width(kHalo1), most1, ring, 6, 1.7) : c.table ? 62 : c.rows1;
+        c.rows1 = c.pl.i32 ? strip_rows(n, imgs, tile_out_width(kHalo1), features ? 62 : 48, 4, 6, 1.7)
+                : c.table ? 62 : c.rows1;
     if (features) {
         // pass 1 keeps a slot per (cell row, cell column) a tile spans in
         // LDS beside the tile: lower the strip height where they would not
@@ -1094,16 +1093,14 @@ int build_launches(logfx_ctx *ctx, const Call &c, const logfx_params *p, double 
     else fill_args<OrbitTapsD, double>(c, ctx, p, L, Z, k.p1.d, k.p2.d, k.dbg, false);
     k.matrix = c.table != nullptr && !k.dbg;
     if (k.matrix) {
-        MatArgs &m = k.i32 ? k.p1.i.mat : k.p1.d.mat;
+        MatArgs &m = k.p1.d.mat;   // the FP64 path only
         m.table = c.table;
-        m.planes = c.pl.maxpix <= 255.0 && k.i32 ? 1 : 2;
         for (int slot = 0; slot < 2; ++slot) {
             // the planes hold the pixels' bytes less 128
             const MaskInfo &mi = c.pl.mi[c.pl.order[slot]];
-            const double sum = 2.0 * mi.sumpos - mi.sumabs, off = (m.planes == 2 ? 128.0 * 257.0 : 128.0) * sum;
+            const double sum = 2.0 * mi.sumpos - mi.sumabs, off = 128.0 * 257.0 * sum;
             m.sum |= off != 0.0;
             m.kd[slot] = off;
-            m.ki[slot] = (int)(uint32_t)(int64_t)off;
         }
     }
     k.gx = c.pl.gx;

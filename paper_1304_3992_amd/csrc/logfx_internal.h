@@ -73,9 +73,7 @@ struct MatTable { unsigned char b[kMatBytes]; };
 struct MatArgs {
     const unsigned char *table;   // device copy of a MatTable
     int sum;                      // the masks do not both sum to zero:
-    int ki[2];                    // what the pixels' offset adds, int32 (modulo 2^32)
-    double kd[2];                 // and FP64
-    int planes;                   // bytes per pixel: 1 (images of at most 8 bits) or 2
+    double kd[2];                 // what the pixels' offset adds
 };
 
 // Device-side statistics written by the finalize kernel (LoG grid units).

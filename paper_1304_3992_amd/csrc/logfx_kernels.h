@@ -793,9 +793,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPass1Waves
         fend = min(__builtin_amdgcn_readfirstlane(cell_end(cy)), flast);
     };
 
-    // One step = one new input row.  Full groups of P steps are unrolled so
-    // the register rings rotate by renaming; the last partial group runs
-    // rolled.
+    // One step = one new input row.  Groups of P steps are unrolled so that
+    // the register rings rotate by renaming; the last group ends where the
+    // strip does.
     auto step = [&](const int si, auto clamp) __attribute__((always_inline)) {
         constexpr bool C = decltype(clamp)::value;
         Acc Ln[2];
@@ -857,13 +857,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPass1Waves
         }
     };
     auto run = [&](auto clamp) __attribute__((always_inline)) {
-        int si0 = 0;
-        for (; si0 + P <= nsteps; si0 += P) {
+        for (int si0 = 0; si0 < nsteps; si0 += P) {
 #pragma unroll
-            for (int ph = 0; ph < P; ++ph) step(si0 + ph, clamp);
+            for (int ph = 0; ph < P; ++ph) {
+                if (ph > 0 && si0 + ph >= nsteps) return;
+                step(si0 + ph, clamp);
+            }
             sums.fold();
         }
-        for (; si0 < nsteps; ++si0) step(si0, clamp);
     };
     static_assert(P <= kFoldRows, "rows between folds");
     // interior tile: every row and column the strip touches lies strictly

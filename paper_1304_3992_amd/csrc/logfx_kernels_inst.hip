@@ -18,16 +18,13 @@ namespace {   // one copy per radius pair: internal linkage keeps the units' cop
 
 // Pass-1 variants built: statistics only, maps, cells, stored strengths,
 // stored strengths with cells; on the integer path each also in the packed
-// form, and all but the maps in the matrix form, for one byte per pixel
-// (integer path) and two.
-template <class Acc, int PL>
-hipError_t pass1_matrix(const Pass1Args<typename kern::AccOps<Acc>::Taps> &a, int mode, int grid, hipStream_t s,
-                        int *max_grid) {
+// form, on the FP64 path all but the maps also in the matrix form.
+hipError_t pass1_matrix(const Pass1Args<OrbitTapsD> &a, int mode, int grid, hipStream_t s, int *max_grid) {
     switch (mode) {
-    case 0: return kern::p1m<Acc, LOGFX_RA, LOGFX_RB, 0, PL>(a, grid, s, max_grid);
-    case kP1Cells: return kern::p1m<Acc, LOGFX_RA, LOGFX_RB, kP1Cells, PL>(a, grid, s, max_grid);
-    case kP1StoreZ: return kern::p1m<Acc, LOGFX_RA, LOGFX_RB, kP1StoreZ, PL>(a, grid, s, max_grid);
-    case kP1StoreZ | kP1Cells: return kern::p1m<Acc, LOGFX_RA, LOGFX_RB, kP1StoreZ | kP1Cells, PL>(a, grid, s, max_grid);
+    case 0: return kern::p1m<LOGFX_RA, LOGFX_RB, 0>(a, grid, s, max_grid);
+    case kP1Cells: return kern::p1m<LOGFX_RA, LOGFX_RB, kP1Cells>(a, grid, s, max_grid);
+    case kP1StoreZ: return kern::p1m<LOGFX_RA, LOGFX_RB, kP1StoreZ>(a, grid, s, max_grid);
+    case kP1StoreZ | kP1Cells: return kern::p1m<LOGFX_RA, LOGFX_RB, kP1StoreZ | kP1Cells>(a, grid, s, max_grid);
     }
     return hipErrorInvalidValue;
 }
@@ -36,7 +33,7 @@ hipError_t pass1_any(const Pass1Args<typename kern::AccOps<Acc>::Taps> &a, int m
                      int *max_grid) {
     if (mode & kP1Matrix) {
         if constexpr (std::is_same<Acc, double>::value)
-            return pass1_matrix<Acc, 2>(a, mode & ~kP1Matrix, grid, s, max_grid);
+            return pass1_matrix(a, mode & ~kP1Matrix, grid, s, max_grid);
         return hipErrorInvalidValue;
     }
     switch (mode) {

@@ -5,17 +5,16 @@
 // spends most of pass 1 on it: a conversion and an FP64 multiply-add per
 // orbit.  The bytes' products need no more than int32, so here it costs the
 // vector unit the issue of the matrix instructions: 6001 x 3501, pass 1 169
-// -> 129 us.  (The integer path's packed form, two taps per instruction,
-// stays ahead of this one: 8192^2, 222 against 256 us; the kernel is bound by
-// vector and matrix instructions one after the other, at three waves per
-// SIMD, and the packed form has fewer of both together.)
+// -> 129 us.  (The integer path keeps its packed form, two taps per vector
+// instruction: 8192^2, 196 us against 256 for this one with int32 responses,
+// whose vector and matrix instructions ran one after the other at three waves
+// per SIMD.)
 //
 // Here pixels and taps are split into signed bytes, p = 256 (ph + 128) +
 // (pl + 128) and k = 256 kh + kl, and the products run as
 // v_mfma_i32_16x16x64_i8, whose sums are exact:
 //   L = 65536 sum kh ph + 256 sum (kh pl + kl ph) + sum kl pl + K0,
-// K0 = 128 * 257 sum k (0 for the zero-sum masks).  Images of at most 8 bits
-// have no high byte: L = 256 sum kh pl + sum kl pl + 128 sum k.
+// K0 = 128 * 257 sum k (0 for the zero-sum masks).
 //
 // GEMM rows are 16 output columns x, GEMM columns are 8 output rows of two
 // neighbouring blocks of 16 x, and the reduction runs over 2 image rows x 32
@@ -48,15 +47,6 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 // a + hi >= 0 iff some neighbour reaches -a; for a > 0, a + hi > 0, and
 // a + lo < 0 likewise: a crossing iff the two sums differ in sign.  ZERO: the
 // rule for a zero centre as well (opposite signs left / right or up / down).
-template <bool ZERO>
-__device__ inline int crossing(int a, int up, int dn, int lf, int rt, int thr, int &c) {
-    const int hi = max(max(max(up, dn), lf), max(rt, a)), lo = min(min(min(up, dn), lf), min(rt, a));
-    c = hi - lo;                  // below 2^31; |L| < 2^30
-    const int strong = thr - c;   // < 0 iff c > thr
-    int m = ((a + hi) ^ (a + lo)) & strong;
-    if constexpr (ZERO) m = a == 0 ? ((opposite(lf, rt) | opposite(up, dn)) ? strong : 0) : m;
-    return m >> 31;
-}
 __device__ inline double max_f64(double a, double b) {   // finite operands
     double r;
     asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
@@ -77,7 +67,6 @@ __device__ inline int crossing(double a, double up, double dn, double lf, double
     if constexpr (ZERO) m = a == 0.0 ? ((opposite(lf, rt) | opposite(up, dn)) ? strong : 0) : m;
     return m >> 31;
 }
-__device__ inline int masked(int c, int m) { return c & m; }
 __device__ inline double masked(double c, int m) {
     return __hiloint2double(__double2hiint(c) & m, __double2loint(c) & m);
 }
@@ -87,47 +76,25 @@ __device__ inline double masked(double c, int m) {
 // wave's planes of 8 rows x 80 bytes (5 units of 16 bytes: 8 rows of an
 // operand read lie in different banks); then the waves' responses, 8 rows of
 // 64 pairs with 16 bytes of padding.
-template <class Acc, int PL>
 struct MatLds {
-    static constexpr int PLANE = 8 * 80, WAVE = PL * PLANE;
-    static constexpr int REGION = PL == 2 ? 8192 : 4096;
+    static constexpr int PLANE = 8 * 80, WAVE = 2 * PLANE;
+    static constexpr int REGION = 8192;
     static_assert(kTileWaves * WAVE <= REGION, "ring region");
     static constexpr int RESP = REGION + kTileWaves * WAVE;
-    static constexpr int LROW = 64 * 2 * (int)sizeof(Acc) + 16, LWAVE = 8 * LROW;
+    static constexpr int LROW = 64 * 2 * (int)sizeof(double) + 16, LWAVE = 8 * LROW;
     static constexpr int BYTES = RESP + kTileWaves * LWAVE;
     static_assert(RESP % 16 == 0, "aligned responses");
 };
 
 // Waves per SIMD that the registers allow (the taps' operands alone take 40,
 // the sums of a block 24).
-template <class Acc, int MODE>
-constexpr int kPass1mWaves = !std::is_same<Acc, int>::value ? 2 : 3;
+constexpr int kPass1mWaves = 2;
 
-// Rows of a plane as a buffer of `bytes` bytes: lanes whose offset lies past
-// it store nothing, so the row loop's stores need no branch around them (a
-// branch would also hide from the compiler how many stores follow a load, and
-// make the wait for the load a wait for all of them).
-__device__ inline __amdgpu_buffer_rsrc_t row_buffer(void *p, unsigned bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)bytes, 0x00027000);
-}
-// store_strengths for column x of the row at element `row`, W columns wide
-// (x >= W: nothing).
-__device__ inline void put_strengths(const ZMap &m, long long row, unsigned x, unsigned W, const int (&z)[2]) {
-    const unsigned c0 = (unsigned)z[0] >> m.shift[0], c1 = (unsigned)z[1] << (16 - m.shift[1]);
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_perm(c1, c0, 0x07060100u),
-                                          row_buffer(static_cast<unsigned *>(m.hi) + row, 4 * W), 4 * x, 0, 0);
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_perm((unsigned)z[1], (unsigned)z[0], 0x05040100u),
-                                          row_buffer(static_cast<unsigned *>(m.lo) + row, 4 * W), 4 * x, 0, 0);
-}
-__device__ inline void put_strengths(const ZMap &m, long long row, unsigned x, unsigned W, const double (&z)[2]) {
-    if (x < W) store_strengths(m, row, x, z);
-}
-
-template <class Acc, int RA, int RB, int MODE, bool LOOP, int PL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPass1mWaves<Acc, MODE>)))
-void pass1m_kernel(Pass1Args<typename AccOps<Acc>::Taps> a) {
-    using M = MatLds<Acc, PL>;
-    constexpr bool I32 = std::is_same<Acc, int>::value;
+template <int RA, int RB, int MODE, bool LOOP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPass1mWaves)))
+void pass1m_kernel(Pass1Args<OrbitTapsD> a) {
+    using M = MatLds;
+    using Acc = double;
     constexpr int HL = kHalo1, OW = kWave - 2 * HL, TW = tile_out_width(HL);
     constexpr int GA = (RA + 1) / 2, GB = (RB + 1) / 2;   // pairs of distances of the two masks
     constexpr int NP = 1 + 2 * GB;                        // row pairs: the centre, then g above, g below
@@ -187,7 +154,6 @@ void pass1m_kernel(Pass1Args<typename AccOps<Acc>::Taps> a) {
     const int Rv = __builtin_amdgcn_readfirstlane(min(a.rows, H - y0));
     const int base = x0 + wave * OW - HL, xc = base + lane;
     const bool outc = lane >= HL && lane < HL + OW && xc < W;
-    const unsigned sx = outc ? (unsigned)xc : 0x3FFFFFFFu;   // the lane's column in the Z map, past every row's end
     const long long zoff = (long long)__builtin_amdgcn_readfirstlane((int)(J.zoff >> 32)) << 32 |
                            (unsigned)__builtin_amdgcn_readfirstlane((int)J.zoff);
     const bool clampL = xc <= 0, clampR = xc >= W - 1;
@@ -272,10 +238,9 @@ void pass1m_kernel(Pass1Args<typename AccOps<Acc>::Taps> a) {
                 *reinterpret_cast<uint2 *>(d) =
                     make_uint2(__builtin_amdgcn_perm(v.y, v.x, 0x06040200u) ^ 0x80808080u,
                                __builtin_amdgcn_perm(v.w, v.z, 0x06040200u) ^ 0x80808080u);
-                if constexpr (PL == 2)
-                    *reinterpret_cast<uint2 *>(d + M::PLANE) =
-                        make_uint2(__builtin_amdgcn_perm(v.y, v.x, 0x07050301u) ^ 0x80808080u,
-                                   __builtin_amdgcn_perm(v.w, v.z, 0x07050301u) ^ 0x80808080u);
+                *reinterpret_cast<uint2 *>(d + M::PLANE) =
+                    make_uint2(__builtin_amdgcn_perm(v.y, v.x, 0x07050301u) ^ 0x80808080u,
+                               __builtin_amdgcn_perm(v.w, v.z, 0x07050301u) ^ 0x80808080u);
             }
         };
         // both responses of the 8 rows of block b to LDS; whether one is zero
@@ -290,7 +255,7 @@ void pass1m_kernel(Pass1Args<typename AccOps<Acc>::Taps> a) {
                 auto read = [&](const int j, i32x4 &l, i32x4 &h) __attribute__((always_inline)) {
                     const unsigned char *src = sm + (at[j] ^ flip) + 32 * p;
                     l = *reinterpret_cast<const i32x4 *>(src);
-                    if constexpr (PL == 2) h = *reinterpret_cast<const i32x4 *>(src + M::PLANE);
+                    h = *reinterpret_cast<const i32x4 *>(src + M::PLANE);
                 };
                 read(0, bl, bh);
 #pragma unroll
@@ -304,12 +269,10 @@ void pass1m_kernel(Pass1Args<typename AccOps<Acc>::Taps> a) {
                         ll[0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ta[gc][1], bl, ll[0], 0, 0, 0);
                         mid[0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ta[gc][0], bl, mid[0], 0, 0, 0);
                     }
-                    if constexpr (PL == 2) {
-                        hh[1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(tb[g][0], bh, hh[1], 0, 0, 0);
-                        if (g <= GA) hh[0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ta[gc][0], bh, hh[0], 0, 0, 0);
-                        mid[1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(tb[g][1], bh, mid[1], 0, 0, 0);
-                        if (g <= GA) mid[0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ta[gc][1], bh, mid[0], 0, 0, 0);
-                    }
+                    hh[1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(tb[g][0], bh, hh[1], 0, 0, 0);
+                    if (g <= GA) hh[0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ta[gc][0], bh, hh[0], 0, 0, 0);
+                    mid[1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(tb[g][1], bh, mid[1], 0, 0, 0);
+                    if (g <= GA) mid[0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ta[gc][1], bh, mid[0], 0, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);   // keeps the reads one pair ahead, not all at once
                     bl = nl;
                     bh = nh;
@@ -321,30 +284,21 @@ void pass1m_kernel(Pass1Args<typename AccOps<Acc>::Taps> a) {
                     for (int i = 0; i < 4; ++i) {
                         int t = (mid[m][i] << 8) + ll[m][i];
                         asm("" : "+v"(t));   // two shift-adds (left to itself the compiler takes three instructions)
-                        if constexpr (I32) r[m][i] = PL == 2 ? (hh[m][i] << 16) + t : t;
-                        else r[m][i] = __fma_rn((double)hh[m][i], 65536.0, (double)t);
+                        r[m][i] = __fma_rn((double)hh[m][i], 65536.0, (double)t);
                     }
                 if (a.mat.sum) {   // masks that do not sum to zero
 #pragma unroll
                     for (int m = 0; m < 2; ++m)
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            if constexpr (I32) r[m][i] += a.mat.ki[m];
-                            else r[m][i] += a.mat.kd[m];
-                        }
+                        for (int i = 0; i < 4; ++i) r[m][i] += a.mat.kd[m];
                 }
 #pragma unroll
                 for (int m = 0; m < 2; ++m)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) zeros |= __ballot(r[m][i] == Acc(0));
                 unsigned char *d = rput + p * 32 * 2 * (int)sizeof(Acc);
-                if constexpr (I32) {
-                    *reinterpret_cast<i32x4 *>(d) = i32x4{r[0][0], r[1][0], r[0][1], r[1][1]};
-                    *reinterpret_cast<i32x4 *>(d + 16) = i32x4{r[0][2], r[1][2], r[0][3], r[1][3]};
-                } else {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) *reinterpret_cast<double2 *>(d + 16 * i) = make_double2(r[0][i], r[1][i]);
-                }
+                for (int i = 0; i < 4; ++i) *reinterpret_cast<double2 *>(d + 16 * i) = make_double2(r[0][i], r[1][i]);
                 __builtin_amdgcn_sched_barrier(0);
             }
             return zeros != 0;
@@ -382,7 +336,7 @@ void pass1m_kernel(Pass1Args<typename AccOps<Acc>::Taps> a) {
                     fc[j] -= (unsigned)m;
                 }
                 if constexpr ((MODE & kP1StoreZ) != 0) {
-                    put_strengths(a.z, zoff + (long long)r * W, sx, (unsigned)W, z);
+                    if (outc) store_strengths(a.z, zoff + (long long)r * W, (unsigned)xc, z);
                 }
                 if constexpr ((MODE & kP1Cells) != 0) {
                     fv += pixel;
@@ -406,8 +360,7 @@ void pass1m_kernel(Pass1Args<typename AccOps<Acc>::Taps> a) {
                 for (int i = 0; i < 8; ++i) {
                     const int sr = i - 1 + RB;
                     const unsigned char *p = sm + (((sr >> 3) ^ (b & 1)) * M::REGION) + wave * M::WAVE + (sr & 7) * 80 + 8 + lane;
-                    pv[i] = p[0] ^ 0x80u;
-                    if constexpr (PL == 2) pv[i] |= (p[M::PLANE] ^ 0x80u) << 8;
+                    pv[i] = (p[0] ^ 0x80u) | (p[M::PLANE] ^ 0x80u) << 8;
                 }
             }
         };
@@ -526,16 +479,16 @@ void pass1m_kernel(Pass1Args<typename AccOps<Acc>::Taps> a) {
     });
 }
 
-template <class Acc, int RA, int RB, int MODE, int PL>
-hipError_t p1m(const Pass1Args<typename AccOps<Acc>::Taps> &a, int grid, hipStream_t s, int *max_grid) {
+template <int RA, int RB, int MODE>
+hipError_t p1m(const Pass1Args<OrbitTapsD> &a, int grid, hipStream_t s, int *max_grid) {
     const size_t shm = (MODE & kP1Cells) != 0 ? 2 * sizeof(unsigned) * a.cell_rows * a.cell_slots : 0;
     const dim3 block(kTileWaves * kWave);
     constexpr bool CAN_LOOP = (MODE & kP1Cells) == 0;   // the cell-summing form runs one tile per workgroup
-    if (max_grid) return occupancy(pass1m_kernel<Acc, RA, RB, MODE, CAN_LOOP, PL>, shm, max_grid);
+    if (max_grid) return occupancy(pass1m_kernel<RA, RB, MODE, CAN_LOOP>, shm, max_grid);
     if (!CAN_LOOP || grid >= a.L.total1)
-        hipLaunchKernelGGL((pass1m_kernel<Acc, RA, RB, MODE, false, PL>), dim3(a.L.total1), block, shm, s, a);
+        hipLaunchKernelGGL((pass1m_kernel<RA, RB, MODE, false>), dim3(a.L.total1), block, shm, s, a);
     else
-        hipLaunchKernelGGL((pass1m_kernel<Acc, RA, RB, MODE, CAN_LOOP, PL>), dim3(grid), block, shm, s, a);
+        hipLaunchKernelGGL((pass1m_kernel<RA, RB, MODE, CAN_LOOP>), dim3(grid), block, shm, s, a);
     return hipGetLastError();
 }
 
