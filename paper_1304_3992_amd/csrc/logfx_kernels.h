@@ -6,7 +6,8 @@
 //   F = hybrid_median(E) (Sec. 3.4).
 // T_j depends on the global deviation of Z_j, a grid-wide quantity, so the
 // work runs as   pass 1 (LoG, Z, per-tile sums; by default the pair
-// (Z_1, Z_2) of every pixel stored to HBM) -> finalize (T_j) -> pass 2.
+// (Z_1, Z_2) of every pixel stored to HBM) -> finalize (T_j; in pass 2
+// itself for images of few tiles) -> pass 2.
 // Pass 2 normally reads the stored pairs (pass2z_kernel, in
 // logfx_pass2z.hip: deviation, OR and the median on per-lane column words);
 // the recompute form below (pass2_kernel) is the fallback when the pair
@@ -26,9 +27,10 @@
 // Exactness.  Mask taps are integers k on a power-of-two grid, and the LoG
 // is evaluated on D4 orbit sums of pixels, L = sum_o k_o * O_o, or in the
 // packed form on the row-pair sums v(d, c) that make up the orbits, two
-// taps per dot product.  Every sum is exact (int32 when
-// sum|k| (2^bits - 1) < 2^30, else FP64 below 2^52), so L and Z agree bit
-// for bit with any exact evaluation.
+// taps per dot product (16-bit images: on bytes on the matrix cores,
+// logfx_pass1m.h).  Every sum is exact (int32 while |L| stays below 2^30,
+// else FP64 below 2^52), so L and Z agree bit for bit with any exact
+// evaluation.
 #pragma once
 #include "logfx_internal.h"
 #include "logfx_bits.h"
@@ -309,7 +311,8 @@ template <> struct LaneSums<int> {
     // word k of the wave's sums; keep: this lane's count
     __device__ unsigned long long word(int k, bool keep) const {
         const int j = k & 1;
-        const unsigned long long v = k < 2 ? s[j] : k < 4 ? (q[j] & 0xFFFFFFFFull) : ((unsigned long long)h[j] << 16) + (q[j] >> 32);
+        const unsigned long long v = k < 2 ? s[j] : k < 4 ? (q[j] & 0xFFFFFFFFull)
+                                                          : ((unsigned long long)h[j] << 16) + (q[j] >> 32);
         return wave_total(keep ? v : 0ull);
     }
     static __device__ unsigned long long plus(unsigned long long a, unsigned long long b) { return a + b; }
@@ -658,7 +661,7 @@ __device__ inline void restore_strengths(const ZMap &m, unsigned hi, uint2 lo, d
 // their sums, 4 for the store), with the staging and the ends of the strips
 // 77 by the counters; its LDS reads, at any pixel alignment, keep the LDS
 // busy for most of the same time.  8192^2: 233 us with 77 + 20 instructions
-// and strips of 64 rows, 196 with these and 43.
+// and strips of 64 rows, 196 with these and 48.
 // Occupancy: the integer path is held to 128 VGPRs (4 waves per SIMD, the
 // LDS limit); the FP64 path keeps its registers.  Variants that need more
 // run at fewer waves rather than spill.  No kernel here may spill vector
