@@ -229,16 +229,17 @@ __device__ inline Acc zc_value(Acc a, Acc up, Acc dn, Acc lf, Acc rt, Thr thr, b
     // hi / lo: largest / smallest of the five values.  For a < 0, a + lo < 0,
     // and a + hi >= 0 iff some neighbour reaches -a (a itself cannot); for
     // a > 0, a + hi > 0, and a + lo < 0 likewise.  So for either sign a is a
-    // crossing iff a + lo < 0 <= a + hi, i.e. 0 <= a + hi < hi - lo (one
-    // unsigned compare of integers).  For a = 0 the branch below decides.
+    // crossing iff a + lo < 0 <= a + hi; in integers 0 <= a + hi < hi - lo,
+    // one unsigned compare (FP64 sums may be rounded ones, which keep the
+    // signs of a + lo and a + hi only).  For a = 0 the branch below decides.
     const Acc hi = max(max(max(max(up, dn), lf), rt), a);
     const Acc lo = min(min(min(min(up, dn), lf), rt), a);
-    const Acc c = hi - lo, u = a + hi;   // exact: |L| < 2^30 (int) or 2^52 (FP64)
+    const Acc c = hi - lo;   // exact: |L| < 2^30 (int) or 2^52 (FP64)
     // lane masks from the compares on: combined on the scalar unit, and the
     // count of crossings needs no compare of its own
     const uint64_t strong = __ballot(c > thr) & __ballot(keep);
-    if constexpr (std::is_same<Acc, int>::value) mask = __ballot((unsigned)u < (unsigned)c) & strong;
-    else mask = __ballot(u >= 0) & __ballot(u < c) & strong;
+    if constexpr (std::is_same<Acc, int>::value) mask = __ballot((unsigned)(a + hi) < (unsigned)c) & strong;
+    else mask = __ballot(((a < 0) & (a + hi >= 0)) | ((a > 0) & (a + lo < 0))) & strong;
     const uint64_t zero = __ballot(a == 0);
     if (zero) mask = (mask & ~zero) | (zero & strong & __ballot(opposite(lf, rt) | opposite(up, dn)));
     return __builtin_amdgcn_inverse_ballot_w64(mask) ? c : Acc(0);
