@@ -611,29 +611,30 @@ __device__ inline ImageJob job_of(const Launch &L, int image) {
 }
 
 
-// p[x] = v for a row p held in scalar registers: the store takes the row as
-// its scalar base and the lane's column as a 32-bit byte offset (W < 2^30),
-// with no 64-bit address arithmetic on the vector unit.
+// Element `at` + lane of a plane = v, `at` wave-uniform (a row's first element
+// plus the wave's first column, at least -1): the store takes plane + at as its
+// 64-bit scalar base and the lane as a 32-bit byte offset, below 64 sizeof(T),
+// with no address arithmetic on the vector unit.
 template <class T>
-__device__ inline void put(void *plane, long long row, unsigned x, T v) {
+__device__ inline void put(void *plane, long long at, int lane, T v) {
     typedef __attribute__((address_space(1))) char G;
-    G *p = (G *)(static_cast<T *>(plane) + row);
-    unsigned off = (unsigned)sizeof(T) * x;
+    G *p = (G *)(static_cast<T *>(plane) + at);
+    unsigned off = (unsigned)sizeof(T) * (unsigned)lane;
     asm("" : "+s"(p), "+v"(off));   // else the sum is taken apart before the store's form is chosen
     *(__attribute__((address_space(1))) T *)(p + off) = v;
 }
 
-// Strengths into and out of the Z map (ZMap in logfx_internal.h), row
-// wave-uniform.  The codes and low halves are packed by byte permutes: two of
+// Strengths into and out of the Z map (ZMap in logfx_internal.h), at element
+// `at` + lane.  The codes and low halves are packed by byte permutes: two of
 // them and two shifts per pixel on the integer path.
-__device__ inline void store_strengths(const ZMap &m, long long row, unsigned x, const int (&z)[2]) {
+__device__ inline void store_strengths(const ZMap &m, long long at, int lane, const int (&z)[2]) {
     const unsigned c0 = (unsigned)z[0] >> m.shift[0], c1 = (unsigned)z[1] << (16 - m.shift[1]);
-    put(m.hi, row, x, __builtin_amdgcn_perm(c1, c0, 0x07060100u));
-    put(m.lo, row, x, __builtin_amdgcn_perm((unsigned)z[1], (unsigned)z[0], 0x05040100u));
+    put(m.hi, at, lane, __builtin_amdgcn_perm(c1, c0, 0x07060100u));
+    put(m.lo, at, lane, __builtin_amdgcn_perm((unsigned)z[1], (unsigned)z[0], 0x05040100u));
 }
-__device__ inline void store_strengths(const ZMap &m, long long row, unsigned x, const double (&z)[2]) {
+__device__ inline void store_strengths(const ZMap &m, long long at, int lane, const double (&z)[2]) {
     if (!m.split) {
-        (static_cast<double2 *>(m.hi) + row)[x] = make_double2(z[0], z[1]);
+        (static_cast<double2 *>(m.hi) + at)[lane] = make_double2(z[0], z[1]);
         return;
     }
     // z + 2^52 holds the integer z in its mantissa
@@ -642,8 +643,8 @@ __device__ inline void store_strengths(const ZMap &m, long long row, unsigned x,
     const unsigned c0 = __builtin_amdgcn_alignbit(__double2hiint(i0), l0, m.shift[0]);
     const unsigned c1 = __builtin_amdgcn_alignbit(__double2hiint(i1), l1, m.shift[1]);
     typedef unsigned V2 __attribute__((ext_vector_type(2)));
-    put(m.hi, row, x, __builtin_amdgcn_perm(c1, c0, 0x05040100u));
-    put(m.lo, row, x, V2{l0, l1});
+    put(m.hi, at, lane, __builtin_amdgcn_perm(c1, c0, 0x05040100u));
+    put(m.lo, at, lane, V2{l0, l1});
 }
 // The exact strengths from both planes.
 __device__ inline void restore_strengths(const ZMap &m, unsigned hi, unsigned lo, double (&z)[2]) {
@@ -847,8 +848,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPass1Waves
             }
         }
         if constexpr ((MODE & kP1StoreZ) != 0) {
-            // the row's base is wave-uniform: scalar base + the lane's column
-            if (use) store_strengths(a.z, J.zoff + (long long)r * g.W, (unsigned)g.xc, zr);
+            // the wave's first column of the row is wave-uniform
+            if (use) store_strengths(a.z, J.zoff + (long long)r * g.W + g.base, g.lane, zr);
         }
         if constexpr ((MODE & kP1Cells) != 0) {
             // every lane accumulates; the halo rows before the strip are

@@ -336,7 +336,7 @@ void pass1m_kernel(Pass1Args<OrbitTapsD> a) {
                     fc[j] -= (unsigned)m;
                 }
                 if constexpr ((MODE & kP1StoreZ) != 0) {
-                    if (outc) store_strengths(a.z, zoff + (long long)r * W, (unsigned)xc, z);
+                    if (outc) store_strengths(a.z, zoff + (long long)r * W + base, lane, z);
                 }
                 if constexpr ((MODE & kP1Cells) != 0) {
                     fv += pixel;

@@ -973,3 +973,29 @@ def test_staging_of_inner_tiles(ctx, w, dtype):
         ctx.set_option(logfx.OPT_STORE_Z, 1)
         ctx.set_option(logfx.OPT_ROWS1, 64)
         ctx.set_option(logfx.OPT_ROWS2, 64)
+
+
+def test_strengths_past_column_2_29():
+    """A 16-bit image of one row, wider than 2^29 columns, on the FP64 path
+    whose low strength words take 8 bytes a pixel: byte offsets of a row pass
+    2^32.  Little noise and a threshold in its midst, so that every decision
+    reads the low words.  The map at the row's two ends, and on either side
+    of column 2^29, equals that of crops (away from their cut edges)."""
+    import torch
+    W, edge = (1 << 29) + 3001, 1 << 29
+    g = torch.Generator(device="cuda").manual_seed(9)
+    img = torch.randint(20000, 20061, (1, W), generator=g, device="cuda", dtype=torch.int16)
+    taps = masks()[1]
+    cuts = [(0, 5000), (edge - 2000, W)]
+    with logfx.Context(0) as c:
+        _, rep = c.extract(img[:, :100000].contiguous(), logfx.Params(*taps), bits=16, report=True)
+        params = logfx.Params(*taps, std_mode=logfx.STD_ABS, std_k=rep["thresh"][0] / 2, smooth=False)
+        out = c.extract(img, params, bits=16)
+        for a, b in cuts:
+            want = c.extract(img[:, a:b].contiguous(), params, bits=16)[0]
+            got = out[0, a:b]
+            lo, hi = (0 if a == 0 else 16), (b - a if b == W else b - a - 16)
+            assert 0.02 < float(want[lo:hi].float().mean()) < 0.98
+            assert torch.equal(got[lo:hi], want[lo:hi]), (a, b)
+    del img, out
+    torch.cuda.empty_cache()
