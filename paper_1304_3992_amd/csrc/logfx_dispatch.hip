@@ -11,7 +11,7 @@ namespace logfx {
 
 #define X(A, B)                                                                                   \
     hipError_t pass1_i_r##A##_##B(const Pass1Args<OrbitTapsI> &, int, int, hipStream_t, int *);  \
-    hipError_t pass1_d_r##A##_##B(const Pass1Args<OrbitTapsD> &, int, int, hipStream_t, int *);  \
+    hipError_t pass1_d_r##A##_##B(const Pass1Args<OrbitTapsD> &, const MatTable &, int, int, hipStream_t, int *);  \
     hipError_t pass2_i_r##A##_##B(const Pass2Args<OrbitTapsI> &, int, hipStream_t, int *);        \
     hipError_t pass2_d_r##A##_##B(const Pass2Args<OrbitTapsD> &, int, hipStream_t, int *);
 LOGFX_RADII(X)
@@ -137,16 +137,7 @@ __global__ __launch_bounds__(kFinThreads) void finalize_exact_kernel(FinalizeArg
     image_stats(a, J.img.H * J.img.W, s, z, a.stats[image]);
 }
 
-__global__ __launch_bounds__(256) void write_table(MatTable t, unsigned char *dst) {
-    for (int i = threadIdx.x; i < kMatBytes; i += 256) dst[i] = t.b[i];
-}
-
 }  // namespace kern
-
-hipError_t launch_write_table(const MatTable &t, unsigned char *dst, hipStream_t s) {
-    hipLaunchKernelGGL(kern::write_table, dim3(1), dim3(256), 0, s, t, dst);
-    return hipGetLastError();
-}
 
 hipError_t launch_pass1_i(int ra, int rb, const Pass1Args<OrbitTapsI> &a, int mode, int grid,
                           hipStream_t s, int *max_grid) {
@@ -155,9 +146,9 @@ hipError_t launch_pass1_i(int ra, int rb, const Pass1Args<OrbitTapsI> &a, int mo
 #undef X
     return hipErrorInvalidValue;
 }
-hipError_t launch_pass1_d(int ra, int rb, const Pass1Args<OrbitTapsD> &a, int mode, int grid,
+hipError_t launch_pass1_d(int ra, int rb, const Pass1Args<OrbitTapsD> &a, const MatTable &t, int mode, int grid,
                           hipStream_t s, int *max_grid) {
-#define X(A, B) if (ra == A && rb == B) return pass1_d_r##A##_##B(a, mode, grid, s, max_grid);
+#define X(A, B) if (ra == A && rb == B) return pass1_d_r##A##_##B(a, t, mode, grid, s, max_grid);
     LOGFX_RADII(X)
 #undef X
     return hipErrorInvalidValue;

@@ -102,12 +102,6 @@ struct logfx_ctx {
     std::vector<hipEvent_t> events;
     long long timed_calls = 0;
     std::vector<char> timed_graph;   // per timed call: 1 if it was a graph replay
-    // tap tables of the matrix form, one per pair of masks the context has
-    // met.  A table is never changed or freed before the context is: a graph
-    // that a caller captured keeps its address.  Past kMatTables pairs the
-    // other forms run.
-    unsigned char *mat_dev = nullptr;          // [kMatTables][kMatBytes]
-    std::vector<MatTable> mat_tabs;            // what the first of them hold
     int alloc_count = 0;
     int fail_alloc_at = -1;          // test hook: LOGFX_FAIL_ALLOC=n fails the n-th allocation
     // device address of the static scratch of logfx_extract_noalloc on this
@@ -135,8 +129,6 @@ struct logfx_ctx {
 };
 
 namespace {
-
-constexpr size_t kMatTables = 64;   // 74 KB of device memory
 
 // LOGFX_LOG=1 (read once): one line per call and every error on stderr.
 bool log_on() {
@@ -627,31 +619,8 @@ void fill_taps(const Plan &pl, Taps &t) {
 // does not turn it off (LOGFX_OPT_PACKED_LOG).
 bool use_packed(const logfx_ctx *ctx, const Plan &pl) { return pl.pk_ok && ctx->pack_log; }
 
-// Device table of the plan's taps for the matrix form, written on the call's
-// stream when the context meets the masks for the first time; nullptr when
-// the form does not apply (LOGFX_OPT_PACKED_LOG = 0 asks for the 32-bit form)
-// or its table cannot be made now: the caller is capturing the stream, which
-// would put off the writing to a replay.
-const unsigned char *matrix_table(logfx_ctx *ctx, const Plan &pl, hipStream_t s) {
-    if (!pl.mat_ok || pl.i32 || !ctx->pack_log) return nullptr;
-    for (size_t i = 0; i < ctx->mat_tabs.size(); ++i)
-        if (std::memcmp(&ctx->mat_tabs[i], &pl.mat, sizeof pl.mat) == 0) return ctx->mat_dev + i * kMatBytes;
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (ctx->mat_tabs.size() >= kMatTables || hipStreamIsCapturing(s, &st) != hipSuccess ||
-        st != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
-    if (!ctx->mat_dev && hipMalloc((void **)&ctx->mat_dev, kMatTables * kMatBytes) != hipSuccess) {
-        ctx->mat_dev = nullptr;
-        (void)hipGetLastError();   // clear the sticky out-of-memory error
-        return nullptr;
-    }
-    unsigned char *dst = ctx->mat_dev + ctx->mat_tabs.size() * kMatBytes;
-    if (launch_write_table(pl.mat, dst, s) != hipSuccess) return nullptr;
-    ctx->mat_tabs.push_back(pl.mat);
-    return dst;
-}
+// The same of the matrix form, on the FP64 path.
+bool use_matrix(const logfx_ctx *ctx, const Plan &pl) { return pl.mat_ok && !pl.i32 && ctx->pack_log; }
 
 // ------------------------------------------------------------ one call
 // Tiling of one image in both passes.
@@ -721,7 +690,6 @@ struct Call {
     int n = 1;
     bool storez = false;   // pass 1 stores the strengths in ctx->zmap, pass 2 reads them
     long long px = 0;      // pixels of all images (when the strengths are stored)
-    const unsigned char *table = nullptr;   // taps of the matrix form, where it runs
     int rows1 = 64, rows2 = 64;   // strip heights of this call
     int cell_slots = 0, cell_rows = 0;   // LDS slots of pass 1's gate cell sums per tile
     std::vector<ImageTiles> tiles;
@@ -798,7 +766,6 @@ int prepare(logfx_ctx *ctx, int n, const logfx_image *imgs, const logfx_params *
     if (n < 1 || !imgs) return set_err(ctx, LOGFX_EINVAL, "no images");
     int rc = check_all(ctx, &imgs[0], p, c.pl);
     if (rc != LOGFX_OK) return rc;
-    c.table = matrix_table(ctx, c.pl, s);
     c.rows1 = ctx->tiles.rows1;
     c.rows2 = ctx->tiles.rows2;
     // (The FP64 path, whose sums round, keeps to one height, so that an
@@ -811,7 +778,7 @@ int prepare(logfx_ctx *ctx, int n, const logfx_image *imgs, const logfx_params *
     // four workgroups' allows (32 of 2048^2: 454 with 48, 449 with 61).
     if (!ctx->tiles.set1)
         c.rows1 = c.pl.i32 ? strip_rows(n, imgs, tile_out_width(kHalo1), features ? 62 : 48, 4, 6, 1.7)
-                : c.table ? 62 : c.rows1;
+                : use_matrix(ctx, c.pl) ? 62 : c.rows1;
     if (features) {
         // pass 1 keeps a slot per (cell row, cell column) a tile spans in
         // LDS beside the tile: lower the strip height where they would not
@@ -954,7 +921,8 @@ struct Launches {
     int ra, rb;
     bool i32;                      // exact int32 LoG, else FP64
     bool packed;                   // pass 1 on packed 16-bit sums (integer path)
-    bool matrix;                   // pass 1 on the matrix cores (either path; before the packed form)
+    bool matrix;                   // pass 1 on the matrix cores (FP64 path), with these taps
+    MatTable table;
     bool dbg;
     bool storez;
     // median cascade: further levels after pass 2 (pass 2 writes the
@@ -1042,7 +1010,7 @@ hipError_t launch_all(const Launches &k, hipStream_t s, hipEvent_t *ev, int unti
                      (k.matrix ? kP1Matrix : k.packed ? kP1Packed : 0);
     if (k.features && (e = gate::launch_zero_cells(k.cells, k.nsets, s)) != hipSuccess) return e;
     e = i32 ? launch_pass1_i(k.ra, k.rb, k.p1.i, mode, k.grid1, s)
-            : launch_pass1_d(k.ra, k.rb, k.p1.d, mode, k.grid1, s);
+            : launch_pass1_d(k.ra, k.rb, k.p1.d, k.table, mode, k.grid1, s);
     if (e != hipSuccess || until == UNTIL_PASS1) return e;
     if (until < UNTIL_OUTPUT) {   // the gate alone: no thresholds needed
         if ((e = gate::launch_finish_features(k.fin.L, k.cells, k.maxval, k.feats, k.gx, k.gy, s)) != hipSuccess) return e;
@@ -1091,10 +1059,10 @@ int build_launches(logfx_ctx *ctx, const Call &c, const logfx_params *p, double 
     k.packed = use_packed(ctx, c.pl);
     if (k.i32) fill_args<OrbitTapsI, int>(c, ctx, p, L, Z, k.p1.i, k.p2.i, k.dbg, k.packed);
     else fill_args<OrbitTapsD, double>(c, ctx, p, L, Z, k.p1.d, k.p2.d, k.dbg, false);
-    k.matrix = c.table != nullptr && !k.dbg;
+    k.matrix = use_matrix(ctx, c.pl) && !k.dbg;
     if (k.matrix) {
-        MatArgs &m = k.p1.d.mat;   // the FP64 path only
-        m.table = c.table;
+        MatArgs &m = k.p1.d.mat;
+        k.table = c.pl.mat;
         for (int slot = 0; slot < 2; ++slot) {
             // the planes hold the pixels' bytes less 128
             const MaskInfo &mi = c.pl.mi[c.pl.order[slot]];
@@ -1171,7 +1139,7 @@ int build_launches(logfx_ctx *ctx, const Call &c, const logfx_params *p, double 
         const bool i32 = k.i32;
         const int mode = (k.storez ? kP1StoreZ : 0) | (k.matrix ? kP1Matrix : k.packed ? kP1Packed : 0);
         hipError_t e = i32 ? launch_pass1_i(k.ra, k.rb, k.p1.i, mode, 0, nullptr, &m1)
-                           : launch_pass1_d(k.ra, k.rb, k.p1.d, mode, 0, nullptr, &m1);
+                           : launch_pass1_d(k.ra, k.rb, k.p1.d, k.table, mode, 0, nullptr, &m1);
         if (e == hipSuccess && k.storez)
             e = i32 ? launch_pass2z_i(k.p2.i, 0, nullptr, &m2) : launch_pass2z_d(k.p2.d, 0, nullptr, &m2);
         else if (e == hipSuccess)
@@ -1299,7 +1267,7 @@ int run(logfx_ctx *ctx, int n, const logfx_image *imgs, const logfx_params *p, u
         log_line("%s: %d image(s), first %lld x %lld, %s path, radii %d/%d, tiles %d/%d (rows %d/%d), %s, smooth %d%s%s",
              maps ? "extract_maps" : (n > 1 ? "extract_batch" : "extract"), n, (long long)imgs[0].height,
              (long long)imgs[0].width,
-             !c.pl.i32 ? "fp64" : k.packed ? "int32 (packed)" : "int32", c.pl.ra, c.pl.rb,
+             !c.pl.i32 ? k.matrix ? "fp64 (matrix)" : "fp64" : k.packed ? "int32 (packed)" : "int32", c.pl.ra, c.pl.rb,
              c.L.total1, c.L.total2, c.rows1, c.rows2, c.storez ? "stored strengths" : "recomputed strengths",
              p->smooth, gated ? " (gated)" : "", use_graph ? ", graph" : "");
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -1518,7 +1486,6 @@ int logfx_destroy(logfx_ctx *ctx) {
             if (S.own1) (void)hipHostFree(S.own1);
             if (S.own2) (void)hipHostFree(S.own2);
         }
-        (void)hipFree(ctx->mat_dev);
         (void)hipFree(ctx->zmap);
         (void)hipFree(ctx->cmap);
         (void)hipFree(ctx->partials);

@@ -52,15 +52,6 @@ __host__ __device__ constexpr int orbit_index(int i, int j) { return i * (i + 1)
 constexpr int kPkPerRow = 3;
 constexpr int kPkTaps = (kMaxRadius + 1) * kPkPerRow;
 
-// Orbit taps of both masks, in integer grid units.  The integer path keeps
-// them as int (they fit 24-bit signed), and in the packed form above when
-// it applies; the FP64 path as double.
-struct OrbitTapsI {
-    int k[2][kMaxOrbits];
-    unsigned pk[2][kPkTaps];
-};
-struct OrbitTapsD { double k[2][kMaxOrbits]; };
-
 // Taps of the matrix form (kP1Matrix): per mask kMatEntries rows, each as two
 // byte rows (high, then low: k = 256 kh + kl) of kMatRow bytes, tap column dx
 // at 23 + dx and zero elsewhere.  Entry 0 is the centre row, entry 1 the
@@ -71,10 +62,18 @@ constexpr int kMatRow = 48;
 constexpr int kMatBytes = 2 * kMatEntries * 2 * kMatRow;
 struct MatTable { unsigned char b[kMatBytes]; };
 struct MatArgs {
-    const unsigned char *table;   // device copy of a MatTable
-    int sum;                      // the masks do not both sum to zero:
-    double kd[2];                 // what the pixels' offset adds
+    int sum;       // the masks do not both sum to zero:
+    double kd[2];  // what the pixels' offset adds
 };
+
+// Orbit taps of both masks, in integer grid units.  The integer path keeps
+// them as int (they fit 24-bit signed), and in the packed form above when
+// it applies; the FP64 path as double.
+struct OrbitTapsI {
+    int k[2][kMaxOrbits];
+    unsigned pk[2][kPkTaps];
+};
+struct OrbitTapsD { double k[2][kMaxOrbits]; };
 
 // Device-side statistics written by the finalize kernel (LoG grid units).
 struct DevStats {
@@ -167,7 +166,7 @@ struct Pass1Args {
     double *dbgL[2];
     double *dbgZ[2];
     double unit[2];
-    MatArgs mat;           // the matrix form's taps (kP1Matrix)
+    MatArgs mat;           // the matrix form (kP1Matrix)
     // Strengths (kP1StoreZ): image i at element jobs[i].zoff, row pitch W.
     ZMap z;
     // Gate features (kP1Cells): [nimg][2][cells] counters, zeroed before
@@ -243,17 +242,16 @@ struct LevelArgs {
 // persistent).  max_grid, when non-null, receives the number of workgroups
 // that fit on the device at once and nothing is launched.
 // mode: a set of kP1* bits; with kP1Maps or kP1Cells one tile per workgroup.
+// t: the matrix form's taps (a kernel argument of its own), read by kP1Matrix alone.
 hipError_t launch_pass1_i(int ra, int rb, const Pass1Args<OrbitTapsI> &a, int mode, int grid,
                           hipStream_t s, int *max_grid = nullptr);
-hipError_t launch_pass1_d(int ra, int rb, const Pass1Args<OrbitTapsD> &a, int mode, int grid,
+hipError_t launch_pass1_d(int ra, int rb, const Pass1Args<OrbitTapsD> &a, const MatTable &t, int mode, int grid,
                           hipStream_t s, int *max_grid = nullptr);
 hipError_t launch_pass2_i(int ra, int rb, const Pass2Args<OrbitTapsI> &a, int grid, hipStream_t s,
                           int *max_grid = nullptr);
 hipError_t launch_pass2_d(int ra, int rb, const Pass2Args<OrbitTapsD> &a, int grid, hipStream_t s,
                           int *max_grid = nullptr);
 hipError_t launch_finalize(const FinalizeArgs &a, hipStream_t s);
-// Writes a tap table to device memory.
-hipError_t launch_write_table(const MatTable &t, unsigned char *dst, hipStream_t s);
 // Pass 2 on the strengths stored by pass 1 (no LoG, no LDS): tiles of
 // tile_out_width(kHalo2Z) columns, or tile_out_width(kHalo2Z5) with the 5x5
 // first stage (a.std5).

@@ -19,23 +19,19 @@ namespace {   // one copy per radius pair: internal linkage keeps the units' cop
 // Pass-1 variants built: statistics only, maps, cells, stored strengths,
 // stored strengths with cells; on the integer path each also in the packed
 // form, on the FP64 path all but the maps also in the matrix form.
-hipError_t pass1_matrix(const Pass1Args<OrbitTapsD> &a, int mode, int grid, hipStream_t s, int *max_grid) {
+hipError_t pass1_matrix(const Pass1Args<OrbitTapsD> &a, const MatTable &t, int mode, int grid, hipStream_t s,
+                        int *max_grid) {
     switch (mode) {
-    case 0: return kern::p1m<LOGFX_RA, LOGFX_RB, 0>(a, grid, s, max_grid);
-    case kP1Cells: return kern::p1m<LOGFX_RA, LOGFX_RB, kP1Cells>(a, grid, s, max_grid);
-    case kP1StoreZ: return kern::p1m<LOGFX_RA, LOGFX_RB, kP1StoreZ>(a, grid, s, max_grid);
-    case kP1StoreZ | kP1Cells: return kern::p1m<LOGFX_RA, LOGFX_RB, kP1StoreZ | kP1Cells>(a, grid, s, max_grid);
+    case 0: return kern::p1m<LOGFX_RA, LOGFX_RB, 0>(a, t, grid, s, max_grid);
+    case kP1Cells: return kern::p1m<LOGFX_RA, LOGFX_RB, kP1Cells>(a, t, grid, s, max_grid);
+    case kP1StoreZ: return kern::p1m<LOGFX_RA, LOGFX_RB, kP1StoreZ>(a, t, grid, s, max_grid);
+    case kP1StoreZ | kP1Cells: return kern::p1m<LOGFX_RA, LOGFX_RB, kP1StoreZ | kP1Cells>(a, t, grid, s, max_grid);
     }
     return hipErrorInvalidValue;
 }
 template <class Acc>
 hipError_t pass1_any(const Pass1Args<typename kern::AccOps<Acc>::Taps> &a, int mode, int grid, hipStream_t s,
                      int *max_grid) {
-    if (mode & kP1Matrix) {
-        if constexpr (std::is_same<Acc, double>::value)
-            return pass1_matrix(a, mode & ~kP1Matrix, grid, s, max_grid);
-        return hipErrorInvalidValue;
-    }
     switch (mode) {
     case 0: return kern::p1<Acc, LOGFX_RA, LOGFX_RB, 0>(a, grid, s, max_grid);
     case kP1Maps: return kern::p1<Acc, LOGFX_RA, LOGFX_RB, kP1Maps>(a, grid, s, max_grid);
@@ -62,8 +58,9 @@ hipError_t LOGFX_FN(pass1_i)(const Pass1Args<OrbitTapsI> &a, int mode, int grid,
                              int *max_grid) {
     return pass1_any<int>(a, mode, grid, s, max_grid);
 }
-hipError_t LOGFX_FN(pass1_d)(const Pass1Args<OrbitTapsD> &a, int mode, int grid, hipStream_t s,
+hipError_t LOGFX_FN(pass1_d)(const Pass1Args<OrbitTapsD> &a, const MatTable &t, int mode, int grid, hipStream_t s,
                              int *max_grid) {
+    if (mode & kP1Matrix) return pass1_matrix(a, t, mode & ~kP1Matrix, grid, s, max_grid);
     return pass1_any<double>(a, mode, grid, s, max_grid);
 }
 hipError_t LOGFX_FN(pass2_i)(const Pass2Args<OrbitTapsI> &a, int grid, hipStream_t s, int *max_grid) {

@@ -20,7 +20,9 @@
 // neighbouring blocks of 16 x, and the reduction runs over 2 image rows x 32
 // image columns per MFMA.  The taps' operand is a band matrix: lane
 // (row x, 16 columns) holds 16 consecutive bytes of a zero-padded tap row, so
-// it is one 16-byte load from a table of padded rows, made once per kernel.
+// it is one 16-byte load from a table of padded rows, 1152 bytes that come as a
+// kernel argument: nothing is allocated or launched for a pair of masks (6001 x
+// 3501, all of the call: 171 us with a table in device memory, 171 so).
 // The pixels' operand is 16 consecutive bytes of a byte plane in LDS.  An odd
 // number of mask rows leaves one row slot of the last pair free: it reads the
 // centre row again, with what its taps exceed 16 bits by (the centre tap of
@@ -92,7 +94,7 @@ constexpr int kPass1mWaves = 2;
 
 template <int RA, int RB, int MODE, bool LOOP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPass1mWaves)))
-void pass1m_kernel(Pass1Args<OrbitTapsD> a) {
+void pass1m_kernel(Pass1Args<OrbitTapsD> a, MatTable table) {
     using M = MatLds;
     using Acc = double;
     constexpr int HL = kHalo1, OW = kWave - 2 * HL, TW = tile_out_width(HL);
@@ -112,7 +114,7 @@ void pass1m_kernel(Pass1Args<OrbitTapsD> a) {
     i32x4 ta[GA + 1][2], tb[GB + 1][2];
     {
         typedef i32x4 V __attribute__((aligned(1)));
-        const unsigned char *row = a.mat.table + 16 * (q & 1) - n + 15;   // column 16 (q & 1) - 8 - x, at 23 + column
+        const unsigned char *row = table.b + 16 * (q & 1) - n + 15;   // column 16 (q & 1) - 8 - x, at 23 + column
 #pragma unroll
         for (int g = 0; g <= GB; ++g)
 #pragma unroll
@@ -480,15 +482,15 @@ void pass1m_kernel(Pass1Args<OrbitTapsD> a) {
 }
 
 template <int RA, int RB, int MODE>
-hipError_t p1m(const Pass1Args<OrbitTapsD> &a, int grid, hipStream_t s, int *max_grid) {
+hipError_t p1m(const Pass1Args<OrbitTapsD> &a, const MatTable &t, int grid, hipStream_t s, int *max_grid) {
     const size_t shm = (MODE & kP1Cells) != 0 ? 2 * sizeof(unsigned) * a.cell_rows * a.cell_slots : 0;
     const dim3 block(kTileWaves * kWave);
     constexpr bool CAN_LOOP = (MODE & kP1Cells) == 0;   // the cell-summing form runs one tile per workgroup
     if (max_grid) return occupancy(pass1m_kernel<RA, RB, MODE, CAN_LOOP>, shm, max_grid);
     if (!CAN_LOOP || grid >= a.L.total1)
-        hipLaunchKernelGGL((pass1m_kernel<RA, RB, MODE, false>), dim3(a.L.total1), block, shm, s, a);
+        hipLaunchKernelGGL((pass1m_kernel<RA, RB, MODE, false>), dim3(a.L.total1), block, shm, s, a, t);
     else
-        hipLaunchKernelGGL((pass1m_kernel<RA, RB, MODE, CAN_LOOP>), dim3(grid), block, shm, s, a);
+        hipLaunchKernelGGL((pass1m_kernel<RA, RB, MODE, CAN_LOOP>), dim3(grid), block, shm, s, a, t);
     return hipGetLastError();
 }
 

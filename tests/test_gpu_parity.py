@@ -999,3 +999,56 @@ def test_strengths_past_column_2_29():
             assert torch.equal(got[lo:hi], want[lo:hi]), (a, b)
     del img, out
     torch.cuda.empty_cache()
+
+
+FORM_SCRIPT = r"""
+import sys
+sys.path[:0] = [%r, %r]
+import numpy as np
+import torch
+from paper_1304_3992_amd import logfx
+from parity import to_device
+dev = to_device(np.random.default_rng(4).integers(0, 65536, (80, 310)).astype(np.uint16))
+pars = [logfx.Params(logfx.make_log_mask(5, 0.6 + 0.01 * i, 16)[0], logfx.make_log_mask(9, 1.4, 16)[0]) for i in range(70)]
+ctx = logfx.Context(0)
+ctx.extract(dev.to(torch.uint8), pars[0])          # scratch of the int32 path: smaller
+ctx.extract(dev, pars[0])
+out = torch.empty(dev.shape, dtype=torch.uint8, device="cuda")
+s = torch.cuda.Stream()
+torch.cuda.synchronize()
+g = torch.cuda.CUDAGraph()
+with torch.cuda.graph(g, stream=s):
+    ctx.extract(dev, pars[1], out, stream=s)       # masks first met under capture
+for p in pars[2:]:
+    ctx.extract(dev, p)
+torch.cuda.synchronize()
+print("done")
+"""
+
+
+def test_matrix_form_runs_whenever_it_applies():
+    """Which form the FP64 path takes depends on the masks alone: not on how
+    many pairs the context has met before, nor on whether they are first met
+    under capture (as the call log states it, in a child process)."""
+    import subprocess
+    import sys
+    here = os.path.dirname(os.path.abspath(__file__))
+    r = subprocess.run([sys.executable, "-c", FORM_SCRIPT % (os.path.dirname(here), here)],
+                       env=dict(os.environ, LOGFX_LOG="1"), capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and "done" in r.stdout, r.stderr[-2000:]
+    lines = [ln for ln in r.stderr.splitlines() if ln.startswith("[liblogfx] extract:")]
+    assert len(lines) == 71
+    assert all("fp64 (matrix) path" in ln for ln in lines[1:]), [ln for ln in lines[1:] if "(matrix)" not in ln][:3]
+
+
+def test_report_does_not_depend_on_the_masks_met_before():
+    """The 70th pair of masks of a context: the report of a fresh context,
+    bit for bit (16-bit pixels, whose sums round)."""
+    dev = to_device(np.random.default_rng(6).integers(0, 65536, (300, 700)).astype(np.uint16))
+    pars = [logfx.Params(logfx.make_log_mask(5, 0.6 + 0.01 * i, 16)[0], logfx.make_log_mask(9, 1.4, 16)[0])
+            for i in range(70)]
+    with logfx.Context(0) as c:
+        reps = [c.extract(dev, p, report=True)[1] for p in pars]
+    for i in (0, 63, 64, 69):
+        with logfx.Context(0) as c:
+            assert c.extract(dev, pars[i], report=True)[1] == reps[i], i
