@@ -781,13 +781,16 @@ int prepare(logfx_ctx *ctx, int n, const logfx_image *imgs, const logfx_params *
                 : use_matrix(ctx, c.pl) ? 62 : c.rows1;
     if (features) {
         // pass 1 keeps a slot per (cell row, cell column) a tile spans in
-        // LDS beside the tile: lower the strip height where they would not
-        // fit in 64 KiB together (only images of a few hundred pixels with
-        // cells of a pixel or two come near it)
+        // LDS beside the tile (the matrix form: beside its rings and
+        // responses, whichever form runs, so that both take one height):
+        // lower the strip height where they would not fit in 64 KiB
+        // together (only images of a few hundred pixels with cells of a
+        // pixel or two come near it)
+        const size_t mat = c.pl.mat_ok && !c.pl.i32 ? kMatLdsBytes : 0;
         long long slots = 1, crows = 1;
         for (; c.rows1 > 1; --c.rows1) {
             cell_layout(n, imgs, c.pl, c.rows1, slots, crows);
-            if (pass1_lds_bytes(c.rows1, c.pl.rb) + 2 * sizeof(unsigned) * slots * crows <= 65536) break;
+            if (std::max(mat, pass1_lds_bytes(c.rows1, c.pl.rb)) + 2 * sizeof(unsigned) * slots * crows <= 65536) break;
         }
         cell_layout(n, imgs, c.pl, c.rows1, slots, crows);
         c.cell_slots = (int)slots;

@@ -283,5 +283,8 @@ inline size_t lds_bytes(int rows, int halo, int rb) {
 inline size_t pass1_lds_bytes(int rows, int rb) {
     return lds_bytes(rows + 1, kHalo1, rb);
 }
+// LDS of a workgroup of the matrix form, whatever the strip height: rings,
+// responses and the reductions (logfx_pass1m.h asserts it).
+constexpr size_t kMatLdsBytes = 46848;
 
 }  // namespace logfx

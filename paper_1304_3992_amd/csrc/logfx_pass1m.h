@@ -86,6 +86,7 @@ struct MatLds {
     static constexpr int LROW = 64 * 2 * (int)sizeof(double) + 16, LWAVE = 8 * LROW;
     static constexpr int BYTES = RESP + kTileWaves * LWAVE;
     static_assert(RESP % 16 == 0, "aligned responses");
+    static_assert(BYTES + (kTileSums + 2) * kTileWaves * 8 == kMatLdsBytes, "LDS that the host counts on");
 };
 
 // Waves per SIMD that the registers allow (the taps' operands alone take 40,

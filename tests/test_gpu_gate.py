@@ -608,3 +608,48 @@ def test_gate_regions_full_width_band(ctx):
             ref[y * R:(y + 1) * R, x * R:(x + 1) * R] = crop(o["F"], y, x)
     info = compare(out.cpu().numpy(), {**o, "F": ref}, smooth=True)
     print("full-width band:", int(dec.sum()), "of", len(regions), "regions smoothed;", info)
+
+
+CELL_LDS_SCRIPT = r"""
+import sys
+sys.path[:0] = [%r, %r]
+import numpy as np
+import torch
+from oracle import gate as og
+from paper_1304_3992_amd import logfx
+from parity import masks, to_device
+ctx = logfx.Context(0)
+ctx.gate_set_params(og.init(1))
+rng = np.random.default_rng(2)
+params = logfx.Params(*masks()[1], smooth=logfx.SMOOTH_GATE)
+for shape in ((32, 32), (131, 257), (300, 60), (60, 300), (500, 500), (1, 1)):
+    dev = to_device(rng.integers(0, 65536, shape).astype(np.uint16))
+    got = []
+    for form in (1, 0):
+        ctx.set_option(logfx.OPT_PACKED_LOG, form)
+        got.append(ctx.extract(dev, params, report=True))
+    assert torch.equal(got[0][0], got[1][0]), shape
+    for k in ("zc_count", "extracted", "output", "gate_logit", "smoothed"):
+        assert got[0][1][k] == got[1][1][k], (shape, k)
+print("done")
+"""
+
+
+def test_cell_sums_of_small_16_bit_images_fit_in_64_kib():
+    """The strip height of a gated call leaves the matrix form's cell sums
+    (two words a slot, test_cell_layout.py) room in 64 KiB beside the 46848
+    bytes it takes itself; the heights are those of the call log (a child
+    process); the maps and decisions of both forms agree."""
+    import re
+    import subprocess
+    import sys
+    from test_cell_layout import bounds
+    here = os.path.dirname(os.path.abspath(__file__))
+    r = subprocess.run([sys.executable, "-c", CELL_LDS_SCRIPT % (os.path.dirname(here), here)],
+                       env=dict(os.environ, LOGFX_LOG="1"), capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and "done" in r.stdout, r.stderr[-2000:]
+    calls = re.findall(r"extract: 1 image\(s\), first (\d+) x (\d+), fp64.*?\(rows (\d+)/", r.stderr)
+    assert len(calls) == 12
+    for h, w, rows in (map(int, c) for c in calls):
+        slots, crows = bounds(w, h, rows)
+        assert 46848 + 8 * slots * crows <= 65536, (h, w, rows)
