@@ -214,13 +214,15 @@ int logfx_extract(logfx_ctx *ctx, const logfx_image *img, const logfx_params *p,
  * graph capture, tight serving loops, harnesses that forbid allocation.
  * The same pipeline and the same output bytes as logfx_extract; the call
  * allocates nothing, host or device.  Its scratch (per-tile sums and counts
- * of both passes, the image's statistics) is a fixed static array of 4.5
+ * of both passes, the image's statistics) is a fixed static array of 8.5
  * MiB on each device, held until the process ends; pass 2 recomputes the
  * crossing strengths (as LOGFX_OPT_STORE_Z = 0 does) instead of storing
- * them.  The tile heights come from ctx's options; no report, no timing.
+ * them.  The tile heights come from ctx's options (on the FP64 path, until
+ * pass 1's is set, it is logfx_extract's, so that the thresholds are the same
+ * bits); no report, no timing.
  * Limits (LOGFX_EINVAL beyond them, before anything is enqueued): at most
- * 65536 tiles per pass -- with the default 64-row strips about 0.94
- * Gpixel, e.g. 30000 x 30000 -- and no std5_max >= 0, median_cascade,
+ * 65536 tiles per pass at the heights logfx_get_option gives -- with the
+ * default 64 rows about 0.94 Gpixel, e.g. 30000 x 30000 -- and no std5_max >= 0, median_cascade,
  * gate_region, nor LOGFX_SMOOTH_GATE with gate parameters loaded (GATE
  * without parameters runs as ALWAYS).  Every call on a device shares that
  * device's array: calls that overlap in time on one device (other streams,

@@ -622,6 +622,14 @@ bool use_packed(const logfx_ctx *ctx, const Plan &pl) { return pl.pk_ok && ctx->
 // The same of the matrix form, on the FP64 path.
 bool use_matrix(const logfx_ctx *ctx, const Plan &pl) { return pl.mat_ok && !pl.i32 && ctx->pack_log; }
 
+// Pass-1 strip height of the FP64 path where none was asked for.  Its sums of
+// strengths round, strip by strip and tile by tile, in the same order in both
+// forms, so the height follows the masks alone: an image's statistics are the
+// same bits whichever form runs, in a batch and alone, and in
+// logfx_extract_noalloc.  The matrix form works through blocks of 8 rows, the
+// strip's and one above and below it: 62.
+int fp64_rows(const Plan &pl) { return pl.mat_ok ? 62 : 64; }
+
 // ------------------------------------------------------------ one call
 // Tiling of one image in both passes.
 struct ImageTiles {
@@ -768,17 +776,12 @@ int prepare(logfx_ctx *ctx, int n, const logfx_image *imgs, const logfx_params *
     if (rc != LOGFX_OK) return rc;
     c.rows1 = ctx->tiles.rows1;
     c.rows2 = ctx->tiles.rows2;
-    // (The FP64 path, whose sums round, keeps to one height, so that an
-    // image's statistics are the same bits in a batch and alone.  Its matrix
-    // form works through blocks of 8 rows, the strip's and one above and below
-    // it: 62 rows.)
     // Integer path: up to 48 rows, for which five workgroups' LDS fit a CU
     // (8192^2: 196 us with 48 rows, 213 with 64, 199 with 43).  With the
     // gate's cells, whose sums leave the tile at its end, the tallest that
     // four workgroups' allows (32 of 2048^2: 454 with 48, 449 with 61).
     if (!ctx->tiles.set1)
-        c.rows1 = c.pl.i32 ? strip_rows(n, imgs, tile_out_width(kHalo1), features ? 62 : 48, 4, 6, 1.7)
-                : use_matrix(ctx, c.pl) ? 62 : c.rows1;
+        c.rows1 = c.pl.i32 ? strip_rows(n, imgs, tile_out_width(kHalo1), features ? 62 : 48, 4, 6, 1.7) : fp64_rows(c.pl);
     if (features) {
         // pass 1 keeps a slot per (cell row, cell column) a tile spans in
         // LDS beside the tile (the matrix form: beside its rings and
@@ -1590,6 +1593,12 @@ int logfx_extract_noalloc(logfx_ctx *ctx, const logfx_image *img, const logfx_pa
         return set_err(ctx, LOGFX_EINVAL, "a %lld x %lld image needs %d pass-1 and %d pass-2 tiles; the static "
                                           "scratch holds %lld per pass", (long long)img->height,
                        (long long)img->width, t.ntiles1, t.ntiles2, kNoAllocMaxTiles);
+    if (!ctx->tiles.set1 && !c.pl.i32) {
+        // logfx_extract's height, for its statistics: at most twice the tiles
+        c.rows1 = fp64_rows(c.pl);
+        static_assert(kNoAllocMaxTiles1 >= 2 * kNoAllocMaxTiles, "ceil(H / 62) <= 2 ceil(H / 64)");
+        if ((rc = tile_image(ctx, img, c.pl, false, c.rows1, c.rows2, t)) != LOGFX_OK) return rc;
+    }
     DeviceGuard dg(ctx->device);
     if (!dg.ok) return set_err(ctx, LOGFX_EDEVICE, "cannot select device %d", ctx->device);
     if (!ctx->noalloc)

@@ -262,11 +262,12 @@ hipError_t launch_pass2z_d(const Pass2Args<OrbitTapsD> &a, int grid, hipStream_t
 
 // Static scratch of logfx_extract_noalloc (one array per device, in
 // logfx_dispatch.hip): the per-tile sums and counts of both passes and the
-// image's statistics, for at most kNoAllocMaxTiles tiles per pass.
-constexpr long long kNoAllocMaxTiles = 65536;
-constexpr size_t kNoAllocPartialsOff = 0;                                              // u64 [T][kTileSums]
-constexpr size_t kNoAllocCounts1Off = kNoAllocPartialsOff + kNoAllocMaxTiles * kTileSums * 8;       // i64 [T][2]
-constexpr size_t kNoAllocCounts2Off = kNoAllocCounts1Off + kNoAllocMaxTiles * 2 * sizeof(long long); // i32 [T][2]
+// image's statistics, for at most kNoAllocMaxTiles tiles per pass at the
+// heights of the context (kNoAllocMaxTiles1 in pass 1 at the FP64 path's own).
+constexpr long long kNoAllocMaxTiles = 65536, kNoAllocMaxTiles1 = 2 * kNoAllocMaxTiles;
+constexpr size_t kNoAllocPartialsOff = 0;                                              // u64 [T1][kTileSums]
+constexpr size_t kNoAllocCounts1Off = kNoAllocPartialsOff + kNoAllocMaxTiles1 * kTileSums * 8;       // i64 [T1][2]
+constexpr size_t kNoAllocCounts2Off = kNoAllocCounts1Off + kNoAllocMaxTiles1 * 2 * sizeof(long long); // i32 [T][2]
 constexpr size_t kNoAllocStatsOff = kNoAllocCounts2Off + kNoAllocMaxTiles * 2 * sizeof(int);        // DevStats
 constexpr size_t kNoAllocBytes = (kNoAllocStatsOff + sizeof(DevStats) + 255) / 256 * 256;
 // Device address of that array on `device` (which must be the current

@@ -1052,3 +1052,29 @@ def test_report_does_not_depend_on_the_masks_met_before():
     for i in (0, 63, 64, 69):
         with logfx.Context(0) as c:
             assert c.extract(dev, pars[i], report=True)[1] == reps[i], i
+
+
+@pytest.mark.parametrize("h,w", [(64, 500), (131, 257), (613, 1037)])
+def test_fp64_statistics_do_not_depend_on_the_form(ctx, h, w):
+    """16-bit images, whose sums round: the reports of the matrix form and of
+    the vector form are the same bits, at the heights the library takes by
+    itself and at set ones, in a batch, with stored and recomputed strengths
+    and under the gate."""
+    from oracle import gate as og
+    img = np.random.default_rng(h).integers(0, 65536, (h, w)).astype(np.uint16)
+    dev, taps = to_device(img), masks()[1]
+    for rows in (0, 30, 64):
+        for smooth in (logfx.SMOOTH_ALWAYS, logfx.SMOOTH_GATE):
+            got = []
+            for form in (1, 0):
+                for store in (1, 0):
+                    with logfx.Context(0) as c:
+                        c.gate_set_params(og.init(1))
+                        c.set_option(logfx.OPT_PACKED_LOG, form)
+                        c.set_option(logfx.OPT_STORE_Z, store)
+                        if rows:
+                            c.set_option(logfx.OPT_ROWS1, rows)
+                        p = logfx.Params(*taps, smooth=smooth)
+                        got.append(c.extract(dev, p, bits=16, report=True)[1])
+                        got.append(c.extract_batch([dev, dev], p, bits=16, report=True)[1][0])
+            assert all(r == got[0] for r in got), (rows, smooth)

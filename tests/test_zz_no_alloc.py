@@ -87,3 +87,23 @@ def test_noalloc_limits_refused():
         from oracle import gate as og
         ctx.gate_set_params(og.init(0))
         assert _call(lib, ctx, small, p, out, 11) == logfx.EINVAL
+
+
+def test_noalloc_more_tiles_in_pass1_than_at_64_rows():
+    """A 16-bit image of 64 rows has one row of tiles at the 64 rows that the
+    limit counts and two at the FP64 path's own height: 117742 tiles in pass
+    1, past the 65536 of the limit.  Same bytes as logfx_extract."""
+    import torch
+    lib = logfx.load()
+    _, lib_t = masks()
+    params = logfx.Params(*lib_t)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    d = torch.randint(-32768, 32768, (64, 14_600_000), generator=g, device="cuda", dtype=torch.int16)
+    out = torch.full(d.shape, 0xAB, dtype=torch.uint8, device="cuda")
+    with logfx.Context(0) as ctx:
+        ref = ctx.extract(d, params, bits=16)
+        assert _call(lib, ctx, d, params, out, 16) == logfx.OK, logfx.last_error(ctx.ptr)
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
+    del d, out, ref
+    torch.cuda.empty_cache()
