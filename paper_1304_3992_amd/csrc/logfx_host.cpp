@@ -636,14 +636,20 @@ struct ImageTiles {
     int tiles_x1, ntiles1, tiles_x2, ntiles2;
 };
 
+int check_sides(logfx_ctx *ctx, const logfx_image &img) {
+    if (img.height >= (1LL << 30) || img.width >= (1LL << 30))
+        return set_err(ctx, LOGFX_EUNSUPPORTED, "image sides must be below 2^30");
+    return LOGFX_OK;
+}
+
 int tile_image(logfx_ctx *ctx, const logfx_image *img, const Plan &pl, bool storez, int rows1, int rows2,
                ImageTiles &t) {
     TileCfg c;
     c.rows1 = rows1;
     c.rows2 = rows2;
     const long long H = img->height, W = img->width;
-    if (H >= (1LL << 30) || W >= (1LL << 30))
-        return set_err(ctx, LOGFX_EUNSUPPORTED, "image sides must be below 2^30");
+    int rc;
+    if ((rc = check_sides(ctx, *img)) != LOGFX_OK) return rc;
     const long long tw1 = tile_out_width(kHalo1);
     const long long tw2 = tile_out_width(storez ? (pl.std5 ? kHalo2Z5 : kHalo2Z) : kHalo2);
     const long long tx1 = (W + tw1 - 1) / tw1, ty1 = (H + c.rows1 - 1) / c.rows1;
@@ -774,6 +780,20 @@ int prepare(logfx_ctx *ctx, int n, const logfx_image *imgs, const logfx_params *
     if (n < 1 || !imgs) return set_err(ctx, LOGFX_EINVAL, "no images");
     int rc = check_all(ctx, &imgs[0], p, c.pl);
     if (rc != LOGFX_OK) return rc;
+    // every image, before any of their sizes is used
+    const int bits0 = imgs[0].bits == 0 ? (imgs[0].dtype == LOGFX_U8 ? 8 : 16) : imgs[0].bits;
+    for (int i = 0; i < n; ++i) {
+        if (i > 0) {
+            Plan tmp;
+            if ((rc = check_all(ctx, &imgs[i], p, tmp)) != LOGFX_OK) return rc;
+            const int bi = imgs[i].bits == 0 ? (imgs[i].dtype == LOGFX_U8 ? 8 : 16) : imgs[i].bits;
+            if (imgs[i].dtype != imgs[0].dtype || bi != bits0)
+                return set_err(ctx, LOGFX_EINVAL, "image %d: all images of a batch must share "
+                                                  "dtype and bits", i);
+        }
+        if ((rc = check_sides(ctx, imgs[i])) != LOGFX_OK) return rc;
+        if (need_out && (!outs || !outs[i])) return set_err(ctx, LOGFX_EINVAL, "output %d is NULL", i);
+    }
     c.rows1 = ctx->tiles.rows1;
     c.rows2 = ctx->tiles.rows2;
     // Integer path: up to 48 rows, for which five workgroups' LDS fit a CU
@@ -830,20 +850,10 @@ int prepare(logfx_ctx *ctx, int n, const logfx_image *imgs, const logfx_params *
     }
     if (!ctx->tiles.set2 && c.storez)
         c.rows2 = strip_rows(n, imgs, tile_out_width(c.pl.std5 ? kHalo2Z5 : kHalo2Z), 64, 8, 4, 1.5);
-    const int bits0 = imgs[0].bits == 0 ? (imgs[0].dtype == LOGFX_U8 ? 8 : 16) : imgs[0].bits;
     c.n = n;
     c.tiles.resize(n);
     long long t1 = 0, t2 = 0;
     for (int i = 0; i < n; ++i) {
-        if (i > 0) {
-            Plan tmp;
-            if ((rc = check_all(ctx, &imgs[i], p, tmp)) != LOGFX_OK) return rc;
-            const int bi = imgs[i].bits == 0 ? (imgs[i].dtype == LOGFX_U8 ? 8 : 16) : imgs[i].bits;
-            if (imgs[i].dtype != imgs[0].dtype || bi != bits0)
-                return set_err(ctx, LOGFX_EINVAL, "image %d: all images of a batch must share "
-                                                  "dtype and bits", i);
-        }
-        if (need_out && (!outs || !outs[i])) return set_err(ctx, LOGFX_EINVAL, "output %d is NULL", i);
         if ((rc = tile_image(ctx, &imgs[i], c.pl, c.storez, c.rows1, c.rows2, c.tiles[i])) != LOGFX_OK) return rc;
         t1 += c.tiles[i].ntiles1;
         t2 += c.tiles[i].ntiles2;
@@ -1261,7 +1271,7 @@ int run(logfx_ctx *ctx, int n, const logfx_image *imgs, const logfx_params *p, u
     if (!dg.ok) return set_err(ctx, LOGFX_EDEVICE, "cannot select device %d", ctx->device);
     hipStream_t s = (hipStream_t)stream;
     Call c;
-    const bool gated = !maps && p->smooth == LOGFX_SMOOTH_GATE && ctx->gate.loaded;
+    const bool gated = !maps && p && p->smooth == LOGFX_SMOOTH_GATE && ctx->gate.loaded;
     int rc = prepare(ctx, n, imgs, p, outs, !maps, gated, c, s);
     if (rc != LOGFX_OK) return rc;
     if (gated && (rc = check_cells(ctx, n, imgs, c.pl)) != LOGFX_OK) return rc;

@@ -216,3 +216,34 @@ def test_alternating_batches_queued_without_sync(ctx, graph):
                 assert torch.equal(g, r), k
     finally:
         ctx.set_option(logfx.OPT_GRAPH, 1)
+
+
+@pytest.mark.parametrize("field,value,rc", [("width", 0, logfx.EINVAL), ("height", 0, logfx.EINVAL),
+                                            ("height", -5, logfx.EINVAL), ("width", 1 << 40, logfx.EINVAL),
+                                            ("height", 1 << 62, logfx.EUNSUPPORTED), ("data", None, logfx.EINVAL)])
+def test_invalid_images_of_a_gated_batch_are_refused(field, value, rc):
+    """Every image is checked before its sizes are used (the gate's cell
+    layout divides by them), and the parameters before they are read."""
+    import ctypes
+    import torch
+    from oracle import gate as og
+    lib = logfx.load()
+    dev = to_device(scenes.panchromatic(130, 140, 3, n_rect=5, noise_sigma=2.0))
+    params = logfx.Params(*masks()[1], smooth=logfx.SMOOTH_GATE)
+    outs = [torch.empty_like(dev) for _ in range(2)]
+    descs = (logfx.logfx_image * 2)(logfx.image(dev), logfx.image(dev))
+    ptrs = (ctypes.c_void_p * 2)(*(o.data_ptr() for o in outs))
+    with logfx.Context(0) as c:
+        c.gate_set_params(og.init(2))
+
+        def call(p):
+            return lib.logfx_extract_batch(c.ptr, 2, descs, p, ctypes.cast(ptrs, ctypes.POINTER(ctypes.c_void_p)),
+                                           None, None)
+
+        want = [o.clone() for o in c.extract_batch([dev, dev], params)]
+        setattr(descs[1], field, value)
+        assert call(ctypes.byref(params.c)) == rc
+        assert call(None) == logfx.EINVAL
+        got = c.extract_batch([dev, dev], params)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
