@@ -262,10 +262,13 @@ int logfx_extract_batch(logfx_ctx *ctx, int32_t n, const logfx_image *imgs, cons
 
 /* Context options (logfx_set_option / logfx_get_option). */
 enum {
-    LOGFX_OPT_ROWS1 = 1,      /* output rows per wave strip in pass 1 (1..1024, default 64; until it is set,
-                                 by this option, logfx_tune or LOGFX_TILE, calls on fewer than 2^25
-                                 pixels take lower strips where those fill the device better) */
-    LOGFX_OPT_ROWS2 = 2,      /* the same for pass 2 (default 64) */
+    LOGFX_OPT_ROWS1 = 1,      /* output rows per wave strip in pass 1 (1..1024) of every call.  Until it is
+                                 set, here or by LOGFX_TILE (or tuned), calls take their own: on the
+                                 integer path at most 48, with the gate's features 62, and fewer on
+                                 less than 2^25 pixels where that fills the device better; on the FP64
+                                 path 62 or 64, by the masks.  Reads 64 until set or tuned. */
+    LOGFX_OPT_ROWS2 = 2,      /* the same for pass 2: at most 64 rows, fewer on less than 2^25 pixels
+                                 (64 where the strengths are recomputed) */
     LOGFX_OPT_PERSISTENT = 3, /* batches: 1 = persistent launch, 0 = one workgroup per tile (default) */
     LOGFX_OPT_GRAPH = 4,      /* batches: 1 = replay a captured hipGraph (default), 0 = direct launches */
     LOGFX_OPT_STORE_Z = 5,    /* 1 (default) = pass 1 stores the crossing strengths of every pixel in
@@ -287,15 +290,20 @@ int logfx_get_option(logfx_ctx *ctx, int32_t option, int64_t *value);
 /* Autotuner (the launch-parameter sweep of Table 4, Sec. 6.2.3, made
  * automatic).  Runs the given call (one image, or a batch when n > 1) with
  * each candidate strip height for pass 1 and pass 2 (32, 40, 48, 56, 64, 96
- * rows, as far as they fit in LDS) and, for batches, with and without the
- * persistent launch, `reps` timed repetitions each, in two round-robin
- * rounds (each candidate keeps its faster round), and keeps the fastest in
- * the context (LOGFX_OPT_ROWS1/ROWS2/PERSISTENT).  The outputs are
- * written as by the call itself.  cache_path (nullable): a text file of
- * JSON lines keyed by device architecture, arithmetic path, mask radii,
- * pixel type, smoothing and batch/single; an entry found there is applied
- * without measuring, a new result is appended.  res (nullable) receives the
- * choice.  cache_path NULL: the file LOGFX_TUNE_CACHE names, if set. */
+ * rows, as far as they fit in LDS, and the heights calls take by themselves)
+ * and, for batches, with and without the persistent launch, `reps` timed
+ * repetitions each, in two round-robin rounds (each candidate keeps its faster
+ * round), and keeps the fastest in the context.  Heights hold for calls of the
+ * same arithmetic and of about the same size: floor(log2) of their pixels is
+ * equal, or both have 2^25 or more; others, and all where none of the list is
+ * faster, go on taking their own.  It replaces heights set by LOGFX_OPT_ROWS1
+ * and ROWS2, which then give what is in `res`: the fastest of the list, or the
+ * height calls take by themselves (the tallest where that goes by the size).
+ * The outputs are written as by the call itself.  cache_path (nullable): a text
+ * file of JSON lines keyed by device architecture, arithmetic path, mask radii,
+ * pixel type, smoothing, batch/single and that size; an entry found there is
+ * applied without measuring, a new result is appended.  res (nullable) receives
+ * the choice.  cache_path NULL: the file LOGFX_TUNE_CACHE names, if set. */
 typedef struct {
     int32_t rows1, rows2, persistent;
     int32_t from_cache;   /* 1 if taken from the cache file */

@@ -30,11 +30,13 @@ namespace {
 thread_local std::string g_thread_error;
 
 // Output rows per wave strip of each pass (tiles are kTileWaves strips wide).
-// Heights that were not asked for are upper bounds (strip_rows).
 struct TileCfg {
     int rows1 = 64;  // pass 1
     int rows2 = 64;  // pass 2
-    bool set1 = false, set2 = false;   // by an option, the tuner or the environment
+    bool set1 = false, set2 = false;       // by an option or the environment: every call takes them
+    bool tuned1 = false, tuned2 = false;   // by the tuner: calls of this class do (call_class)
+    int tuned_class = -1;
+    // other calls take the heights prepare works out
 };
 
 // LOGFX_TILE="rows1,rows2" overrides the defaults (used by the tuner and
@@ -727,6 +729,24 @@ void cell_layout(int n, const logfx_image *imgs, const Plan &pl, int rows, long 
     }
 }
 
+// The tallest strips that calls take by themselves (pass 1 of the integer
+// path, the same with the gate's cells, pass 2), and the pixels from which on
+// they take these.
+constexpr int kTall1 = 48, kTallCells = 62, kTall2 = 64;
+constexpr long long kTallPixels = 1LL << 25;
+
+long long call_pixels(int n, const logfx_image *imgs) {
+    long long px = 0;
+    for (int i = 0; i < n; ++i) px += (long long)imgs[i].height * imgs[i].width;
+    return px;
+}
+
+// Calls that tuned heights hold for: of the tuned call's path, and within a
+// factor of two of its size, which is what the best height depends on.
+int call_class(const Plan &pl, int n, const logfx_image *imgs) {
+    return 2 * std::ilogb((double)std::min(call_pixels(n, imgs), kTallPixels)) + pl.i32;
+}
+
 // Strip height for tiles `tw` columns wide, where none was asked for.  A
 // workgroup takes about rows + halo row times, alone on its CU each half as
 // long again (`alone`) as with others to fill its waits, so a call takes
@@ -738,10 +758,7 @@ void cell_layout(int n, const logfx_image *imgs, const Plan &pl, int rows, long 
 // From 2^25 pixels on, the tallest is within 4 % of the best.
 int strip_rows(int n, const logfx_image *imgs, long long tw, int most, int step, int halo, double alone) {
     constexpr int kCus = 256;
-    if (n > 64) return most;
-    long long px = 0;
-    for (int i = 0; i < n; ++i) px += (long long)imgs[i].height * imgs[i].width;
-    if (px >= (1LL << 25)) return most;
+    if (n > 64 || call_pixels(n, imgs) >= kTallPixels) return most;
     int best = most;
     double cost = 1e300;
     for (int r = most; r >= std::min(most, 6); r -= step) {
@@ -794,14 +811,16 @@ int prepare(logfx_ctx *ctx, int n, const logfx_image *imgs, const logfx_params *
         if ((rc = check_sides(ctx, imgs[i])) != LOGFX_OK) return rc;
         if (need_out && (!outs || !outs[i])) return set_err(ctx, LOGFX_EINVAL, "output %d is NULL", i);
     }
-    c.rows1 = ctx->tiles.rows1;
-    c.rows2 = ctx->tiles.rows2;
     // Integer path: up to 48 rows, for which five workgroups' LDS fit a CU
     // (8192^2: 196 us with 48 rows, 213 with 64, 199 with 43).  With the
     // gate's cells, whose sums leave the tile at its end, the tallest that
     // four workgroups' allows (32 of 2048^2: 454 with 48, 449 with 61).
-    if (!ctx->tiles.set1)
-        c.rows1 = c.pl.i32 ? strip_rows(n, imgs, tile_out_width(kHalo1), features ? 62 : 48, 4, 6, 1.7) : fp64_rows(c.pl);
+    const bool tuned = call_class(c.pl, n, imgs) == ctx->tiles.tuned_class;
+    const bool keep1 = ctx->tiles.set1 || (ctx->tiles.tuned1 && tuned);
+    const bool keep2 = ctx->tiles.set2 || (ctx->tiles.tuned2 && tuned);
+    c.rows1 = keep1      ? ctx->tiles.rows1
+              : c.pl.i32 ? strip_rows(n, imgs, tile_out_width(kHalo1), features ? kTallCells : kTall1, 4, 6, 1.7)
+                         : fp64_rows(c.pl);
     if (features) {
         // pass 1 keeps a slot per (cell row, cell column) a tile spans in
         // LDS beside the tile (the matrix form: beside its rings and
@@ -828,8 +847,7 @@ int prepare(logfx_ctx *ctx, int n, const logfx_image *imgs, const logfx_params *
     c.storez = false;
     const bool need_z = c.pl.std5 || c.pl.ncas > 0 || c.pl.region > 0;
     if (need_out && (ctx->store_z || need_z)) {
-        long long &px = c.px;
-        for (int i = 0; i < n; ++i) px += (long long)imgs[i].height * imgs[i].width;
+        const long long px = c.px = call_pixels(n, imgs);
         c.storez = ensure_zmap(ctx, px, c.pl.i32);
         if (!c.storez && need_z)
             return set_err(ctx, LOGFX_ENOMEM, "the 5x5 first deviation stage, the median cascade and the "
@@ -848,8 +866,9 @@ int prepare(logfx_ctx *ctx, int n, const logfx_image *imgs, const logfx_params *
             ctx->ccap = px;
         }
     }
-    if (!ctx->tiles.set2 && c.storez)
-        c.rows2 = strip_rows(n, imgs, tile_out_width(c.pl.std5 ? kHalo2Z5 : kHalo2Z), 64, 8, 4, 1.5);
+    c.rows2 = keep2      ? ctx->tiles.rows2
+              : c.storez ? strip_rows(n, imgs, tile_out_width(c.pl.std5 ? kHalo2Z5 : kHalo2Z), kTall2, 8, 4, 1.5)
+                         : kTall2;
     c.n = n;
     c.tiles.resize(n);
     long long t1 = 0, t2 = 0;
@@ -1350,8 +1369,8 @@ int gate_batch_args(logfx_ctx *ctx, int B, const uint16_t *feats) {
 
 // ------------------------------------------------------------ autotuner
 // Key of a tuned configuration: device architecture, arithmetic path, mask
-// radii, pixel type, smoothing and whether the call is a batch.
-std::string tune_key(logfx_ctx *ctx, const Call &c, const logfx_params *p, const logfx_image *img0) {
+// radii, pixel type, smoothing, whether the call is a batch and its size.
+std::string tune_key(logfx_ctx *ctx, const Call &c, const logfx_params *p, const logfx_image *imgs) {
     hipDeviceProp_t prop;
     std::string arch = "unknown";
     if (hipGetDeviceProperties(&prop, ctx->device) == hipSuccess) {
@@ -1362,40 +1381,50 @@ std::string tune_key(logfx_ctx *ctx, const Call &c, const logfx_params *p, const
     std::ostringstream k;
     k << arch << "|" << (!c.pl.i32 ? "fp64" : use_packed(ctx, c.pl) ? "int32pk" : "int32")
       << "|r" << c.pl.ra << c.pl.rb
-      << "|" << (img0->dtype == LOGFX_U8 ? "u8" : "u16") << "|med"
+      << "|" << (imgs[0].dtype == LOGFX_U8 ? "u8" : "u16") << "|med"
       << (p->smooth != LOGFX_SMOOTH_NEVER ? p->median_size : 0) << (p->smooth == LOGFX_SMOOTH_GATE ? "g" : "")
-      << "|" << (c.n > 1 ? "batch" : "single") << (c.pl.std5 ? "|s5" : "");
+      << "|" << (c.n > 1 ? "batch" : "single") << (c.pl.std5 ? "|s5" : "") << "|px" << call_class(c.pl, c.n, imgs) / 2;
     for (int i = 0; i < c.pl.ncas; ++i) k << (i == 0 ? "|c" : "") << c.pl.cas[i];
     return k.str();
 }
 
 // The cache is a text file of JSON objects, one per line:
-// {"key": "...", "rows1": R1, "rows2": R2, "persistent": P, "ms": T}
-bool cache_lookup(const char *path, const std::string &key, logfx_tune_result &r) {
+// {"key": "...", "rows1": R1, "rows2": R2, "persistent": P, "ms": T, "auto1": A1, "auto2": A2}
+// where A = 1 leaves the pass the heights that calls take by themselves.
+struct Tuned {
+    logfx_tune_result r;
+    int auto1, auto2;
+};
+bool cache_lookup(const char *path, const std::string &key, Tuned &t) {
     std::ifstream f(path);
     std::string line;
     bool found = false;
     while (std::getline(f, line)) {
         const std::string tag = "\"key\": \"" + key + "\"";
         if (line.find(tag) == std::string::npos) continue;
-        int r1, r2, pe;
+        int r1, r2, pe, a1, a2;
         double ms;
         const size_t at = line.find("\"rows1\"");
         if (at == std::string::npos) continue;
-        if (std::sscanf(line.c_str() + at, "\"rows1\": %d, \"rows2\": %d, \"persistent\": %d, \"ms\": %lf",
-                        &r1, &r2, &pe, &ms) == 4) {
-            r.rows1 = r1, r.rows2 = r2, r.persistent = pe, r.ms = ms;
+        if (std::sscanf(line.c_str() + at,
+                        "\"rows1\": %d, \"rows2\": %d, \"persistent\": %d, \"ms\": %lf, \"auto1\": %d, \"auto2\": %d",
+                        &r1, &r2, &pe, &ms, &a1, &a2) == 6 &&
+            r1 >= 1 && r1 <= 1024 && r2 >= 1 && r2 <= 1024) {
+            t.r.rows1 = r1, t.r.rows2 = r2, t.r.persistent = pe, t.r.ms = ms;
+            t.auto1 = a1, t.auto2 = a2;
             found = true;   // the last entry for a key wins
         }
     }
     return found;
 }
 
-void cache_store(const char *path, const std::string &key, const logfx_tune_result &r) {
+void cache_store(const char *path, const std::string &key, const Tuned &t) {
     std::ofstream f(path, std::ios::app);
     char buf[512];
-    std::snprintf(buf, sizeof buf, "{\"key\": \"%s\", \"rows1\": %d, \"rows2\": %d, \"persistent\": %d, \"ms\": %.6f}\n",
-                  key.c_str(), r.rows1, r.rows2, r.persistent, r.ms);
+    std::snprintf(buf, sizeof buf,
+                  "{\"key\": \"%s\", \"rows1\": %d, \"rows2\": %d, \"persistent\": %d, \"ms\": %.6f, "
+                  "\"auto1\": %d, \"auto2\": %d}\n",
+                  key.c_str(), t.r.rows1, t.r.rows2, t.r.persistent, t.r.ms, t.auto1, t.auto2);
     f << buf;
 }
 
@@ -1603,10 +1632,10 @@ int logfx_extract_noalloc(logfx_ctx *ctx, const logfx_image *img, const logfx_pa
         return set_err(ctx, LOGFX_EINVAL, "a %lld x %lld image needs %d pass-1 and %d pass-2 tiles; the static "
                                           "scratch holds %lld per pass", (long long)img->height,
                        (long long)img->width, t.ntiles1, t.ntiles2, kNoAllocMaxTiles);
-    if (!ctx->tiles.set1 && !c.pl.i32) {
+    if (!c.pl.i32 && !ctx->tiles.set1 && !(ctx->tiles.tuned1 && call_class(c.pl, 1, img) == ctx->tiles.tuned_class)) {
         // logfx_extract's height, for its statistics: at most twice the tiles
         c.rows1 = fp64_rows(c.pl);
-        static_assert(kNoAllocMaxTiles1 >= 2 * kNoAllocMaxTiles, "ceil(H / 62) <= 2 ceil(H / 64)");
+        static_assert(kNoAllocMaxTiles1 >= 2 * kNoAllocMaxTiles, "ceil(H / 62) <= 2 ceil(H / 96)");
         if ((rc = tile_image(ctx, img, c.pl, false, c.rows1, c.rows2, t)) != LOGFX_OK) return rc;
     }
     DeviceGuard dg(ctx->device);
@@ -1924,20 +1953,30 @@ int logfx_tune(logfx_ctx *ctx, int32_t n, const logfx_image *imgs, const logfx_p
     hipStream_t s = (hipStream_t)stream;
     DeviceGuard dg(ctx->device);
     Call c;
-    int rc = prepare(ctx, n, imgs, p, outs, true, p && p->smooth == LOGFX_SMOOTH_GATE && ctx->gate.loaded, c, s);
+    const TileCfg saved = ctx->tiles;
+    const bool gated = p && p->smooth == LOGFX_SMOOTH_GATE && ctx->gate.loaded;
+    ctx->tiles = TileCfg();   // c takes the heights that calls take by themselves
+    int rc = prepare(ctx, n, imgs, p, outs, true, gated, c, s);
+    ctx->tiles = saved;
     if (rc != LOGFX_OK) return rc;
-    const std::string key = tune_key(ctx, c, p, &imgs[0]);
-    logfx_tune_result best;
+    const std::string key = tune_key(ctx, c, p, imgs);
+    Tuned best;
     std::memset(&best, 0, sizeof best);
     if (!cache_path) cache_path = std::getenv("LOGFX_TUNE_CACHE");   // may stay NULL
     if (cache_path && !*cache_path) cache_path = nullptr;
+    // the heights `t` leaves in force
+    auto chosen = [&](const Tuned &t) {
+        TileCfg g;
+        g.rows1 = t.r.rows1, g.rows2 = t.r.rows2;
+        g.tuned1 = !t.auto1, g.tuned2 = !t.auto2;
+        g.tuned_class = call_class(c.pl, n, imgs);
+        return g;
+    };
     if (cache_path && cache_lookup(cache_path, key, best)) {
-        best.from_cache = 1;
+        best.r.from_cache = 1;
     } else {
-        const TileCfg saved = ctx->tiles;
         const bool saved_p = ctx->persistent, saved_g = ctx->graph, saved_t = ctx->timing;
         ctx->graph = false;   // direct launches, so that each kernel is timed on its own
-        ctx->tiles.set1 = ctx->tiles.set2 = true;
         const int cand[] = {32, 40, 48, 56, 64, 96};
         constexpr int ncand = sizeof cand / sizeof cand[0];
         // the candidates are timed round-robin, twice, and each keeps its
@@ -1955,27 +1994,38 @@ int logfx_tune(logfx_ctx *ctx, int32_t n, const logfx_image *imgs, const logfx_p
             int64_t calls;
             return logfx_timing_read(ctx, ms, &calls);
         };
-        double t1[ncand], t2[ncand];
-        for (int i = 0; i < ncand; ++i) t1[i] = t2[i] = 1e300;
+        // candidate ncand: the heights that calls take by themselves
+        double t1[ncand + 1], t2[ncand + 1];
+        for (int i = 0; i <= ncand; ++i) t1[i] = t2[i] = 1e300;
         for (int round = 0; round < kRounds && rc == LOGFX_OK; ++round)
-            for (int i = 0; i < ncand; ++i) {
-                const int rows = cand[i];
-                if (pass1_lds_bytes(rows, c.pl.rb) > 65536 && lds_bytes(rows, kHalo2, c.pl.rb) > 65536) continue;
-                ctx->tiles.rows1 = pass1_lds_bytes(rows, c.pl.rb) <= 65536 ? rows : saved.rows1;
-                ctx->tiles.rows2 = lds_bytes(rows, kHalo2, c.pl.rb) <= 65536 ? rows : saved.rows2;
+            for (int i = 0; i <= ncand; ++i) {
+                TileCfg g;
+                bool use1 = true, use2 = true;
+                if (i < ncand) {
+                    g.set1 = use1 = pass1_lds_bytes(cand[i], c.pl.rb) <= 65536;
+                    g.set2 = use2 = lds_bytes(cand[i], kHalo2, c.pl.rb) <= 65536;
+                    if (!use1 && !use2) continue;
+                    if (use1) g.rows1 = cand[i];
+                    if (use2) g.rows2 = cand[i];
+                }
+                ctx->tiles = g;
                 double ms[4];
                 if ((rc = measure(ms)) != LOGFX_OK) break;
-                if (ctx->tiles.rows1 == rows) t1[i] = std::min(t1[i], ms[0]);
-                if (ctx->tiles.rows2 == rows) t2[i] = std::min(t2[i], ms[2]);
+                if (use1) t1[i] = std::min(t1[i], ms[0]);
+                if (use2) t2[i] = std::min(t2[i], ms[2]);
             }
-        int r1 = saved.rows1, r2 = saved.rows2;
-        double best1 = 1e300, best2 = 1e300;
+        // reported where these win: their height, or the tallest of those
+        // that go by the size
+        const bool tall = call_pixels(n, imgs) >= kTallPixels;
+        best.auto1 = best.auto2 = 1;
+        best.r.rows1 = !c.pl.i32 || tall ? c.rows1 : gated ? kTallCells : kTall1;
+        best.r.rows2 = !c.storez || tall ? c.rows2 : kTall2;
+        double best1 = t1[ncand], best2 = t2[ncand];
         for (int i = 0; i < ncand; ++i) {
-            if (t1[i] < best1) best1 = t1[i], r1 = cand[i];
-            if (t2[i] < best2) best2 = t2[i], r2 = cand[i];
+            if (t1[i] < best1) best1 = t1[i], best.r.rows1 = cand[i], best.auto1 = 0;
+            if (t2[i] < best2) best2 = t2[i], best.r.rows2 = cand[i], best.auto2 = 0;
         }
-        ctx->tiles.rows1 = r1;
-        ctx->tiles.rows2 = r2;
+        ctx->tiles = chosen(best);
         int pe = 0;
         double bestms = 0.0;
         if (rc == LOGFX_OK) {
@@ -1999,15 +2049,13 @@ int logfx_tune(logfx_ctx *ctx, int32_t n, const logfx_image *imgs, const logfx_p
             ctx->tiles = saved;
             return rc;
         }
-        best.rows1 = r1, best.rows2 = r2, best.persistent = pe, best.ms = bestms / reps;
-        best.from_cache = 0;
+        best.r.persistent = pe, best.r.ms = bestms / reps;
+        best.r.from_cache = 0;
         if (cache_path) cache_store(cache_path, key, best);
     }
-    ctx->tiles.rows1 = best.rows1;
-    ctx->tiles.rows2 = best.rows2;
-    ctx->tiles.set1 = ctx->tiles.set2 = true;
-    ctx->persistent = best.persistent != 0;
-    if (res) *res = best;
+    ctx->tiles = chosen(best);
+    ctx->persistent = best.r.persistent != 0;
+    if (res) *res = best.r;
     return LOGFX_OK;
 }
 
