@@ -1,7 +1,8 @@
 // Bit-sliced logic of the binary hybrid median (Sec. 3.4).  Every bit of a
 // word is one pixel, so one logic operation treats a whole word of pixels.
 // Plain C++ with no GPU types, so that a host test can check the logic
-// against the median's definition on every input pattern.
+// against the median's definition on every input pattern; for the same reason
+// the rounding of exact sums of squares stands here.
 #pragma once
 
 #if defined(__HIP__)
@@ -12,6 +13,15 @@
 
 namespace logfx {
 namespace kern {
+
+// low + 2^32 high as a double, for sums below 2^96.  How the total is split
+// into the two words depends on the tiling (low sums one 32-bit word per lane
+// and strip, past 2^53 from about 100 Mpixel on), so low's carry goes to high
+// first: the result depends on the total alone.  Rounded at most twice.
+LOGFX_HD inline double sum_of_words(unsigned long long low, unsigned long long high) {
+    high += low >> 32;
+    return __builtin_fma((double)high, 4294967296.0, (double)(low & 0xFFFFFFFFull));
+}
 
 // Full adder: a + b + c = s + 2 cy.
 template <class T>

@@ -930,12 +930,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPass1Waves
 
 // ------------------------------------------------------------- statistics
 // The four sums as doubles from the words of exact sums: sum Z_j rounded
-// once, sum Z_j^2 = low + 2^32 high rounded at most twice.
+// once, sum Z_j^2 = low + 2^32 high (sum_of_words).
 __device__ inline void exact_sums(const unsigned long long (&w)[kTileSums], double (&s)[4]) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         s[j] = (double)w[j];
-        s[2 + j] = __fma_rn((double)w[4 + j], 4294967296.0, (double)w[2 + j]);
+        s[2 + j] = sum_of_words(w[2 + j], w[4 + j]);
     }
 }
 // sigma_j, T_j and 72 T_j^2 of an image from the sums over its pixels:
