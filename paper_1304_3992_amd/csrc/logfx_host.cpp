@@ -755,7 +755,10 @@ int call_class(const Plan &pl, int n, const logfx_image *imgs) {
 // Pass 1, measured: 512^2 34 us with 64 rows, 12 with 8; 2000^2 45 and 29
 // with 24; 4000^2 68 with 61 and 64 with 32; pass 2: 512^2 14.7 and 8.4
 // with 8, 2000^2 19.4 and 14.0 with 24, 6000^2 57 with 64 and 83 with 8.
-// From 2^25 pixels on, the tallest is within 4 % of the best.
+// From 2^25 pixels on, the tallest is within 4 % of the best.  Batches of more
+// than 64 images take it too: below that size they wait for the host's work on
+// each image (100 of 131 x 257, whole call, 264 us with 64 rows and 261 with
+// 12; 100 of 500 x 500, 268 and 286).
 int strip_rows(int n, const logfx_image *imgs, long long tw, int most, int step, int halo, double alone) {
     constexpr int kCus = 256;
     if (n > 64 || call_pixels(n, imgs) >= kTallPixels) return most;
@@ -770,11 +773,11 @@ int strip_rows(int n, const logfx_image *imgs, long long tw, int most, int step,
     return best;
 }
 
+// Words of the code plane, rounded up so that the plane of low bits after it
+// is aligned.
+long long zmap_words(long long px) { return (px + 63) / 64 * 64; }
 // Device memory for the strengths of `px` pixels (ZMap); false if it cannot
 // be had (the call then recomputes the strengths in pass 2).
-// zmap_words: words of the code plane, rounded up so that the plane of low
-// bits after it is aligned.
-long long zmap_words(long long px) { return (px + 63) / 64 * 64; }
 bool ensure_zmap(logfx_ctx *ctx, long long px, bool i32) {
     const long long bytes = zmap_words(px) * (i32 ? 8 : 16);
     if (bytes <= ctx->zcap) return true;

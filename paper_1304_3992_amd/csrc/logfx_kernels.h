@@ -41,10 +41,6 @@ namespace logfx {
 namespace kern {
 
 // ----------------------------------------------------------------- helpers
-__device__ inline long long clampll(long long v, long long lo, long long hi) {
-    return v < lo ? lo : (v > hi ? hi : v);
-}
-
 // Values of the lanes to the left (column x - 1) and right (x + 1), by DPP
 // wave shifts on the vector ALU.  Lanes 0 and 63 receive 0 (they are halo
 // lanes whose results are never used; no copy of the source is needed).
@@ -664,8 +660,10 @@ __device__ inline void restore_strengths(const ZMap &m, unsigned hi, uint2 lo, d
 // 77 by the counters; its LDS reads, at any pixel alignment, keep the LDS
 // busy for most of the same time.  8192^2: 233 us with 77 + 20 instructions
 // and strips of 64 rows, 196 with these and 48.
-// Occupancy: the integer path is held to 128 VGPRs (4 waves per SIMD, the
-// LDS limit); the FP64 path keeps its registers.  Variants that need more
+// Occupancy: the integer path is held to 128 VGPRs (4 waves per SIMD); its
+// packed form takes 90 and runs at 5, the workgroups whose 48 rows fit the
+// LDS, with the gate's cells 106 and 4 (masks of 5 and 9).  The FP64 path
+// keeps its registers.  Variants that need more
 // run at fewer waves rather than spill.  No kernel here may spill vector
 // registers (the build refuses one that does): the crossing test reads its
 // neighbours from the adjacent lanes (DPP), and a spill reload that the

@@ -89,8 +89,9 @@ struct MatLds {
     static_assert(BYTES + (kTileSums + 2) * kTileWaves * 8 == kMatLdsBytes, "LDS that the host counts on");
 };
 
-// Waves per SIMD that the registers allow (the taps' operands alone take 40,
-// the sums of a block 24).
+// Waves per SIMD the registers have to allow (the taps' operands alone take
+// 40, the sums of a block 24).  With masks of 5 and 9 the form that stores the
+// strengths takes 159 and runs at 3, with the gate's cells 169 and 2.
 constexpr int kPass1mWaves = 2;
 
 template <int RA, int RB, int MODE, bool LOOP>

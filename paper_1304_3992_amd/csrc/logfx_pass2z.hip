@@ -181,8 +181,6 @@ template <class LO> struct ZFull {
 };
 template <class Acc> using LowBits = typename std::conditional<std::is_same<Acc, int>::value, unsigned, uint2>::type;
 
-template <int MED, bool LOOP, bool S5> constexpr int kPass2zWaves = S5 ? 3 : MED < 0 || LOOP ? 4 : 5;
-
 // The finalize of a single image of few pass-1 tiles, by every workgroup for
 // itself, with the finalize kernel's bits: integer sums on the integer path,
 // and on the FP64 path its order (thread t of 256 adds tiles t and t + 256,
