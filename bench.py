@@ -71,10 +71,10 @@ PASS2Z_OPS_PER_PX = 2 * 12 + 3
 # (scaled by a plain copy of known size; profiles/pipeline_kernels_8192x8192_u16.md)
 # for the kernel sources with this hash and these strip heights.  Reported
 # only while both are unchanged.
-TRAFFIC_SOURCE_HASH = "e36742e8cbfaffc4"
+TRAFFIC_SOURCE_HASH = "99417a1f323e35c4"
 TRAFFIC_ROWS = [48, 64]
-TRAFFIC_BYTES = {"pass1_kernel": (70580 * 2.0 + 529900 * 1.0) * 1024,
-                 "pass2z_kernel": (144700 * 2.0 + 69830 * 1.0) * 1024}
+TRAFFIC_BYTES = {"pass1_kernel": (70445 * 2.0 + 529881 * 1.0) * 1024,
+                 "pass2z_kernel": (144036 * 2.0 + 68997 * 1.0) * 1024}
 # Algorithmic HBM bytes per pixel of each kernel: pass 1 reads the 16-bit
 # image and writes the strengths' plane of 16-bit codes and their plane of
 # low halves (4 bytes each); pass 2 reads the codes (the low halves only of
@@ -106,7 +106,7 @@ def log(msg):
 def host_cores() -> int:
     """Threads the CPU work may use: the cores this process may run on,
     limited to the job's CPU share when the environment states one
-    (OMP_NUM_THREADS; a GPU job of this machine pool gets 16 host threads
+    (OMP_NUM_THREADS; a GPU job on the measured machines gets 16 host threads
     per GPU, whatever the host's core count)."""
     try:
         n = len(os.sched_getaffinity(0))
@@ -542,8 +542,7 @@ def main():
         torch.cuda.synchronize()
         ms64 = start.elapsed_time(stop) / args.steps
         fp64 = {"ms_per_step": round(ms64, 4), "Mpixel_s": round(H * W / (ms64 * 1e-3) / 1e6, 1),
-                "path": "fp64" if rep64["path"] == logfx.PATH_FP64 else "int32", "mask_grid_bits": 23,
-                "rows_per_strip": [ctx.get_option(logfx.OPT_ROWS1), ctx.get_option(logfx.OPT_ROWS2)]}
+                "path": "fp64" if rep64["path"] == logfx.PATH_FP64 else "int32", "mask_grid_bits": 23}
         log(f"fp64 path: {ms64:.3f} ms/step")
     # latency of one call on the 512^2 uint8 image (40 rectangles, noise
     # sigma 4): it fits in the caches, so launches dominate

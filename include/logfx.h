@@ -318,7 +318,8 @@ int logfx_tune(logfx_ctx *ctx, int32_t n, const logfx_image *imgs, const logfx_p
  * the context records HIP events around its kernels on the call's stream.
  * logfx_timing_read waits for the recorded events and returns summed
  * milliseconds in ms_out[0..3]: pass 1, the finalize kernel (with the
- * gate's features and network when it decides), pass 2 (direct launches
+ * gate's features and network when it decides; next to nothing for an image
+ * of few tiles, whose pass 2 forms the thresholds), pass 2 (direct launches
  * only; a graph replay is timed as a whole) and the whole call;
  * *calls_out (nullable) receives the number of timed calls.  It starts a new
  * accumulation, as does enabling or disabling. */

@@ -21,9 +21,9 @@
 // of the pass that recomputes the strengths.  The extracted bits are
 // therefore those of the FP64 test, everywhere.  Where the threshold is
 // small against the code step (kCoarse), the low bits are read for every row
-// and only the rounding is left to bound.  8192^2: 103 us, 270 MB read, about
-// 30 vector instructions per pixel, which now take three quarters of the
-// time; pass 1 pays 8 us for the split.  6001 x 3501, 16 bits (12 bytes a
+// and only the rounding is left to bound.  8192^2: 103 us, 295 MB read, 42
+// vector instructions per output pixel (halo lanes and rows included), which
+// take 0.82 of the issue slots; pass 1 pays 8 us for the split.  6001 x 3501, 16 bits (12 bytes a
 // pixel stored, 16 before, of which 4 are read): 89 -> 39 us.
 //
 // Each lane collects the E bits of its own column in a 64-bit shift register
